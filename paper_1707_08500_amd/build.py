@@ -10,12 +10,16 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import tempfile
 
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libpsatd.so")
 
+# (source, defines): the kernels are compiled as one translation unit per
+# precision form (psatd_kernels.hip, PSATD_TU), all units at once
+UNITS = [("psatd_api.hip", [])] + [("psatd_kernels.hip", [f"-DPSATD_TU={i}"]) for i in range(5)]
 SOURCES = ["psatd_api.hip", "psatd_kernels.hip"]
 HEADERS = ["fft_engine.hpp", "psatd_device.hpp", "psatd_launch.hpp", "plan_host.hpp", "dft_consts.h",
            "mfma_dft.hpp", "reg_fft.hpp", "zreg.hpp"]
@@ -26,7 +30,6 @@ FLAGS = [
     "-O3",
     "-std=c++17",
     "-fPIC",
-    "-shared",
     # hand-written code only: keep the compiler from forming packed FP32 ops
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall",
@@ -38,14 +41,24 @@ FLAGS = [
 def build(verbose: bool = True) -> str:
     """Compiles every HIP source into libpsatd.so; returns its path."""
     tmp = LIB + ".tmp"
-    cmd = [HIPCC] + FLAGS + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-o", tmp] + \
-        [os.path.join(CSRC, s) for s in SOURCES]
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    res = subprocess.run(cmd, capture_output=True, text=True)
-    if res.returncode != 0:
-        sys.stderr.write(res.stdout + res.stderr)
-        raise RuntimeError("hipcc failed building libpsatd.so")
+    with tempfile.TemporaryDirectory() as obj:
+        jobs, objs = [], []
+        for i, (src, defs) in enumerate(UNITS):
+            objs.append(os.path.join(obj, f"{i}.o"))
+            cmd = [HIPCC] + FLAGS + defs + ["-I", os.path.join(ROOT, "include"), "-I", CSRC, "-c",
+                                            os.path.join(CSRC, src), "-o", objs[-1]]
+            if verbose:
+                print(" ".join(cmd), flush=True)
+            jobs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))
+        outs = [j.communicate()[0] for j in jobs]
+        if not any(j.returncode for j in jobs):
+            res = subprocess.run([HIPCC, "--offload-arch=gfx950", "-shared", "-o", tmp] + objs,
+                                 capture_output=True, text=True)
+            outs.append(res.stdout + res.stderr)
+            jobs.append(res)
+        if any(j.returncode for j in jobs):
+            sys.stderr.write("".join(outs))
+            raise RuntimeError("hipcc failed building libpsatd.so")
     os.replace(tmp, LIB)
     return LIB
 

@@ -158,7 +158,7 @@ __global__ __launch_bounds__(kThreadsXY) void k_gather(ScatterArgs<T> a, int nit
     body_gather(a, item, threadIdx.x, blockDim.x);
 }
 
-__global__ __launch_bounds__(256) void k_modk(const KEntry* ent, int nent, int maxN, int p,
+static __global__ __launch_bounds__(256) void k_modk(const KEntry* ent, int nent, int maxN, int p,
                                               double* kmod) {
   const int e = blockIdx.y;
   if (e >= nent) return;
@@ -191,19 +191,8 @@ static hipError_t set_lds(const void* f, int lds) {
   return hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
 }
 
-// Calls f(std::integral_constant<int, SPL>) for the plan's precision form;
-// the matrix-core forms exist for FP32 data only.
-template <typename T, class F>
-static hipError_t with_spl(int spl, F f) {
-  if constexpr (std::is_same<T, float>::value) {
-    if (spl == 2) return f(std::integral_constant<int, 2>{});
-    if (spl == 3) return f(std::integral_constant<int, 3>{});
-  }
-  return f(std::integral_constant<int, 0>{});
-}
-
 template <typename T, int MAXR, int SPL>
-static hipError_t prepare_t(int ldsF, int ldsI, int ldsU, int ldsX, int ldsY) {
+hipError_t prepare_t(int ldsF, int ldsI, int ldsU, int ldsX, int ldsY) {
   constexpr bool I = IncOf<T>::value;
   const void* xy[] = {(const void*)k_fwd_xy<T, 256, MAXR, SPL>, (const void*)k_fwd_xy<T, 512, MAXR, SPL>,
                       (const void*)k_fwd_xy<T, 1024, MAXR, SPL>};
@@ -239,6 +228,335 @@ static hipError_t prepare_t(int ldsF, int ldsI, int ldsU, int ldsX, int ldsY) {
   return set_lds((const void*)k_y<T, 1, MAXR, SPL>, ldsY);
 }
 
+// ---------------------------------------------------------------- launchers
+// MAXR = 8 kernels exist for the VALU form only.  MR: the pass's largest
+// radix (p.maxr for the x/y passes, p.maxrz for the z passes).
+#define PSATD_MAXR_SWITCH(SPL, MR, CALL8, CALL16) \
+  do {                                             \
+    if constexpr ((SPL) > 0) {                     \
+      CALL16;                                      \
+    } else if ((MR) >= 16) {                       \
+      CALL16;                                      \
+    } else {                                       \
+      CALL8;                                       \
+    }                                              \
+  } while (0)
+
+template <typename T, int NT, int MAXR, int SPL>
+static hipError_t fwd_go(const DevPlan& p, const FwdArgs<T>& a, int g, int lds, int item0, int n,
+                         hipStream_t st) {
+  hipLaunchKernelGGL((k_fwd_xy<T, NT, MAXR, SPL>), dim3(g), dim3(NT), lds, st, a, item0, n, p.xcd);
+  return hipGetLastError();
+}
+
+// One x/y launch of n items from item0 with nt threads per group.
+template <typename T, int SPL, class Go>
+static hipError_t xy_shape(const DevPlan& p, int nt, Go go) {
+  if (nt == 1024)
+    PSATD_MAXR_SWITCH(SPL, p.maxr, return (go.template run<1024, 8, SPL>()), return (go.template run<1024, 16, SPL>()));
+  if (nt == 512)
+    PSATD_MAXR_SWITCH(SPL, p.maxr, return (go.template run<512, 8, SPL>()), return (go.template run<512, 16, SPL>()));
+  PSATD_MAXR_SWITCH(SPL, p.maxr, return (go.template run<256, 8, SPL>()), return (go.template run<256, 16, SPL>()));
+  return hipSuccess;
+}
+
+template <typename T>
+struct FwdGo {
+  const DevPlan& p;
+  const FwdArgs<T>& a;
+  int g, lds, item0, n;
+  hipStream_t st;
+  template <int NT, int MAXR, int SPL>
+  hipError_t run() const { return fwd_go<T, NT, MAXR, SPL>(p, a, g, lds, item0, n, st); }
+};
+
+template <typename T, int SPL>
+hipError_t fwd_t(const DevPlan& p, const Batch& b, void* const* in9, void* spec, hipStream_t st,
+                        bool scalar) {
+  FwdArgs<T> a;
+  a.t = tables<T>(p);
+  a.items = scalar ? p.itemsP : p.itemsF;  // one field: P[2] planes per box
+  a.nfield = scalar ? 1 : 9;
+  a.npull = (p.pull && !scalar) ? 6 : 0;
+  a.pull = p.pullp;
+  a.pull_off = p.pull_off;
+  for (int f = 0; f < 9; ++f) a.in[f] = (f < a.nfield) ? reinterpret_cast<const T*>(in9[f]) : nullptr;
+  a.spec = reinterpret_cast<cx<T>*>(spec);
+  a.sbias = b.sbias;
+  if (p.ntxy == 0) {  // one launch per class of plane size (unbatched plans only)
+    for (int c = 0; c < p.nxyc; ++c) {
+      const XyClass& k = p.xyc[c];
+      a.items = p.itemsXYC + (scalar ? k.P : k.F);
+      const int n = scalar ? k.nP : k.nF;
+      const int g = grid_for(n, p.grid_cap[kPhaseFwd]);
+      if (!g) continue;
+      const hipError_t e = xy_shape<T, SPL>(p, k.nt, FwdGo<T>{p, a, g, k.lds, 0, n, st});
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  const int g = grid_for(b.nF, p.grid_cap[kPhaseFwd]);
+  if (!g) return hipSuccess;
+  return xy_shape<T, SPL>(p, p.ntxy, FwdGo<T>{p, a, g, p.ldsF, b.F0, b.nF, st});
+}
+
+// One z launch: n items from item0, PB pencils per tile, lds bytes of LDS.
+struct UpdLaunch {
+  int g, PB, lds, item0, n;
+};
+
+template <typename T, int NT, int PB, int MAXR, int SPL>
+static hipError_t upd_launch(const DevPlan& p, const UpdLaunch& l, const UpdArgs<T>& a, hipStream_t st) {
+  hipLaunchKernelGGL((k_z_update<T, NT, PB, IncOf<T>::value, MAXR, SPL>), dim3(l.g), dim3(NT), l.lds, st, a,
+                     l.item0, l.n, p.xcd);
+  return hipGetLastError();
+}
+
+template <typename T, int MAXR, int SPL>
+static hipError_t upd_shape(const DevPlan& p, const UpdLaunch& l, const UpdArgs<T>& a, hipStream_t st) {
+  if (l.PB == 4) return upd_launch<T, 512, 4, MAXR, SPL>(p, l, a, st);
+  if (l.PB == 6) return upd_launch<T, 512, 6, MAXR, SPL>(p, l, a, st);
+  if (l.PB == 10) return upd_launch<T, 512, 10, MAXR, SPL>(p, l, a, st);
+  if (p.ntu == 1024)
+    return l.PB == 16 ? upd_launch<T, 1024, 16, MAXR, SPL>(p, l, a, st)
+                      : upd_launch<T, 1024, 8, MAXR, SPL>(p, l, a, st);
+  return l.PB == 16 ? upd_launch<T, 512, 16, MAXR, SPL>(p, l, a, st)
+                    : upd_launch<T, 512, 8, MAXR, SPL>(p, l, a, st);
+}
+
+template <typename T, int SPL>
+hipError_t upd_t(const DevPlan& p, const Batch& b, void* spec, hipStream_t st) {
+  UpdArgs<T> a;
+  a.t = tables<T>(p);
+  a.items = p.itemsU;
+  a.spec = reinterpret_cast<cx<T>*>(spec);
+  a.sbias = b.sbias;
+  a.k.c = p.c;
+  a.k.dt = p.dt;
+  auto go = [&](const UpdLaunch& l) -> hipError_t {
+    PSATD_MAXR_SWITCH(SPL, p.maxrz, return (upd_shape<T, 8, SPL>(p, l, a, st)),
+                      return (upd_shape<T, 16, SPL>(p, l, a, st)));
+    return hipSuccess;
+  };
+  if (p.zcl) {  // one launch per class of tile size (unbatched plans only)
+    for (int c = 0; c < p.nzc; ++c) {
+      const ZClass& k = p.zc[c];
+      a.items = p.itemsZC + k.U;
+      const int g = grid_for(k.nU, p.grid_cap[kPhaseUpd]);
+      if (!g) continue;
+      const hipError_t e = go(UpdLaunch{g, k.PB, k.lds, 0, k.nU});
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  const int g = grid_for(b.nU, p.grid_cap[kPhaseUpd]);
+  if (!g) return hipSuccess;
+  return go(UpdLaunch{g, p.PB, p.ldsU, b.U0, b.nU});
+}
+
+template <typename T, int NT, int MAXR, int SPL>
+static hipError_t inv_go(const DevPlan& p, const InvArgs<T>& a, int g, int lds, int item0, int n,
+                         hipStream_t st) {
+  if (a.push_off)
+    hipLaunchKernelGGL((k_inv_xy<T, IncOf<T>::value, NT, MAXR, SPL, true>), dim3(g), dim3(NT), lds, st, a,
+                       item0, n, p.xcd);
+  else
+    hipLaunchKernelGGL((k_inv_xy<T, IncOf<T>::value, NT, MAXR, SPL, false>), dim3(g), dim3(NT), lds, st, a,
+                       item0, n, p.xcd);
+  return hipGetLastError();
+}
+
+template <typename T>
+struct InvGo {
+  const DevPlan& p;
+  const InvArgs<T>& a;
+  int g, lds, item0, n;
+  hipStream_t st;
+  template <int NT, int MAXR, int SPL>
+  hipError_t run() const { return inv_go<T, NT, MAXR, SPL>(p, a, g, lds, item0, n, st); }
+};
+
+template <typename T, int SPL>
+hipError_t inv_t(const DevPlan& p, const Batch& b, const void* spec, void* const* out6, hipStream_t st,
+                        bool scalar) {
+  InvArgs<T> a;
+  a.t = tables<T>(p);
+  a.items = scalar ? p.itemsN : p.itemsI;  // one field: n[2] planes per box
+  a.spec = reinterpret_cast<const cx<T>*>(spec);
+  a.sbias = b.sbias;
+  for (int f = 0; f < 6; ++f) a.out[f] = (f == 0 || !scalar) ? reinterpret_cast<T*>(out6[f]) : nullptr;
+  a.push = (p.fuse && !scalar) ? p.push : nullptr;
+  a.push_off = (p.fuse && !scalar) ? p.push_off : nullptr;
+  if (p.ntxy == 0) {  // one launch per class of plane size (unbatched plans only)
+    for (int c = 0; c < p.nxyc; ++c) {
+      const XyClass& k = p.xyc[c];
+      a.items = p.itemsXYC + (scalar ? k.N : k.I);
+      const int n = scalar ? k.nN : k.nI;
+      const int g = grid_for(n, p.grid_cap[kPhaseInv]);
+      if (!g) continue;
+      const hipError_t e = xy_shape<T, SPL>(p, k.nt, InvGo<T>{p, a, g, k.lds, 0, n, st});
+      if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+  }
+  const int g = grid_for(b.nI, p.grid_cap[kPhaseInv]);
+  if (!g) return hipSuccess;
+  return xy_shape<T, SPL>(p, p.ntxy, InvGo<T>{p, a, g, p.ldsI, b.I0, b.nI, st});
+}
+
+template <typename T, int SPL>
+hipError_t heat_z_t(const DevPlan& p, void* spec, double D, double dt, hipStream_t st) {
+  HeatArgs<T> a;
+  a.t = tables<T>(p);
+  a.items = p.itemsU;
+  a.spec = reinterpret_cast<cx<T>*>(spec);
+  a.D = D;
+  a.dt = dt;
+  const int g = grid_for(p.nU, p.grid_cap[kPhaseUpd]);
+  if (!g) return hipSuccess;
+  constexpr bool I = IncOf<T>::value;
+  auto go = [&](auto pbc) -> hipError_t {
+    constexpr int PB = decltype(pbc)::value;
+    PSATD_MAXR_SWITCH(SPL, p.maxrz,
+                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsH, st,
+                                         a, p.nU, p.xcd),
+                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsH, st,
+                                         a, p.nU, p.xcd));
+    return hipGetLastError();
+  };
+  if (p.PB == 4) return go(std::integral_constant<int, 4>{});
+  if (p.PB == 6) return go(std::integral_constant<int, 6>{});
+  if (p.PB == 10) return go(std::integral_constant<int, 10>{});
+  if (p.PB == 8) return go(std::integral_constant<int, 8>{});
+  return go(std::integral_constant<int, 16>{});
+}
+
+template <typename T>
+static SplitArgs<T> split_args(const DevPlan& p, void* spec) {
+  SplitArgs<T> a;
+  a.t = tables<T>(p);
+  a.items = nullptr;
+  for (int f = 0; f < 9; ++f) a.in[f] = nullptr;
+  for (int f = 0; f < 6; ++f) a.out[f] = nullptr;
+  a.spec = reinterpret_cast<cx<T>*>(spec);
+  a.sbias = 0;
+  a.push = p.fuse ? p.push : nullptr;
+  a.push_off = p.fuse ? p.push_off : nullptr;
+  return a;
+}
+
+template <typename T, int SPL>
+hipError_t x_fwd_t(const DevPlan& p, void* const* in9, void* spec, hipStream_t st) {
+  SplitArgs<T> a = split_args<T>(p, spec);
+  a.items = p.itemsXF;
+  for (int f = 0; f < 9; ++f) a.in[f] = reinterpret_cast<const T*>(in9[f]);
+  const int g = grid_for(p.nXF, p.grid_cap[kPhaseFwd]);
+  if (!g) return hipSuccess;
+  PSATD_MAXR_SWITCH(SPL, p.maxr,
+                    hipLaunchKernelGGL((k_x_fwd<T, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a,
+                                       p.nXF, p.xcd),
+                    hipLaunchKernelGGL((k_x_fwd<T, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a,
+                                       p.nXF, p.xcd));
+  return hipGetLastError();
+}
+
+template <typename T, int SPL>
+hipError_t y_t(const DevPlan& p, int dir, void* spec, hipStream_t st) {
+  SplitArgs<T> a = split_args<T>(p, spec);
+  a.items = dir < 0 ? p.itemsYF : p.itemsYI;
+  const int n = dir < 0 ? p.nYF : p.nYI;
+  const int g = grid_for(n, p.grid_cap[dir < 0 ? kPhaseFwd : kPhaseInv]);
+  if (!g) return hipSuccess;
+  if (dir < 0)
+    PSATD_MAXR_SWITCH(SPL, p.maxr,
+                      hipLaunchKernelGGL((k_y<T, -1, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
+                                         p.xcd),
+                      hipLaunchKernelGGL((k_y<T, -1, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
+                                         p.xcd));
+  else
+    PSATD_MAXR_SWITCH(SPL, p.maxr,
+                      hipLaunchKernelGGL((k_y<T, 1, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
+                                         p.xcd),
+                      hipLaunchKernelGGL((k_y<T, 1, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
+                                         p.xcd));
+  return hipGetLastError();
+}
+
+template <typename T, int SPL>
+hipError_t x_inv_t(const DevPlan& p, const void* spec, void* const* out6, hipStream_t st) {
+  SplitArgs<T> a = split_args<T>(p, const_cast<void*>(spec));
+  a.items = p.itemsXI;
+  for (int f = 0; f < 6; ++f) a.out[f] = reinterpret_cast<T*>(out6[f]);
+  const int g = grid_for(p.nXI, p.grid_cap[kPhaseInv]);
+  if (!g) return hipSuccess;
+  constexpr bool I = IncOf<T>::value;
+  auto go = [&](auto pc) {
+    constexpr bool PUSH = decltype(pc)::value;
+    PSATD_MAXR_SWITCH(SPL, p.maxr,
+                      hipLaunchKernelGGL((k_x_inv<T, I, 8, SPL, PUSH>), dim3(g), dim3(kThreadsXY), p.ldsX, st,
+                                         a, p.nXI, p.xcd),
+                      hipLaunchKernelGGL((k_x_inv<T, I, 16, SPL, PUSH>), dim3(g), dim3(kThreadsXY), p.ldsX, st,
+                                         a, p.nXI, p.xcd));
+  };
+  if (a.push_off) go(std::true_type{});
+  else go(std::false_type{});
+  return hipGetLastError();
+}
+
+#undef PSATD_MAXR_SWITCH
+
+// The kernels of the four precision forms are instantiated by explicit
+// instantiation definitions, so that the library can be compiled as one
+// translation unit per form in parallel (PSATD_TU 1..4: FP64, FP32, BF16x3,
+// BF16x6; 0: the dispatch below) or, without PSATD_TU, as a whole.
+#define PSATD_FORM(KIND, T, SPL)                                                                              \
+  KIND template hipError_t fwd_t<T, SPL>(const DevPlan&, const Batch&, void* const*, void*, hipStream_t,      \
+                                         bool);                                                               \
+  KIND template hipError_t upd_t<T, SPL>(const DevPlan&, const Batch&, void*, hipStream_t);                   \
+  KIND template hipError_t inv_t<T, SPL>(const DevPlan&, const Batch&, const void*, void* const*, hipStream_t, \
+                                         bool);                                                               \
+  KIND template hipError_t heat_z_t<T, SPL>(const DevPlan&, void*, double, double, hipStream_t);              \
+  KIND template hipError_t x_fwd_t<T, SPL>(const DevPlan&, void* const*, void*, hipStream_t);                 \
+  KIND template hipError_t y_t<T, SPL>(const DevPlan&, int, void*, hipStream_t);                              \
+  KIND template hipError_t x_inv_t<T, SPL>(const DevPlan&, const void*, void* const*, hipStream_t);           \
+  KIND template hipError_t prepare_t<T, 16, SPL>(int, int, int, int, int);
+#define PSATD_FORM_VALU(KIND, T) \
+  PSATD_FORM(KIND, T, 0)         \
+  KIND template hipError_t prepare_t<T, 8, 0>(int, int, int, int, int);
+
+#ifndef PSATD_TU
+#define PSATD_TU -1
+#endif
+#if PSATD_TU == 1 || PSATD_TU < 0
+PSATD_FORM_VALU(, double)
+#else
+PSATD_FORM_VALU(extern, double)
+#endif
+#if PSATD_TU == 2 || PSATD_TU < 0
+PSATD_FORM_VALU(, float)
+#else
+PSATD_FORM_VALU(extern, float)
+#endif
+#if PSATD_TU == 3 || PSATD_TU < 0
+PSATD_FORM(, float, 2)
+#else
+PSATD_FORM(extern, float, 2)
+#endif
+#if PSATD_TU == 4 || PSATD_TU < 0
+PSATD_FORM(, float, 3)
+#else
+PSATD_FORM(extern, float, 3)
+#endif
+
+#if PSATD_TU <= 0
+#define PSATD_BY_FORM(F, ...)                        \
+  do {                                               \
+    if (p.f64) return F<double, 0>(__VA_ARGS__);     \
+    if (p.spl == 2) return F<float, 2>(__VA_ARGS__); \
+    if (p.spl == 3) return F<float, 3>(__VA_ARGS__); \
+    return F<float, 0>(__VA_ARGS__);                 \
+  } while (0)
+
 hipError_t prepare_kernels(bool f64, int spl, int ldsF, int ldsI, int ldsU, int ldsX, int ldsY) {
   hipError_t e;
   if (f64) {
@@ -251,7 +569,36 @@ hipError_t prepare_kernels(bool f64, int spl, int ldsF, int ldsI, int ldsU, int 
   return prepare_t<float, 16, 0>(ldsF, ldsI, ldsU, ldsX, ldsY);
 }
 
-// ---------------------------------------------------------------- launchers
+hipError_t launch_fwd(const DevPlan& p, const Batch& b, void* const* in9, void* spec, hipStream_t st,
+                      bool scalar) {
+  PSATD_BY_FORM(fwd_t, p, b, in9, spec, st, scalar);
+}
+
+hipError_t launch_upd(const DevPlan& p, const Batch& b, void* spec, hipStream_t st) {
+  PSATD_BY_FORM(upd_t, p, b, spec, st);
+}
+
+hipError_t launch_inv(const DevPlan& p, const Batch& b, const void* spec, void* const* out6, hipStream_t st,
+                      bool scalar) {
+  PSATD_BY_FORM(inv_t, p, b, spec, out6, st, scalar);
+}
+
+hipError_t launch_heat_z(const DevPlan& p, void* spec, double D, double dt, hipStream_t st) {
+  PSATD_BY_FORM(heat_z_t, p, spec, D, dt, st);
+}
+
+hipError_t launch_x_fwd(const DevPlan& p, void* const* in9, void* spec, hipStream_t st) {
+  PSATD_BY_FORM(x_fwd_t, p, in9, spec, st);
+}
+
+hipError_t launch_y(const DevPlan& p, int dir, void* spec, hipStream_t st) {
+  PSATD_BY_FORM(y_t, p, dir, spec, st);
+}
+
+hipError_t launch_x_inv(const DevPlan& p, const void* spec, void* const* out6, hipStream_t st) {
+  PSATD_BY_FORM(x_inv_t, p, spec, out6, st);
+}
+
 template <typename T>
 static hipError_t fill_t(const DevPlan& p, void* const* comps, int ncomp, hipStream_t st) {
   FillArgs<T> a;
@@ -290,146 +637,6 @@ hipError_t launch_sum(const DevPlan& p, void* const* J, hipStream_t st) {
   return p.f64 ? sum_t<double>(p, J, st) : sum_t<float>(p, J, st);
 }
 
-// MAXR = 8 kernels exist for the VALU form only.  MR: the pass's largest
-// radix (p.maxr for the x/y passes, p.maxrz for the z passes).
-#define PSATD_MAXR_SWITCH(SPL, MR, CALL8, CALL16) \
-  do {                                             \
-    if constexpr ((SPL) > 0) {                     \
-      CALL16;                                      \
-    } else if ((MR) >= 16) {                       \
-      CALL16;                                      \
-    } else {                                       \
-      CALL8;                                       \
-    }                                              \
-  } while (0)
-
-template <typename T, int NT, int MAXR, int SPL>
-static hipError_t fwd_go(const DevPlan& p, const FwdArgs<T>& a, int g, int lds, int item0, int n,
-                         hipStream_t st) {
-  hipLaunchKernelGGL((k_fwd_xy<T, NT, MAXR, SPL>), dim3(g), dim3(NT), lds, st, a, item0, n, p.xcd);
-  return hipGetLastError();
-}
-
-// One x/y launch of n items from item0 with nt threads per group.
-template <typename T, class Go>
-static hipError_t xy_shape(const DevPlan& p, int nt, Go go) {
-  return with_spl<T>(p.spl, [&](auto sc) -> hipError_t {
-    constexpr int SPL = decltype(sc)::value;
-    if (nt == 1024)
-      PSATD_MAXR_SWITCH(SPL, p.maxr, return (go.template run<1024, 8, SPL>()), return (go.template run<1024, 16, SPL>()));
-    if (nt == 512)
-      PSATD_MAXR_SWITCH(SPL, p.maxr, return (go.template run<512, 8, SPL>()), return (go.template run<512, 16, SPL>()));
-    PSATD_MAXR_SWITCH(SPL, p.maxr, return (go.template run<256, 8, SPL>()), return (go.template run<256, 16, SPL>()));
-    return hipSuccess;
-  });
-}
-
-template <typename T>
-struct FwdGo {
-  const DevPlan& p;
-  const FwdArgs<T>& a;
-  int g, lds, item0, n;
-  hipStream_t st;
-  template <int NT, int MAXR, int SPL>
-  hipError_t run() const { return fwd_go<T, NT, MAXR, SPL>(p, a, g, lds, item0, n, st); }
-};
-
-template <typename T>
-static hipError_t fwd_t(const DevPlan& p, const Batch& b, void* const* in9, void* spec, hipStream_t st,
-                        bool scalar) {
-  FwdArgs<T> a;
-  a.t = tables<T>(p);
-  a.items = scalar ? p.itemsP : p.itemsF;  // one field: P[2] planes per box
-  a.nfield = scalar ? 1 : 9;
-  a.npull = (p.pull && !scalar) ? 6 : 0;
-  a.pull = p.pullp;
-  a.pull_off = p.pull_off;
-  for (int f = 0; f < 9; ++f) a.in[f] = (f < a.nfield) ? reinterpret_cast<const T*>(in9[f]) : nullptr;
-  a.spec = reinterpret_cast<cx<T>*>(spec);
-  a.sbias = b.sbias;
-  if (p.ntxy == 0) {  // one launch per class of plane size (unbatched plans only)
-    for (int c = 0; c < p.nxyc; ++c) {
-      const XyClass& k = p.xyc[c];
-      a.items = p.itemsXYC + (scalar ? k.P : k.F);
-      const int n = scalar ? k.nP : k.nF;
-      const int g = grid_for(n, p.grid_cap[kPhaseFwd]);
-      if (!g) continue;
-      const hipError_t e = xy_shape<T>(p, k.nt, FwdGo<T>{p, a, g, k.lds, 0, n, st});
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  const int g = grid_for(b.nF, p.grid_cap[kPhaseFwd]);
-  if (!g) return hipSuccess;
-  return xy_shape<T>(p, p.ntxy, FwdGo<T>{p, a, g, p.ldsF, b.F0, b.nF, st});
-}
-
-hipError_t launch_fwd(const DevPlan& p, const Batch& b, void* const* in9, void* spec, hipStream_t st,
-                      bool scalar) {
-  return p.f64 ? fwd_t<double>(p, b, in9, spec, st, scalar) : fwd_t<float>(p, b, in9, spec, st, scalar);
-}
-
-// One z launch: n items from item0, PB pencils per tile, lds bytes of LDS.
-struct UpdLaunch {
-  int g, PB, lds, item0, n;
-};
-
-template <typename T, int NT, int PB, int MAXR, int SPL>
-static hipError_t upd_launch(const DevPlan& p, const UpdLaunch& l, const UpdArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL((k_z_update<T, NT, PB, IncOf<T>::value, MAXR, SPL>), dim3(l.g), dim3(NT), l.lds, st, a,
-                     l.item0, l.n, p.xcd);
-  return hipGetLastError();
-}
-
-template <typename T, int MAXR, int SPL>
-static hipError_t upd_shape(const DevPlan& p, const UpdLaunch& l, const UpdArgs<T>& a, hipStream_t st) {
-  if (l.PB == 4) return upd_launch<T, 512, 4, MAXR, SPL>(p, l, a, st);
-  if (l.PB == 6) return upd_launch<T, 512, 6, MAXR, SPL>(p, l, a, st);
-  if (l.PB == 10) return upd_launch<T, 512, 10, MAXR, SPL>(p, l, a, st);
-  if (p.ntu == 1024)
-    return l.PB == 16 ? upd_launch<T, 1024, 16, MAXR, SPL>(p, l, a, st)
-                      : upd_launch<T, 1024, 8, MAXR, SPL>(p, l, a, st);
-  return l.PB == 16 ? upd_launch<T, 512, 16, MAXR, SPL>(p, l, a, st)
-                    : upd_launch<T, 512, 8, MAXR, SPL>(p, l, a, st);
-}
-
-template <typename T>
-static hipError_t upd_t(const DevPlan& p, const Batch& b, void* spec, hipStream_t st) {
-  UpdArgs<T> a;
-  a.t = tables<T>(p);
-  a.items = p.itemsU;
-  a.spec = reinterpret_cast<cx<T>*>(spec);
-  a.sbias = b.sbias;
-  a.k.c = p.c;
-  a.k.dt = p.dt;
-  auto go = [&](const UpdLaunch& l) -> hipError_t {
-    return with_spl<T>(p.spl, [&](auto sc) -> hipError_t {
-      constexpr int SPL = decltype(sc)::value;
-      PSATD_MAXR_SWITCH(SPL, p.maxrz, return (upd_shape<T, 8, SPL>(p, l, a, st)),
-                        return (upd_shape<T, 16, SPL>(p, l, a, st)));
-      return hipSuccess;
-    });
-  };
-  if (p.zcl) {  // one launch per class of tile size (unbatched plans only)
-    for (int c = 0; c < p.nzc; ++c) {
-      const ZClass& k = p.zc[c];
-      a.items = p.itemsZC + k.U;
-      const int g = grid_for(k.nU, p.grid_cap[kPhaseUpd]);
-      if (!g) continue;
-      const hipError_t e = go(UpdLaunch{g, k.PB, k.lds, 0, k.nU});
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  const int g = grid_for(b.nU, p.grid_cap[kPhaseUpd]);
-  if (!g) return hipSuccess;
-  return go(UpdLaunch{g, p.PB, p.ldsU, b.U0, b.nU});
-}
-
-hipError_t launch_upd(const DevPlan& p, const Batch& b, void* spec, hipStream_t st) {
-  return p.f64 ? upd_t<double>(p, b, spec, st) : upd_t<float>(p, b, spec, st);
-}
-
 template <int N, int L, int W, int MINW>
 static hipError_t zreg_go(const UpdArgs<float>& a, const int32_t* items, int n, int cap, int remap,
                           hipStream_t st) {
@@ -464,188 +671,6 @@ hipError_t launch_upd_reg(const DevPlan& p, void* spec, hipStream_t st) {
     if (e != hipSuccess) return e;
   }
   return hipSuccess;
-}
-
-template <typename T, int NT, int MAXR, int SPL>
-static hipError_t inv_go(const DevPlan& p, const InvArgs<T>& a, int g, int lds, int item0, int n,
-                         hipStream_t st) {
-  if (a.push_off)
-    hipLaunchKernelGGL((k_inv_xy<T, IncOf<T>::value, NT, MAXR, SPL, true>), dim3(g), dim3(NT), lds, st, a,
-                       item0, n, p.xcd);
-  else
-    hipLaunchKernelGGL((k_inv_xy<T, IncOf<T>::value, NT, MAXR, SPL, false>), dim3(g), dim3(NT), lds, st, a,
-                       item0, n, p.xcd);
-  return hipGetLastError();
-}
-
-template <typename T>
-struct InvGo {
-  const DevPlan& p;
-  const InvArgs<T>& a;
-  int g, lds, item0, n;
-  hipStream_t st;
-  template <int NT, int MAXR, int SPL>
-  hipError_t run() const { return inv_go<T, NT, MAXR, SPL>(p, a, g, lds, item0, n, st); }
-};
-
-template <typename T>
-static hipError_t inv_t(const DevPlan& p, const Batch& b, const void* spec, void* const* out6, hipStream_t st,
-                        bool scalar) {
-  InvArgs<T> a;
-  a.t = tables<T>(p);
-  a.items = scalar ? p.itemsN : p.itemsI;  // one field: n[2] planes per box
-  a.spec = reinterpret_cast<const cx<T>*>(spec);
-  a.sbias = b.sbias;
-  for (int f = 0; f < 6; ++f) a.out[f] = (f == 0 || !scalar) ? reinterpret_cast<T*>(out6[f]) : nullptr;
-  a.push = (p.fuse && !scalar) ? p.push : nullptr;
-  a.push_off = (p.fuse && !scalar) ? p.push_off : nullptr;
-  if (p.ntxy == 0) {  // one launch per class of plane size (unbatched plans only)
-    for (int c = 0; c < p.nxyc; ++c) {
-      const XyClass& k = p.xyc[c];
-      a.items = p.itemsXYC + (scalar ? k.N : k.I);
-      const int n = scalar ? k.nN : k.nI;
-      const int g = grid_for(n, p.grid_cap[kPhaseInv]);
-      if (!g) continue;
-      const hipError_t e = xy_shape<T>(p, k.nt, InvGo<T>{p, a, g, k.lds, 0, n, st});
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  const int g = grid_for(b.nI, p.grid_cap[kPhaseInv]);
-  if (!g) return hipSuccess;
-  return xy_shape<T>(p, p.ntxy, InvGo<T>{p, a, g, p.ldsI, b.I0, b.nI, st});
-}
-
-hipError_t launch_inv(const DevPlan& p, const Batch& b, const void* spec, void* const* out6, hipStream_t st,
-                      bool scalar) {
-  return p.f64 ? inv_t<double>(p, b, spec, out6, st, scalar) : inv_t<float>(p, b, spec, out6, st, scalar);
-}
-
-template <typename T>
-static hipError_t heat_z_t(const DevPlan& p, void* spec, double D, double dt, hipStream_t st) {
-  HeatArgs<T> a;
-  a.t = tables<T>(p);
-  a.items = p.itemsU;
-  a.spec = reinterpret_cast<cx<T>*>(spec);
-  a.D = D;
-  a.dt = dt;
-  const int g = grid_for(p.nU, p.grid_cap[kPhaseUpd]);
-  if (!g) return hipSuccess;
-  constexpr bool I = IncOf<T>::value;
-  return with_spl<T>(p.spl, [&](auto sc) -> hipError_t {
-    constexpr int SPL = decltype(sc)::value;
-    auto go = [&](auto pbc) -> hipError_t {
-      constexpr int PB = decltype(pbc)::value;
-      PSATD_MAXR_SWITCH(SPL, p.maxrz,
-                        hipLaunchKernelGGL((k_z_heat<T, PB, I, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsH, st,
-                                           a, p.nU, p.xcd),
-                        hipLaunchKernelGGL((k_z_heat<T, PB, I, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsH, st,
-                                           a, p.nU, p.xcd));
-      return hipGetLastError();
-    };
-    if (p.PB == 4) return go(std::integral_constant<int, 4>{});
-    if (p.PB == 6) return go(std::integral_constant<int, 6>{});
-    if (p.PB == 10) return go(std::integral_constant<int, 10>{});
-    if (p.PB == 8) return go(std::integral_constant<int, 8>{});
-    return go(std::integral_constant<int, 16>{});
-  });
-}
-
-hipError_t launch_heat_z(const DevPlan& p, void* spec, double D, double dt, hipStream_t st) {
-  return p.f64 ? heat_z_t<double>(p, spec, D, dt, st) : heat_z_t<float>(p, spec, D, dt, st);
-}
-
-template <typename T>
-static SplitArgs<T> split_args(const DevPlan& p, void* spec) {
-  SplitArgs<T> a;
-  a.t = tables<T>(p);
-  a.items = nullptr;
-  for (int f = 0; f < 9; ++f) a.in[f] = nullptr;
-  for (int f = 0; f < 6; ++f) a.out[f] = nullptr;
-  a.spec = reinterpret_cast<cx<T>*>(spec);
-  a.sbias = 0;
-  a.push = p.fuse ? p.push : nullptr;
-  a.push_off = p.fuse ? p.push_off : nullptr;
-  return a;
-}
-
-template <typename T>
-static hipError_t x_fwd_t(const DevPlan& p, void* const* in9, void* spec, hipStream_t st) {
-  SplitArgs<T> a = split_args<T>(p, spec);
-  a.items = p.itemsXF;
-  for (int f = 0; f < 9; ++f) a.in[f] = reinterpret_cast<const T*>(in9[f]);
-  const int g = grid_for(p.nXF, p.grid_cap[kPhaseFwd]);
-  if (!g) return hipSuccess;
-  return with_spl<T>(p.spl, [&](auto sc) -> hipError_t {
-    constexpr int SPL = decltype(sc)::value;
-    PSATD_MAXR_SWITCH(SPL, p.maxr,
-                      hipLaunchKernelGGL((k_x_fwd<T, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a,
-                                         p.nXF, p.xcd),
-                      hipLaunchKernelGGL((k_x_fwd<T, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a,
-                                         p.nXF, p.xcd));
-    return hipGetLastError();
-  });
-}
-
-template <typename T>
-static hipError_t y_t(const DevPlan& p, int dir, void* spec, hipStream_t st) {
-  SplitArgs<T> a = split_args<T>(p, spec);
-  a.items = dir < 0 ? p.itemsYF : p.itemsYI;
-  const int n = dir < 0 ? p.nYF : p.nYI;
-  const int g = grid_for(n, p.grid_cap[dir < 0 ? kPhaseFwd : kPhaseInv]);
-  if (!g) return hipSuccess;
-  return with_spl<T>(p.spl, [&](auto sc) -> hipError_t {
-    constexpr int SPL = decltype(sc)::value;
-    if (dir < 0)
-      PSATD_MAXR_SWITCH(SPL, p.maxr,
-                        hipLaunchKernelGGL((k_y<T, -1, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
-                                           p.xcd),
-                        hipLaunchKernelGGL((k_y<T, -1, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
-                                           p.xcd));
-    else
-      PSATD_MAXR_SWITCH(SPL, p.maxr,
-                        hipLaunchKernelGGL((k_y<T, 1, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
-                                           p.xcd),
-                        hipLaunchKernelGGL((k_y<T, 1, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
-                                           p.xcd));
-    return hipGetLastError();
-  });
-}
-
-template <typename T>
-static hipError_t x_inv_t(const DevPlan& p, const void* spec, void* const* out6, hipStream_t st) {
-  SplitArgs<T> a = split_args<T>(p, const_cast<void*>(spec));
-  a.items = p.itemsXI;
-  for (int f = 0; f < 6; ++f) a.out[f] = reinterpret_cast<T*>(out6[f]);
-  const int g = grid_for(p.nXI, p.grid_cap[kPhaseInv]);
-  if (!g) return hipSuccess;
-  constexpr bool I = IncOf<T>::value;
-  return with_spl<T>(p.spl, [&](auto sc) -> hipError_t {
-    constexpr int SPL = decltype(sc)::value;
-    auto go = [&](auto pc) {
-      constexpr bool PUSH = decltype(pc)::value;
-      PSATD_MAXR_SWITCH(SPL, p.maxr,
-                        hipLaunchKernelGGL((k_x_inv<T, I, 8, SPL, PUSH>), dim3(g), dim3(kThreadsXY), p.ldsX, st,
-                                           a, p.nXI, p.xcd),
-                        hipLaunchKernelGGL((k_x_inv<T, I, 16, SPL, PUSH>), dim3(g), dim3(kThreadsXY), p.ldsX, st,
-                                           a, p.nXI, p.xcd));
-    };
-    if (a.push_off) go(std::true_type{});
-    else go(std::false_type{});
-    return hipGetLastError();
-  });
-}
-
-#undef PSATD_MAXR_SWITCH
-
-hipError_t launch_x_fwd(const DevPlan& p, void* const* in9, void* spec, hipStream_t st) {
-  return p.f64 ? x_fwd_t<double>(p, in9, spec, st) : x_fwd_t<float>(p, in9, spec, st);
-}
-hipError_t launch_y(const DevPlan& p, int dir, void* spec, hipStream_t st) {
-  return p.f64 ? y_t<double>(p, dir, spec, st) : y_t<float>(p, dir, spec, st);
-}
-hipError_t launch_x_inv(const DevPlan& p, const void* spec, void* const* out6, hipStream_t st) {
-  return p.f64 ? x_inv_t<double>(p, spec, out6, st) : x_inv_t<float>(p, spec, out6, st);
 }
 
 template <typename T>
@@ -684,5 +709,7 @@ hipError_t launch_modk(const KEntry* entries, int nent, int maxN, int order_p, d
   hipLaunchKernelGGL(k_modk, dim3(bx, nent), dim3(256), 0, st, entries, nent, maxN, order_p, kmod);
   return hipGetLastError();
 }
+
+#endif  // PSATD_TU <= 0
 
 }  // namespace psatd
