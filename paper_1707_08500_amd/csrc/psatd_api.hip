@@ -70,7 +70,8 @@ struct psatd_plan_s {
   hipStream_t cap_stream = nullptr;
   int device = 0;
   void* blob = nullptr;  // device tables
-  int32_t* d_itemsU = nullptr;  // z-update work list (depends on the z tile)
+  void* lists = nullptr;  // device work lists (they depend on the knobs)
+  size_t lists_bytes = 0;
   int32_t tune[PSATD_NTUNE] = {0, 1, 0, 0, 0, 0, 0, 16, 256, 512, 0, 1, 0, 0};
   void* ws = nullptr;
   int64_t ws_bytes = 0;
@@ -140,6 +141,50 @@ psatd_status ensure_workspace(psatd_plan_t p) {
   return PSATD_OK;
 }
 
+// Builds the work lists for the plan's current knobs and uploads them.  Boxes
+// share the planes of their columns in an unbatched plan, except under the
+// register z pass, which addresses each box's own 9 fields.
+psatd_status upload_lists(psatd_plan_t p) {
+  HostTables& h = p->h;
+  DevPlan& d = p->dp;
+  std::vector<unsigned char> hb;
+  size_t off[5];
+  try {
+    const bool one = h.batches.size() == 1;
+    build_lists(h, one && !d.zreg, d.ntxy == 0 && !h.split && one, d.zcl && one);
+    const WorkLists& w = h.lists;
+    size_t total = 0;
+    auto put = [&](int i, const void* src, size_t bytes) {
+      off[i] = total;
+      total += (bytes + 255) & ~(size_t)255;
+      hb.resize(total);
+      if (bytes) std::memcpy(hb.data() + off[i], src, bytes);
+    };
+    put(0, w.box.data(), w.box.size() * sizeof(BoxD));
+    put(1, w.pull.data(), w.pull.size() * sizeof(PullPiece));
+    put(2, w.fwd.data(), w.fwd.size() * sizeof(PlaneRec));
+    put(3, w.inv.data(), w.inv.size() * sizeof(PlaneRec));
+    put(4, w.tiles.data(), w.tiles.size() * sizeof(ZItem));
+  } catch (...) {
+    return fail(p, PSATD_E_NOMEM, "host allocation failed");
+  }
+  if (hb.size() > p->lists_bytes) {
+    void* fresh = nullptr;
+    HIPCHK(p, hipMalloc(&fresh, hb.size()));
+    if (p->lists) (void)hipFree(p->lists);
+    p->lists = fresh;
+    p->lists_bytes = hb.size();
+  }
+  HIPCHK(p, hipMemcpy(p->lists, hb.data(), hb.size(), hipMemcpyHostToDevice));
+  unsigned char* base = reinterpret_cast<unsigned char*>(p->lists);
+  d.box = reinterpret_cast<const BoxD*>(base + off[0]);
+  d.pullp = reinterpret_cast<const PullPiece*>(base + off[1]);
+  d.fwd = reinterpret_cast<const PlaneRec*>(base + off[2]);
+  d.inv = reinterpret_cast<const PlaneRec*>(base + off[3]);
+  d.tiles = reinterpret_cast<const ZItem*>(base + off[4]);
+  return PSATD_OK;
+}
+
 bool aligned16(const void* q) { return ((uintptr_t)q & 15u) == 0; }
 
 psatd_status check_fields(psatd_plan_t p, void* const* v, int count, const char* what) {
@@ -189,27 +234,35 @@ psatd_status enqueue_step(psatd_plan_t p, void* const E[3], void* const B[3], vo
     HIPCHK(p, launch_fill(d, J, 3, st));
     PSATD_MARK(kPhaseExchJ, false);
   }
-  for (const Batch& b : p->h.batches) {
+  const int npull = d.pull ? 6 : 0;
+  const WorkLists& w = p->h.lists;
+  for (size_t bi = 0; bi < p->h.batches.size(); ++bi) {
+    const int64_t sbias = p->h.batches[bi].sbias;
     PSATD_MARK(kPhaseFwd, true);
-    if (d.split) {
-      HIPCHK(p, launch_x_fwd(d, in9, ws, st));
-      HIPCHK(p, launch_y(d, -1, ws, st));
-    } else {
-      HIPCHK(p, launch_fwd(d, b, in9, ws, st));
+    for (const XyLaunch& l : w.xy[bi]) {
+      if (d.split) {
+        HIPCHK(p, launch_x_fwd(d, l, in9, 9, ws, st));
+        HIPCHK(p, launch_y(d, l, -1, 9, ws, st));
+      } else {
+        HIPCHK(p, launch_fwd(d, l, sbias, in9, 9, npull, ws, st));
+      }
     }
     PSATD_MARK(kPhaseFwd, false);
     PSATD_MARK(kPhaseUpd, true);
-    if (d.zreg && p->h.batches.size() == 1)
+    if (d.zreg && p->h.batches.size() == 1) {
       HIPCHK(p, launch_upd_reg(d, ws, st));
-    else
-      HIPCHK(p, launch_upd(d, b, ws, st));
+    } else {
+      for (const ZLaunch& l : w.z[bi]) HIPCHK(p, launch_upd(d, l, sbias, ws, st));
+    }
     PSATD_MARK(kPhaseUpd, false);
     PSATD_MARK(kPhaseInv, true);
-    if (d.split) {
-      HIPCHK(p, launch_y(d, 1, ws, st));
-      HIPCHK(p, launch_x_inv(d, ws, eb, st));
-    } else {
-      HIPCHK(p, launch_inv(d, b, ws, eb, st));
+    for (const XyLaunch& l : w.xy[bi]) {
+      if (d.split) {
+        HIPCHK(p, launch_y(d, l, 1, 6, ws, st));
+        HIPCHK(p, launch_x_inv(d, l, ws, eb, st));
+      } else {
+        HIPCHK(p, launch_inv(d, l, sbias, ws, eb, 6, st));
+      }
     }
     PSATD_MARK(kPhaseInv, false);
   }
@@ -220,10 +273,10 @@ psatd_status enqueue_step(psatd_plan_t p, void* const E[3], void* const B[3], vo
   return PSATD_OK;
 }
 
-// LDS of the heat z pass: PB staged pencils, the z twiddles and z indices.
-int32_t heat_lds(const HostTables& h) {
+// LDS of a heat z tile of PB pencils: the staged field, the z twiddles and z indices.
+int32_t heat_lds(const HostTables& h, int PB) {
   const int maxPz = max_padded_z(h);
-  return (int32_t)((int64_t)maxPz * (h.PB + 1) * (int64_t)(2 * real_size(h.prec)) + (int64_t)maxPz * 4);
+  return (int32_t)((int64_t)maxPz * (PB + 1) * (int64_t)(2 * real_size(h.prec)) + (int64_t)maxPz * 4);
 }
 
 psatd_status check_step_args(psatd_plan_t p, void* const E[3], void* const B[3], void* const J[3]) {
@@ -305,36 +358,24 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
     total += (bytes + 255) & ~(size_t)255;
     return off;
   };
-  const size_t o_box = reserve(h.box.size() * sizeof(BoxD));
   const size_t o_plan = reserve(h.plans.size() * sizeof(FftPlanD));
   const size_t o_tw = reserve(h.twr.size() * cs);
   const size_t o_kmod = reserve((size_t)h.kmod_len * 8);
   const size_t o_kent = reserve(h.kent.size() * sizeof(KEntry));
   const size_t o_nbo = reserve(h.nbr_off.size() * 4);
   const size_t o_nbr = reserve(std::max<size_t>(h.nbr.size(), 1) * 4);
-  const size_t o_iF = reserve(h.itemsF.size() * 4);
-  const size_t o_iI = reserve(h.itemsI.size() * 4);
   const size_t o_iP = reserve(h.itemsP.size() * 4);
   const size_t o_iN = reserve(h.itemsN.size() * 4);
-  const size_t o_iXF = reserve(h.itemsXF.size() * 4);
-  const size_t o_iYF = reserve(h.itemsYF.size() * 4);
-  const size_t o_iYI = reserve(h.itemsYI.size() * 4);
-  const size_t o_iXI = reserve(h.itemsXI.size() * 4);
   const size_t o_push = reserve(std::max<size_t>(h.push.size(), 1) * sizeof(PushBlk));
   const size_t o_pof = reserve(h.push_off.size() * 4);
   const size_t o_iG = reserve(h.itemsG.size() * 4);
   const size_t o_fp = reserve(std::max<size_t>(h.fillp.size(), 1) * sizeof(FillPiece));
   const size_t o_pOf = reserve(std::max<size_t>(h.pieceOf.size(), 1) * 4);
   const size_t o_iZR = reserve(std::max<size_t>(h.itemsZR.size(), 1) * 4);
-  const size_t o_pull = reserve(std::max<size_t>(h.pullp.size(), 1) * sizeof(PullPiece));
-  const size_t o_poff = reserve(h.pull_off.size() * 4);
-  const size_t o_xyc = reserve(std::max<size_t>(h.itemsXYC.size(), 1) * 4);
-  const size_t o_zc = reserve(std::max<size_t>(h.itemsZC.size(), 1) * 4);
   std::vector<unsigned char> hb(total, 0);
   auto put = [&](size_t off, const void* src, size_t bytes) {
     if (bytes) std::memcpy(hb.data() + off, src, bytes);
   };
-  put(o_box, h.box.data(), h.box.size() * sizeof(BoxD));
   put(o_plan, h.plans.data(), h.plans.size() * sizeof(FftPlanD));
   {
     const std::vector<unsigned char> t = device_twiddles(h);
@@ -343,30 +384,17 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   put(o_kent, h.kent.data(), h.kent.size() * sizeof(KEntry));
   put(o_nbo, h.nbr_off.data(), h.nbr_off.size() * 4);
   put(o_nbr, h.nbr.data(), h.nbr.size() * 4);
-  put(o_iF, h.itemsF.data(), h.itemsF.size() * 4);
-  put(o_iI, h.itemsI.data(), h.itemsI.size() * 4);
   put(o_iP, h.itemsP.data(), h.itemsP.size() * 4);
   put(o_iN, h.itemsN.data(), h.itemsN.size() * 4);
-  put(o_iXF, h.itemsXF.data(), h.itemsXF.size() * 4);
-  put(o_iYF, h.itemsYF.data(), h.itemsYF.size() * 4);
-  put(o_iYI, h.itemsYI.data(), h.itemsYI.size() * 4);
-  put(o_iXI, h.itemsXI.data(), h.itemsXI.size() * 4);
   put(o_push, h.push.data(), h.push.size() * sizeof(PushBlk));
   put(o_pof, h.push_off.data(), h.push_off.size() * 4);
   put(o_iG, h.itemsG.data(), h.itemsG.size() * 4);
   put(o_fp, h.fillp.data(), h.fillp.size() * sizeof(FillPiece));
   put(o_pOf, h.pieceOf.data(), h.pieceOf.size() * 4);
   put(o_iZR, h.itemsZR.data(), h.itemsZR.size() * 4);
-  put(o_pull, h.pullp.data(), h.pullp.size() * sizeof(PullPiece));
-  put(o_poff, h.pull_off.data(), h.pull_off.size() * 4);
-  put(o_xyc, h.itemsXYC.data(), h.itemsXYC.size() * 4);
-  put(o_zc, h.itemsZC.data(), h.itemsZC.size() * 4);
   if ((e = hipMalloc(&p->blob, total)) != hipSuccess) return hipfail(e, "hipMalloc(tables)");
   if ((e = hipMemcpy(p->blob, hb.data(), total, hipMemcpyHostToDevice)) != hipSuccess)
     return hipfail(e, "hipMemcpy(tables)");
-  if ((e = hipMalloc(&p->d_itemsU, h.itemsU.size() * 4)) != hipSuccess) return hipfail(e, "hipMalloc(work list)");
-  if ((e = hipMemcpy(p->d_itemsU, h.itemsU.data(), h.itemsU.size() * 4, hipMemcpyHostToDevice)) != hipSuccess)
-    return hipfail(e, "hipMemcpy(work list)");
   // boxes of several tile sizes: one z launch per class (z_pencils 0)
   p->tune[PSATD_TUNE_Z_PENCILS] = h.zcls.empty() ? h.PB : 0;
   p->tune[PSATD_TUNE_MAX_RADIX] = h.maxr;
@@ -389,25 +417,13 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   d.f64 = f64;
   d.nsub = h.nsub;
   for (int u = 0; u < 3; ++u) d.N[u] = (int32_t)h.N[u];
-  d.box = reinterpret_cast<const BoxD*>(B + o_box);
   d.plans = reinterpret_cast<const FftPlanD*>(B + o_plan);
   d.tw = B + o_tw;
   d.kmod = reinterpret_cast<const double*>(B + o_kmod);
   d.nbr_off = reinterpret_cast<const int32_t*>(B + o_nbo);
   d.nbr = reinterpret_cast<const int32_t*>(B + o_nbr);
-  d.itemsF = reinterpret_cast<const int32_t*>(B + o_iF);
-  d.itemsU = p->d_itemsU;
-  d.itemsI = reinterpret_cast<const int32_t*>(B + o_iI);
   d.itemsP = reinterpret_cast<const int32_t*>(B + o_iP);
   d.itemsN = reinterpret_cast<const int32_t*>(B + o_iN);
-  d.itemsXF = reinterpret_cast<const int32_t*>(B + o_iXF);
-  d.itemsYF = reinterpret_cast<const int32_t*>(B + o_iYF);
-  d.itemsYI = reinterpret_cast<const int32_t*>(B + o_iYI);
-  d.itemsXI = reinterpret_cast<const int32_t*>(B + o_iXI);
-  d.nXF = h.itemsXF.back();
-  d.nYF = h.itemsYF.back();
-  d.nYI = h.itemsYI.back();
-  d.nXI = h.itemsXI.back();
   d.ldsX = h.ldsX;
   d.ldsY = h.ldsY;
   d.split = h.split ? 1 : 0;
@@ -422,8 +438,6 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   d.nzg = (int32_t)h.zgroups.size();
   for (int i = 0; i < d.nzg; ++i) d.zg[i] = h.zgroups[i];
   d.zreg = 0;  // opt-in: measured slower than the LDS-staged z pass on 96^3 and 176^3 boxes
-  d.pullp = reinterpret_cast<const PullPiece*>(B + o_pull);
-  d.pull_off = reinterpret_cast<const int32_t*>(B + o_poff);
 
   p->tune[PSATD_TUNE_Z_REG] = d.zreg;
   d.fuse = (h.fuse_eb && h.batches.size() == 1) ? 1 : 0;
@@ -431,31 +445,21 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   p->tune[PSATD_TUNE_FUSE_EB] = d.fuse;
   d.pull = (!h.split && !d.fuse && h.batches.size() == 1) ? 1 : 0;
   p->tune[PSATD_TUNE_PULL_EB] = d.pull;
-  d.nF = h.itemsF.back();
-  d.nU = h.itemsU.back();
-  d.nI = h.itemsI.back();
   d.nP = h.itemsP.back();
   d.nN = h.itemsN.back();
-  d.ldsF = h.ldsF;
-  d.ldsI = h.ldsI;
-  d.ldsU = h.ldsU;
-  d.PB = h.PB;
   d.zcl = h.zcls.empty() ? 0 : 1;
-  d.nzc = (int32_t)h.zcls.size();
-  for (int i = 0; i < d.nzc; ++i) d.zc[i] = h.zcls[i];
-  d.itemsZC = reinterpret_cast<const int32_t*>(B + o_zc);
-  d.ldsH = heat_lds(h);
   d.ntu = h.ntu;
   d.ntxy = p->tune[PSATD_TUNE_XY_THREADS];
-  d.nxyc = (int32_t)h.xyc.size();
-  for (int i = 0; i < d.nxyc; ++i) d.xyc[i] = h.xyc[i];
-  d.itemsXYC = reinterpret_cast<const int32_t*>(B + o_xyc);
   d.maxr = h.maxr;
   d.maxrz = h.maxrz;
   d.xcd = 1;
-  d.slab = h.batch_slab;
   d.c = h.c;
   d.dt = h.dt;
+  if ((st = upload_lists(p)) != PSATD_OK) {
+    const std::string m = p->err;
+    psatd_destroy(p);
+    return fail(nullptr, st, m);
+  }
   *out = p;
   return PSATD_OK;
 }
@@ -465,7 +469,7 @@ void psatd_destroy(psatd_plan_t p) {
   drop_graphs(p);
   if (p->ws_owned && p->ws) (void)hipFree(p->ws);
   if (p->blob) (void)hipFree(p->blob);
-  if (p->d_itemsU) (void)hipFree(p->d_itemsU);
+  if (p->lists) (void)hipFree(p->lists);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
   delete p;
 }
@@ -576,13 +580,13 @@ psatd_status psatd_heat_run(psatd_plan_t p, void* u, double diffusivity, int32_t
   if (p->h.batches.size() != 1) return fail(p, PSATD_E_STATE, "the heat step needs all boxes in one batch");
   if ((r = ensure_workspace(p)) != PSATD_OK) return r;
   const DevPlan& d = p->dp;
-  const Batch all{0, d.nsub, 0, d.nP, 0, d.nU, 0, d.nN, 0};
   void* in9[9] = {u, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   void* out6[6] = {u, nullptr, nullptr, nullptr, nullptr, nullptr};
   for (int i = 0; i < nsteps; ++i) {
-    HIPCHK(p, launch_fwd(d, all, in9, p->ws, p->stream, true));
-    HIPCHK(p, launch_heat_z(d, p->ws, diffusivity, d.dt, p->stream));
-    HIPCHK(p, launch_inv(d, all, p->ws, out6, p->stream, true));
+    for (const XyLaunch& l : p->h.lists.xy[0]) HIPCHK(p, launch_fwd(d, l, 0, in9, 1, 0, p->ws, p->stream));
+    for (const ZLaunch& l : p->h.lists.z[0])
+      HIPCHK(p, launch_heat_z(d, l, heat_lds(p->h, l.PB), p->ws, diffusivity, d.dt, p->stream));
+    for (const XyLaunch& l : p->h.lists.xy[0]) HIPCHK(p, launch_inv(d, l, 0, p->ws, out6, 1, p->stream));
     HIPCHK(p, launch_fill(d, out6, 1, p->stream));
   }
   return PSATD_OK;
@@ -676,6 +680,7 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
   if (!p) return fail(nullptr, PSATD_E_INVALID, "null plan");
   if (key < 0 || key >= PSATD_NTUNE) return fail(p, PSATD_E_INVALID, "unknown tuning key");
   DevPlan& d = p->dp;
+  bool relist = false;  // the work lists follow the knob
   switch (key) {
     case PSATD_TUNE_Z_PENCILS: {
       if (value == 0) {  // one launch per class of tile size
@@ -683,6 +688,7 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
           return fail(p, PSATD_E_INVALID,
                       "per-class z launches need an unbatched plan whose boxes take several tile sizes");
         d.zcl = 1;
+        relist = true;
         break;
       }
       if (value != 4 && value != 6 && value != 8 && value != 10 && value != 16)
@@ -691,13 +697,9 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
         return fail(p, PSATD_E_INVALID, "z tile does not fit the LDS");
       HIPCHK(p, hipStreamSynchronize(p->stream));
       set_z_tile(p->h, value);
-      HIPCHK(p, hipMemcpy(p->d_itemsU, p->h.itemsU.data(), p->h.itemsU.size() * 4, hipMemcpyHostToDevice));
       HIPCHK(p, prepare_kernels(d.f64, d.spl, p->h.ldsF, p->h.ldsI, z_lds_max(p->h), p->h.ldsX, p->h.ldsY));
       d.zcl = 0;
-      d.PB = p->h.PB;
-      d.ldsU = p->h.ldsU;
-      d.ldsH = heat_lds(p->h);
-      d.nU = p->h.itemsU.back();
+      relist = true;
       break;
     }
     case PSATD_TUNE_SPLIT_XY: {
@@ -706,6 +708,7 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
       if (value && p->h.batches.size() > 1) return fail(p, PSATD_E_INVALID, "the split passes do not batch");
       p->h.split = value != 0;
       d.split = value;
+      relist = true;
       if (value) {  // the split x pass reads its rows in place
         d.pull = 0;
         p->tune[PSATD_TUNE_PULL_EB] = 0;
@@ -718,7 +721,7 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
         return fail(p, PSATD_E_INVALID, "the split x/y passes do not batch");
       HIPCHK(p, hipStreamSynchronize(p->stream));
       set_batches(p->h, value);
-      d.slab = p->h.batch_slab;
+      relist = true;
       if (p->h.batches.size() > 1) {  // a later batch must still read its old guards
         p->h.fuse_eb = false;
         d.fuse = 0;
@@ -760,6 +763,7 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
       if (value && !p->h.zreg)
         return fail(p, PSATD_E_INVALID, "no register z schedule for this plan (FP32 VALU form, compiled lengths)");
       d.zreg = value;
+      relist = true;
       break;
     case PSATD_TUNE_XCD_REMAP:
       if (value != 0 && value != 1) return fail(p, PSATD_E_INVALID, "xcd remap must be 0 or 1");
@@ -797,6 +801,7 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
                     "per-class x/y launches need an unbatched plan whose boxes have several plane sizes");
       if (value) p->h.ntxy = value;
       d.ntxy = value;
+      relist = true;
       break;
     case PSATD_TUNE_Z_THREADS:
       if (value != 512 && value != 1024) return fail(p, PSATD_E_INVALID, "z threads must be 512 or 1024");
@@ -812,6 +817,10 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
   }
   p->tune[key] = value;
   drop_graphs(p);
+  if (relist) {
+    HIPCHK(p, hipStreamSynchronize(p->stream));
+    return upload_lists(p);
+  }
   return PSATD_OK;
 }
 

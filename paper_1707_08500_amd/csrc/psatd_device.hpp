@@ -31,30 +31,78 @@ struct BoxD {
   int32_t planz;   // FFT plan of length P[2]
   int32_t twr;     // offset of the W_{P[0]}^e table (real <-> half spectrum)
   int32_t kx, ky, kz;  // offsets of the FP64 modified-wavenumber tables
-  int32_t pad_;
+  int32_t ring;    // planes of the box's spectral ring (below)
+  int32_t zb;      // ring slot of padded plane 0
+  int32_t slo, shi;  // interior planes at the low / high end that other boxes read
   int64_t foff;    // element offset of the box in a field buffer
   int64_t soff;    // sum of the half-spectrum sizes of the boxes before it
   int64_t svol;    // half-spectrum size of one field of the box, P[2] P[1] H (complex)
+  int64_t sb, sv;  // spectral ring: offset of field 0, field stride (complex)
+  int64_t xb, xv;  // results of the shared planes: offset of field 0, field stride
 };
 
-// The spectral workspace is box-major: box s holds the half spectra of its 9
-// fields back to back, field f at 9 soff + f svol (complex elements, relative
-// to the first box of the batch the workspace holds), [z][ky][kx] each.  So
-// every field of a box lies within 9 svol elements of the box's first one.
+// The spectral workspace holds rings of (ky, kx) planes.  Boxes with the same
+// x/y extent and x/y guards (a column of the decomposition) have the same
+// padded (x, y) plane wherever their padded z ranges meet: a z-guard plane is
+// the neighbour's interior plane, cell for cell.  So a column shares one ring
+// of its distinct z-planes, each transformed once along x and y, and the z
+// pass of a box reads its P[2] consecutive slots zb, zb + 1, ... (mod ring).
+// A ring holds the 9 fields back to back, field f at sb + f sv, [slot][ky][kx]
+// each.  The z pass writes the E and B results over the spectra of the box's
+// interior planes, except the planes that other boxes of the column still read:
+// those results go to the box's own slots after the ring's fields (slo planes
+// of the low end, then shi of the high end; 6 fields at xb + f xv).  A box that
+// shares with no other is a ring of its own P[2] planes.
 template <typename T>
 PSATD_HD cx<T>* spec_at(cx<T>* spec, const BoxD& bx, int64_t sbias, int f) {
-  return spec + 9 * (bx.soff - sbias) + f * bx.svol;
+  return spec + (bx.sb - sbias) + f * bx.sv;
 }
 template <typename T>
 PSATD_HD const cx<T>* spec_at(const cx<T>* spec, const BoxD& bx, int64_t sbias, int f) {
-  return spec + 9 * (bx.soff - sbias) + f * bx.svol;
+  return spec + (bx.sb - sbias) + f * bx.sv;
 }
 
-// A batch of boxes [b0, b1) for the FFT/update passes: its work-item ranges
-// and the spectral offset of box b0 (the workspace holds the batch only).
+// Ring slot of padded plane z (zb + z < 2 ring, checked at plan time).
+PSATD_HD int ring_slot(const BoxD& bx, int z) {
+  const int s = bx.zb + z;
+  return s >= bx.ring ? s - bx.ring : s;
+}
+
+// Offset of the result of field f at interior plane i, nq = P[1] H elements
+// per plane (relative to the workspace's first element).
+PSATD_HD int64_t result_plane(const BoxD& bx, int64_t sbias, int f, int i, int nq) {
+  const int h = i - (bx.n[2] - bx.shi);
+  if (i < bx.slo) return bx.xb - sbias + f * bx.xv + (int64_t)i * nq;
+  if (h >= 0) return bx.xb - sbias + f * bx.xv + (int64_t)(bx.slo + h) * nq;
+  return bx.sb - sbias + f * bx.sv + (int64_t)ring_slot(bx, bx.g[2] + i) * nq;
+}
+
+// One (x, y) plane of the x/y passes' work lists.  Forward: padded plane z of
+// the box, with its guard pieces [p0, p1) of the pull list; inverse: interior
+// plane z.  Split passes: a block of the plane's rows or columns from p0 on.
+struct PlaneRec {
+  int32_t box, z, p0, p1;
+};
+
+// One z tile: the pencils q0, q0 + 1, ... of a box.
+struct ZItem {
+  int32_t box, q0;
+};
+
+// Launches of the x/y and z passes: ranges of the plane and tile lists with
+// their group size or tile width and their dynamic LDS.
+struct XyLaunch {
+  int32_t nt, lds, f0, nf, i0, ni;  // forward planes [f0, f0 + nf), inverse [i0, i0 + ni)
+  int32_t c0, nc, d0, nd;           // split passes: forward and inverse column blocks
+};
+struct ZLaunch {
+  int32_t PB, lds, u0, nu;
+};
+
+// A batch of boxes [b0, b1) for the FFT/update passes and the spectral offset
+// of box b0 (the workspace holds the batch only).
 struct Batch {
   int32_t b0, b1;
-  int32_t F0, nF, U0, nU, I0, nI;
   int64_t sbias;
 };
 
@@ -394,17 +442,16 @@ struct PullPiece {
 template <typename T>
 struct FwdArgs {
   Tables<T> t;
-  const int32_t* items;    // prefix over boxes of P[2] * nfield
-  int32_t nfield;
+  const PlaneRec* planes;  // item = field * planes + plane
+  FastDiv np;
   const T* in[9];
   cx<T>* spec;             // spectral workspace (box-major, see spec_at)
   int64_t sbias;           // spectral offset of the first box held by spec
   // Fields f < npull read their guard cells from the owners (pull pieces of
-  // box s: pull[pull_off[s] .. pull_off[s+1])) instead of the box's own,
-  // possibly stale, guard copies; npull = 0 reads every padded cell in place.
+  // the plane's record) instead of the box's own, possibly stale, guard
+  // copies; npull = 0 reads every padded cell in place.
   int32_t npull;
   const PullPiece* pull;
-  const int32_t* pull_off;
 };
 
 // Copies a rectangle of real cells src[r * sP0 + c] (r < ly, c < lx) into the
@@ -448,12 +495,11 @@ PSATD_HD void copy_rect_to_plane(const T* src, int sP0, int ly, int lx, int y0, 
 // (Nh), the y plan (Py) and W_Px (real <-> half spectrum).
 template <typename T, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_fwd_xy(const FwdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
-  const int s = find_box(a.items, a.t.nsub, item);
-  const BoxD& bx = a.t.box[s];
-  const int local = item - a.items[s];
-  const int Px = bx.P[0], Py = bx.P[1], Pz = bx.P[2];
-  const int f = local / Pz;
-  const int z = local - f * Pz;
+  const int f = (int)fdiv((uint32_t)item, a.np);
+  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
+  const BoxD& bx = a.t.box[rec.box];
+  const int z = rec.z;
+  const int Px = bx.P[0], Py = bx.P[1];
   const int Nh = Px >> 1, H = bx.H, ld = bx.ld;
   const FftPlanD* plx = a.t.plans + bx.planx;
   const FftPlanD* ply = a.t.plans + bx.plany;
@@ -495,10 +541,9 @@ PSATD_HD void body_fwd_xy(const FwdArgs<T>& a, int item, int tid, int nt, cx<T>*
                               gx, lds, ld, posx, lane, 64);
       dealt = nw;
     }
-    for (int b = a.pull_off[s]; b < a.pull_off[s + 1]; ++b) {
-      const PullPiece k = a.pull[b];
-      if (z < k.qz || z >= k.qz + k.lz) continue;
+    for (int b = rec.p0; b < rec.p1; ++b) {
       if (dealt++ % nw != wave) continue;
+      const PullPiece k = a.pull[b];
       copy_rect_to_plane<T>(inf + k.so + (int64_t)(z - k.qz) * k.sPl, k.sP0, k.ly, k.lx, k.qy, k.qx, lds, ld, posx,
                             lane, 64);
     }
@@ -520,7 +565,7 @@ PSATD_HD void body_fwd_xy(const FwdArgs<T>& a, int item, int tid, int nt, cx<T>*
   pair_pass_rows<true>(lds, Py, ld, Nh, twr, tid, nt);
   bar();
   eng.template dif<-1, MAXR>(lds, H, 1, ld, ply, twy, tid, nt, bar);
-  cx<T>* dst = spec_at(a.spec, bx, a.sbias, f) + (int64_t)z * Py * H;
+  cx<T>* dst = spec_at(a.spec, bx, a.sbias, f) + (int64_t)ring_slot(bx, z) * Py * H;
   copy_grid<8, cx<T>>(Py, H, tid, nt, [&](int, int ky, int kx) { return lds[posy[ky] * ld + kx]; },
                       [&](int i, int, int, cx<T> v) { dst[i] = v; });
 }
@@ -688,7 +733,7 @@ PSATD_HD void psatd_point(T* vr, T* vi /* E0 E1 E2 B0 B1 B2 J0 J1 J2 */, double 
 template <typename T>
 struct UpdArgs {
   Tables<T> t;
-  const int32_t* items;  // prefix over boxes of ceil(P[1] H / PB)
+  const ZItem* items;
   cx<T>* spec;
   int64_t sbias;
   UpdConst k;
@@ -700,12 +745,11 @@ struct UpdArgs {
 // element stride W.  Pencils past the end of the box (last block) are zeros.
 template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
-  const int s = find_box(a.items, a.t.nsub, item);
-  const BoxD& bx = a.t.box[s];
-  const int blk = item - a.items[s];
+  const ZItem it = a.items[item];
+  const BoxD& bx = a.t.box[it.box];
   const int Py = bx.P[1], Pz = bx.P[2], H = bx.H;
   const int nq = Py * H;
-  const int q0 = blk * PB;
+  const int q0 = it.q0;
   const int np = (nq - q0) < PB ? (nq - q0) : PB;
   const FftPlanD* plz = a.t.plans + bx.planz;
   constexpr int W = 9 * PB;
@@ -714,18 +758,23 @@ PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
   const cx<T>* gtz = a.t.tw + plz->tw;
   for (int i = tid; i < Pz; i += nt) kzi[i] = plan_index(plz, i);
   const cx<T>* src = spec_at(a.spec, bx, a.sbias, 0) + q0;
-  const int64_t slab = bx.svol;  // field stride
+  const int64_t slab = bx.sv;  // field stride
+  const int ring = bx.ring, zb = bx.zb;
+  auto plane = [&](int z) {
+    const int v = zb + z;
+    return (int64_t)(v >= ring ? v - ring : v) * nq;
+  };
   for (int i = tid; i < Pz; i += nt) twz[i] = gtz[i];
   // a full tile whose pencil runs start at even offsets moves two neighbouring
   // pencils per access
   const bool pairs = (PB % 2) == 0 && np == PB &&
-                     (((int64_t)nq | slab | (int64_t)(9 * (bx.soff - a.sbias) + q0)) & 1) == 0;
+                     (((int64_t)nq | slab | (bx.sb - a.sbias + q0) | (bx.xb - a.sbias + q0) | bx.xv) & 1) == 0;
   if (pairs) {
     // up to 8 loads in flight per thread (a 96-plane FP32 tile of 8 pencils is
     // 6.75 pairs per thread of 512: one batch)
     copy_grid3<8, Pair<cx<T>>>(9, Pz, PB / 2, tid, nt,
         [&](int, int f, int z, int p2) {
-          return *reinterpret_cast<const Pair<cx<T>>*>(src + f * slab + (int64_t)z * nq + 2 * p2);
+          return *reinterpret_cast<const Pair<cx<T>>*>(src + f * slab + plane(z) + 2 * p2);
         },
         [&](int, int f, int z, int p2, Pair<cx<T>> v) {
           *reinterpret_cast<Pair<cx<T>>*>(lds + z * W + f * PB + 2 * p2) = v;
@@ -733,7 +782,7 @@ PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
   } else {
     copy_grid3<8, cx<T>>(9, Pz, PB, tid, nt,
         [&](int, int f, int z, int p) {
-          return (p < np) ? src[f * slab + (int64_t)z * nq + p] : cx<T>{T(0), T(0)};
+          return (p < np) ? src[f * slab + plane(z) + p] : cx<T>{T(0), T(0)};
         },
         [&](int, int f, int z, int p, cx<T> v) { lds[z * W + f * PB + p] = v; });
   }
@@ -769,22 +818,22 @@ PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
   // only the interior z-planes: the inverse pass reads nothing else (the guard
   // planes of E and B are rewritten by the exchange)
   const int gz = bx.g[2];
-  cx<T>* dst = spec_at(a.spec, bx, a.sbias, 0) + q0 + (int64_t)gz * nq;
   const cx<T>* res = lds + gz * W;
+  cx<T>* dst = a.spec + q0;
   if (pairs) {
     copy_grid3<4, Pair<cx<T>>>(6, bx.n[2], PB / 2, tid, nt,
         [&](int, int f, int z, int p2) {
           return *reinterpret_cast<const Pair<cx<T>>*>(res + z * W + f * PB + 2 * p2);
         },
         [&](int, int f, int z, int p2, Pair<cx<T>> v) {
-          *reinterpret_cast<Pair<cx<T>>*>(dst + f * slab + (int64_t)z * nq + 2 * p2) = v;
+          *reinterpret_cast<Pair<cx<T>>*>(dst + result_plane(bx, a.sbias, f, z, nq) + 2 * p2) = v;
         });
     return;
   }
   copy_grid3<8, cx<T>>(6, bx.n[2], PB, tid, nt,
                        [&](int, int f, int z, int p) { return res[z * W + f * PB + p]; },
                        [&](int, int f, int z, int p, cx<T> v) {
-                         if (p < np) dst[f * slab + (int64_t)z * nq + p] = v;
+                         if (p < np) dst[result_plane(bx, a.sbias, f, z, nq) + p] = v;
                        });
 }
 
@@ -796,7 +845,7 @@ PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
 template <typename T>
 struct HeatArgs {
   Tables<T> t;
-  const int32_t* items;  // prefix over boxes of ceil(P[1] H / PB)
+  const ZItem* items;
   cx<T>* spec;           // the half spectrum of u
   double D, dt;
 };
@@ -807,25 +856,24 @@ struct HeatArgs {
 template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_z_heat(const HeatArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar,
                           Eng eng = Eng{}) {
-  const int s = find_box(a.items, a.t.nsub, item);
-  const BoxD& bx = a.t.box[s];
-  const int blk = item - a.items[s];
+  const ZItem it = a.items[item];
+  const BoxD& bx = a.t.box[it.box];
   const int Py = bx.P[1], Pz = bx.P[2], H = bx.H;
   const int nq = Py * H;
-  const int q0 = blk * PB;
+  const int q0 = it.q0;
   const int np = (nq - q0) < PB ? (nq - q0) : PB;
   const FftPlanD* plz = a.t.plans + bx.planz;
   cx<T>* twz = lds + Pz * PB;
   int32_t* kzi = reinterpret_cast<int32_t*>(twz + Pz);
   const cx<T>* gtz = a.t.tw + plz->tw;
   for (int i = tid; i < Pz; i += nt) kzi[i] = plan_index(plz, i);
-  cx<T>* col = spec_at(a.spec, bx, 0, 0) + q0;
+  const cx<T>* col = spec_at(a.spec, bx, 0, 0) + q0;
   const int ndata = Pz * PB;
   copy_batched<8, cx<T>>(ndata + Pz, tid, nt,
       [&](int i) {
         if (i >= ndata) return gtz[i - ndata];
         const int p = i % PB;
-        return (p < np) ? col[(int64_t)(i / PB) * nq + p] : cx<T>{T(0), T(0)};
+        return (p < np) ? col[(int64_t)ring_slot(bx, i / PB) * nq + p] : cx<T>{T(0), T(0)};
       },
       [&](int i, cx<T> v) {
         if (i >= ndata) twz[i - ndata] = v;
@@ -855,7 +903,7 @@ PSATD_HD void body_z_heat(const HeatArgs<T>& a, int item, int tid, int nt, cx<T>
   copy_batched<8, cx<T>>(bx.n[2] * PB, tid, nt, [&](int i) { return lds[gz * PB + i]; },
                          [&](int i, cx<T> v) {
                            const int p = i % PB;
-                           if (p < np) col[(int64_t)(gz + i / PB) * nq + p] = v;
+                           if (p < np) a.spec[result_plane(bx, 0, 0, i / PB, nq) + q0 + p] = v;
                          });
 }
 
@@ -865,7 +913,8 @@ PSATD_HD void body_z_heat(const HeatArgs<T>& a, int item, int tid, int nt, cx<T>
 template <typename T>
 struct InvArgs {
   Tables<T> t;
-  const int32_t* items;  // prefix over boxes of n[2] * 6
+  const PlaneRec* planes;  // interior planes; item = field * planes + plane
+  FastDiv np;
   const cx<T>* spec;
   int64_t sbias;
   T* out[6];
@@ -877,12 +926,11 @@ struct InvArgs {
 // the x plan (Nh) and W_Px.
 template <typename T, bool INC, int MAXR, bool PUSH = false, class Bar, class Eng = FftValu>
 PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
-  const int s = find_box(a.items, a.t.nsub, item);
+  const int f = (int)fdiv((uint32_t)item, a.np);
+  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
+  const int s = rec.box;
   const BoxD& bx = a.t.box[s];
-  const int local = item - a.items[s];
-  const int nz = bx.n[2];
-  const int f = local / nz;
-  const int z = bx.g[2] + (local - f * nz);
+  const int z = bx.g[2] + rec.z;
   const int Px = bx.P[0], Py = bx.P[1], Pz = bx.P[2];
   const int Nh = Px >> 1, H = bx.H, ld = bx.ld;
   const FftPlanD* plx = a.t.plans + bx.planx;
@@ -904,7 +952,7 @@ PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>*
   bar();
 
   // half-spectrum rows (ky natural) -> LDS rows in stage-digit order along y
-  const cx<T>* src = spec_at(a.spec, bx, a.sbias, f) + (int64_t)z * Py * H;
+  const cx<T>* src = a.spec + result_plane(bx, a.sbias, f, rec.z, Py * H);
   for (int i = tid; i < Py + Nh + Px; i += nt)  // twy, twx, twr are contiguous
     twy[i] = i < Py ? gty[i] : (i < Py + Nh ? gtx[i - Py] : gtr[i - Py - Nh]);
   // FP32: two spectrum entries per access (measured slower in FP64)
@@ -1010,14 +1058,15 @@ PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>*
 constexpr int kRB = 16;
 constexpr int kCB = 16;
 
+// Records: p0 is the block's first row or column; item = field * records + record.
 template <typename T>
 struct SplitArgs {
   Tables<T> t;
-  const int32_t* items;
+  const PlaneRec* planes;
+  FastDiv np;
   const T* in[9];      // x forward: field inputs
   T* out[6];           // x inverse: field outputs
   cx<T>* spec;
-  int64_t sbias;
   const PushBlk* push;       // x inverse: fused E,B guard exchange (or null)
   const int32_t* push_off;
 };
@@ -1025,15 +1074,12 @@ struct SplitArgs {
 // x forward: kRB rows of (box, z, field): packed real rows -> half spectrum rows.
 template <typename T, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_x_fwd(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
-  const int s = find_box(a.items, a.t.nsub, item);
-  const BoxD& bx = a.t.box[s];
-  const int Px = bx.P[0], Py = bx.P[1], Pz = bx.P[2];
-  const int nrb = (Py + kRB - 1) / kRB;
-  const int local = item - a.items[s];
-  const int f = local / (Pz * nrb);
-  const int r = local - f * Pz * nrb;
-  const int z = r / nrb;
-  const int y0 = (r - z * nrb) * kRB;
+  const int f = (int)fdiv((uint32_t)item, a.np);
+  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
+  const BoxD& bx = a.t.box[rec.box];
+  const int Px = bx.P[0], Py = bx.P[1];
+  const int z = rec.z;
+  const int y0 = rec.p0;
   const int ny = (Py - y0) < kRB ? (Py - y0) : kRB;
   const int Nh = Px >> 1, H = bx.H, ld = bx.ld;
   const FftPlanD* plx = a.t.plans + bx.planx;
@@ -1065,7 +1111,7 @@ PSATD_HD void body_x_fwd(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>
   eng.template dit<-1, MAXR>(lds, ny, ld, 1, plx, twx, tid, nt, bar);
   pair_pass_rows<true>(lds, ny, ld, Nh, twr, tid, nt);
   bar();
-  cx<T>* dst = spec_at(a.spec, bx, a.sbias, f) + ((int64_t)z * Py + y0) * H;
+  cx<T>* dst = spec_at(a.spec, bx, 0, f) + ((int64_t)ring_slot(bx, z) * Py + y0) * H;
   const FastDiv dH = make_fastdiv((uint32_t)H);
   copy_batched<8, cx<T>>(ny * H, tid, nt,
                          [&](int i) {
@@ -1080,24 +1126,19 @@ PSATD_HD void body_x_fwd(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>
 // interior planes and the 6 outputs.
 template <typename T, int DIR, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_y(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
-  const int s = find_box(a.items, a.t.nsub, item);
-  const BoxD& bx = a.t.box[s];
+  const int f = (int)fdiv((uint32_t)item, a.np);
+  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
+  const BoxD& bx = a.t.box[rec.box];
   const int Py = bx.P[1], H = bx.H;
-  const int ncb = (H + kCB - 1) / kCB;
-  const int nzp = DIR < 0 ? bx.P[2] : bx.n[2];
-  const int local = item - a.items[s];
-  const int f = local / (nzp * ncb);
-  const int r = local - f * nzp * ncb;
-  const int zz = r / ncb;
-  const int z = DIR < 0 ? zz : bx.g[2] + zz;
-  const int c0 = (r - zz * ncb) * kCB;
+  const int c0 = rec.p0;
   const int nc = (H - c0) < kCB ? (H - c0) : kCB;
   const FftPlanD* ply = a.t.plans + bx.plany;
   cx<T>* twy = lds + Py * kCB;
   int32_t* posy = reinterpret_cast<int32_t*>(twy + Py);
   for (int i = tid; i < Py; i += nt) posy[i] = plan_pos(ply, i);
   bar();
-  cx<T>* col = spec_at(a.spec, bx, a.sbias, f) + (int64_t)z * Py * H + c0;
+  cx<T>* col = c0 + (DIR < 0 ? spec_at(a.spec, bx, 0, f) + (int64_t)ring_slot(bx, rec.z) * Py * H
+                             : a.spec + result_plane(bx, 0, f, rec.z, Py * H));
   const cx<T>* gty = a.t.tw + ply->tw;
   const int ntot = Py * kCB;
   copy_batched<8, cx<T>>(ntot + Py, tid, nt,
@@ -1134,17 +1175,15 @@ PSATD_HD void body_y(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>* ld
 // half spectrum rows -> real rows, interior cells written (INC: added).
 template <typename T, bool INC, int MAXR, bool PUSH = false, class Bar, class Eng = FftValu>
 PSATD_HD void body_x_inv(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
-  const int s = find_box(a.items, a.t.nsub, item);
+  const int f = (int)fdiv((uint32_t)item, a.np);
+  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
+  const int s = rec.box;
   const BoxD& bx = a.t.box[s];
   const int Px = bx.P[0], Py = bx.P[1], Pz = bx.P[2];
-  const int nyi = bx.n[1], nz = bx.n[2];
-  const int nrb = (nyi + kRB - 1) / kRB;
-  const int local = item - a.items[s];
-  const int f = local / (nz * nrb);
-  const int r = local - f * nz * nrb;
-  const int zz = r / nrb;
+  const int nyi = bx.n[1];
+  const int zz = rec.z;
   const int z = bx.g[2] + zz;
-  const int yy0 = (r - zz * nrb) * kRB;
+  const int yy0 = rec.p0;
   const int ny = (nyi - yy0) < kRB ? (nyi - yy0) : kRB;
   const int y0 = bx.g[1] + yy0;
   const int Nh = Px >> 1, H = bx.H, ld = bx.ld;
@@ -1153,7 +1192,7 @@ PSATD_HD void body_x_inv(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>
   cx<T>* twr = twx + Nh;
   int32_t* posx = reinterpret_cast<int32_t*>(twr + Px);
   for (int i = tid; i < Nh; i += nt) posx[i] = plan_pos(plx, i);
-  const cx<T>* src = spec_at(a.spec, bx, a.sbias, f) + ((int64_t)z * Py + y0) * H;
+  const cx<T>* src = a.spec + result_plane(bx, 0, f, zz, Py * H) + (int64_t)y0 * H;
   const cx<T>* gtx = a.t.tw + plx->tw;
   const cx<T>* gtr = a.t.tw + bx.twr;
   const int nrow = ny * H;

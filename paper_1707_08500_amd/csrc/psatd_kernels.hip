@@ -52,19 +52,19 @@ __device__ __forceinline__ int first_item(int remap) {
 }
 
 template <typename T, int NT, int MAXR, int SPL>
-__global__ __launch_bounds__(NT) void k_fwd_xy(FwdArgs<T> a, int item0, int nitems, int remap) {
+__global__ __launch_bounds__(NT) void k_fwd_xy(FwdArgs<T> a, int nitems, int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_fwd_xy<T, MAXR>(a, item0 + it, threadIdx.x, NT, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
+    body_fwd_xy<T, MAXR>(a, it, threadIdx.x, NT, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
     __syncthreads();
   }
 }
 
 template <typename T, bool INC, int NT, int MAXR, int SPL, bool PUSH>
-__global__ __launch_bounds__(NT) void k_inv_xy(InvArgs<T> a, int item0, int nitems, int remap) {
+__global__ __launch_bounds__(NT) void k_inv_xy(InvArgs<T> a, int nitems, int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_inv_xy<T, INC, MAXR, PUSH>(a, item0 + it, threadIdx.x, NT, lds, BlockBarrier{},
+    body_inv_xy<T, INC, MAXR, PUSH>(a, it, threadIdx.x, NT, lds, BlockBarrier{},
                                     typename EngOf<SPL>::type{});
     __syncthreads();
   }
@@ -73,11 +73,11 @@ __global__ __launch_bounds__(NT) void k_inv_xy(InvArgs<T> a, int item0, int nite
 // FP32: at most 128 VGPRs, so that two 512-thread tiles share a CU (four
 // waves per SIMD); FP64 tiles measured slower when held to that budget.
 template <typename T, int NT, int PB, bool INC, int MAXR, int SPL>
-__global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 1) void k_z_update(UpdArgs<T> a, int item0, int nitems,
+__global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 1) void k_z_update(UpdArgs<T> a, int nitems,
                                                                           int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_z_update<T, PB, INC, MAXR>(a, item0 + it, threadIdx.x, NT, lds, BlockBarrier{},
+    body_z_update<T, PB, INC, MAXR>(a, it, threadIdx.x, NT, lds, BlockBarrier{},
                                     typename EngOf<SPL>::type{});
     __syncthreads();
   }
@@ -242,14 +242,7 @@ hipError_t prepare_t(int ldsF, int ldsI, int ldsU, int ldsX, int ldsY) {
     }                                              \
   } while (0)
 
-template <typename T, int NT, int MAXR, int SPL>
-static hipError_t fwd_go(const DevPlan& p, const FwdArgs<T>& a, int g, int lds, int item0, int n,
-                         hipStream_t st) {
-  hipLaunchKernelGGL((k_fwd_xy<T, NT, MAXR, SPL>), dim3(g), dim3(NT), lds, st, a, item0, n, p.xcd);
-  return hipGetLastError();
-}
-
-// One x/y launch of n items from item0 with nt threads per group.
+// One x/y launch with nt threads per group.
 template <typename T, int SPL, class Go>
 static hipError_t xy_shape(const DevPlan& p, int nt, Go go) {
   if (nt == 1024)
@@ -264,239 +257,190 @@ template <typename T>
 struct FwdGo {
   const DevPlan& p;
   const FwdArgs<T>& a;
-  int g, lds, item0, n;
+  int g, lds, n;
   hipStream_t st;
   template <int NT, int MAXR, int SPL>
-  hipError_t run() const { return fwd_go<T, NT, MAXR, SPL>(p, a, g, lds, item0, n, st); }
+  hipError_t run() const {
+    hipLaunchKernelGGL((k_fwd_xy<T, NT, MAXR, SPL>), dim3(g), dim3(NT), lds, st, a, n, p.xcd);
+    return hipGetLastError();
+  }
 };
 
 template <typename T, int SPL>
-hipError_t fwd_t(const DevPlan& p, const Batch& b, void* const* in9, void* spec, hipStream_t st,
-                        bool scalar) {
+hipError_t fwd_t(const DevPlan& p, const XyLaunch& l, int64_t sbias, void* const* in9, int nf, int npull, void* spec,
+                 hipStream_t st) {
+  const int n = l.nf * nf;
+  const int g = grid_for(n, p.grid_cap[kPhaseFwd]);
+  if (!g) return hipSuccess;
   FwdArgs<T> a;
   a.t = tables<T>(p);
-  a.items = scalar ? p.itemsP : p.itemsF;  // one field: P[2] planes per box
-  a.nfield = scalar ? 1 : 9;
-  a.npull = (p.pull && !scalar) ? 6 : 0;
+  a.planes = p.fwd + l.f0;
+  a.np = make_fastdiv((uint32_t)l.nf);
+  a.npull = npull;
   a.pull = p.pullp;
-  a.pull_off = p.pull_off;
-  for (int f = 0; f < 9; ++f) a.in[f] = (f < a.nfield) ? reinterpret_cast<const T*>(in9[f]) : nullptr;
+  for (int f = 0; f < 9; ++f) a.in[f] = (f < nf) ? reinterpret_cast<const T*>(in9[f]) : nullptr;
   a.spec = reinterpret_cast<cx<T>*>(spec);
-  a.sbias = b.sbias;
-  if (p.ntxy == 0) {  // one launch per class of plane size (unbatched plans only)
-    for (int c = 0; c < p.nxyc; ++c) {
-      const XyClass& k = p.xyc[c];
-      a.items = p.itemsXYC + (scalar ? k.P : k.F);
-      const int n = scalar ? k.nP : k.nF;
-      const int g = grid_for(n, p.grid_cap[kPhaseFwd]);
-      if (!g) continue;
-      const hipError_t e = xy_shape<T, SPL>(p, k.nt, FwdGo<T>{p, a, g, k.lds, 0, n, st});
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  const int g = grid_for(b.nF, p.grid_cap[kPhaseFwd]);
-  if (!g) return hipSuccess;
-  return xy_shape<T, SPL>(p, p.ntxy, FwdGo<T>{p, a, g, p.ldsF, b.F0, b.nF, st});
+  a.sbias = sbias;
+  return xy_shape<T, SPL>(p, l.nt, FwdGo<T>{p, a, g, l.lds, n, st});
 }
 
-// One z launch: n items from item0, PB pencils per tile, lds bytes of LDS.
-struct UpdLaunch {
-  int g, PB, lds, item0, n;
-};
-
 template <typename T, int NT, int PB, int MAXR, int SPL>
-static hipError_t upd_launch(const DevPlan& p, const UpdLaunch& l, const UpdArgs<T>& a, hipStream_t st) {
-  hipLaunchKernelGGL((k_z_update<T, NT, PB, IncOf<T>::value, MAXR, SPL>), dim3(l.g), dim3(NT), l.lds, st, a,
-                     l.item0, l.n, p.xcd);
+static hipError_t upd_launch(const DevPlan& p, const ZLaunch& l, int g, const UpdArgs<T>& a, hipStream_t st) {
+  hipLaunchKernelGGL((k_z_update<T, NT, PB, IncOf<T>::value, MAXR, SPL>), dim3(g), dim3(NT), l.lds, st, a, l.nu,
+                     p.xcd);
   return hipGetLastError();
 }
 
 template <typename T, int MAXR, int SPL>
-static hipError_t upd_shape(const DevPlan& p, const UpdLaunch& l, const UpdArgs<T>& a, hipStream_t st) {
-  if (l.PB == 4) return upd_launch<T, 512, 4, MAXR, SPL>(p, l, a, st);
-  if (l.PB == 6) return upd_launch<T, 512, 6, MAXR, SPL>(p, l, a, st);
-  if (l.PB == 10) return upd_launch<T, 512, 10, MAXR, SPL>(p, l, a, st);
+static hipError_t upd_shape(const DevPlan& p, const ZLaunch& l, int g, const UpdArgs<T>& a, hipStream_t st) {
+  if (l.PB == 4) return upd_launch<T, 512, 4, MAXR, SPL>(p, l, g, a, st);
+  if (l.PB == 6) return upd_launch<T, 512, 6, MAXR, SPL>(p, l, g, a, st);
+  if (l.PB == 10) return upd_launch<T, 512, 10, MAXR, SPL>(p, l, g, a, st);
   if (p.ntu == 1024)
-    return l.PB == 16 ? upd_launch<T, 1024, 16, MAXR, SPL>(p, l, a, st)
-                      : upd_launch<T, 1024, 8, MAXR, SPL>(p, l, a, st);
-  return l.PB == 16 ? upd_launch<T, 512, 16, MAXR, SPL>(p, l, a, st)
-                    : upd_launch<T, 512, 8, MAXR, SPL>(p, l, a, st);
+    return l.PB == 16 ? upd_launch<T, 1024, 16, MAXR, SPL>(p, l, g, a, st)
+                      : upd_launch<T, 1024, 8, MAXR, SPL>(p, l, g, a, st);
+  return l.PB == 16 ? upd_launch<T, 512, 16, MAXR, SPL>(p, l, g, a, st)
+                    : upd_launch<T, 512, 8, MAXR, SPL>(p, l, g, a, st);
 }
 
 template <typename T, int SPL>
-hipError_t upd_t(const DevPlan& p, const Batch& b, void* spec, hipStream_t st) {
+hipError_t upd_t(const DevPlan& p, const ZLaunch& l, int64_t sbias, void* spec, hipStream_t st) {
+  const int g = grid_for(l.nu, p.grid_cap[kPhaseUpd]);
+  if (!g) return hipSuccess;
   UpdArgs<T> a;
   a.t = tables<T>(p);
-  a.items = p.itemsU;
+  a.items = p.tiles + l.u0;
   a.spec = reinterpret_cast<cx<T>*>(spec);
-  a.sbias = b.sbias;
+  a.sbias = sbias;
   a.k.c = p.c;
   a.k.dt = p.dt;
-  auto go = [&](const UpdLaunch& l) -> hipError_t {
-    PSATD_MAXR_SWITCH(SPL, p.maxrz, return (upd_shape<T, 8, SPL>(p, l, a, st)),
-                      return (upd_shape<T, 16, SPL>(p, l, a, st)));
-    return hipSuccess;
-  };
-  if (p.zcl) {  // one launch per class of tile size (unbatched plans only)
-    for (int c = 0; c < p.nzc; ++c) {
-      const ZClass& k = p.zc[c];
-      a.items = p.itemsZC + k.U;
-      const int g = grid_for(k.nU, p.grid_cap[kPhaseUpd]);
-      if (!g) continue;
-      const hipError_t e = go(UpdLaunch{g, k.PB, k.lds, 0, k.nU});
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  const int g = grid_for(b.nU, p.grid_cap[kPhaseUpd]);
-  if (!g) return hipSuccess;
-  return go(UpdLaunch{g, p.PB, p.ldsU, b.U0, b.nU});
-}
-
-template <typename T, int NT, int MAXR, int SPL>
-static hipError_t inv_go(const DevPlan& p, const InvArgs<T>& a, int g, int lds, int item0, int n,
-                         hipStream_t st) {
-  if (a.push_off)
-    hipLaunchKernelGGL((k_inv_xy<T, IncOf<T>::value, NT, MAXR, SPL, true>), dim3(g), dim3(NT), lds, st, a,
-                       item0, n, p.xcd);
-  else
-    hipLaunchKernelGGL((k_inv_xy<T, IncOf<T>::value, NT, MAXR, SPL, false>), dim3(g), dim3(NT), lds, st, a,
-                       item0, n, p.xcd);
-  return hipGetLastError();
+  PSATD_MAXR_SWITCH(SPL, p.maxrz, return (upd_shape<T, 8, SPL>(p, l, g, a, st)),
+                    return (upd_shape<T, 16, SPL>(p, l, g, a, st)));
+  return hipSuccess;
 }
 
 template <typename T>
 struct InvGo {
   const DevPlan& p;
   const InvArgs<T>& a;
-  int g, lds, item0, n;
+  int g, lds, n;
   hipStream_t st;
   template <int NT, int MAXR, int SPL>
-  hipError_t run() const { return inv_go<T, NT, MAXR, SPL>(p, a, g, lds, item0, n, st); }
+  hipError_t run() const {
+    if (a.push_off)
+      hipLaunchKernelGGL((k_inv_xy<T, IncOf<T>::value, NT, MAXR, SPL, true>), dim3(g), dim3(NT), lds, st, a, n, p.xcd);
+    else
+      hipLaunchKernelGGL((k_inv_xy<T, IncOf<T>::value, NT, MAXR, SPL, false>), dim3(g), dim3(NT), lds, st, a, n,
+                         p.xcd);
+    return hipGetLastError();
+  }
 };
 
 template <typename T, int SPL>
-hipError_t inv_t(const DevPlan& p, const Batch& b, const void* spec, void* const* out6, hipStream_t st,
-                        bool scalar) {
+hipError_t inv_t(const DevPlan& p, const XyLaunch& l, int64_t sbias, const void* spec, void* const* out6, int nf,
+                 hipStream_t st) {
+  const int n = l.ni * nf;
+  const int g = grid_for(n, p.grid_cap[kPhaseInv]);
+  if (!g) return hipSuccess;
   InvArgs<T> a;
   a.t = tables<T>(p);
-  a.items = scalar ? p.itemsN : p.itemsI;  // one field: n[2] planes per box
+  a.planes = p.inv + l.i0;
+  a.np = make_fastdiv((uint32_t)l.ni);
   a.spec = reinterpret_cast<const cx<T>*>(spec);
-  a.sbias = b.sbias;
-  for (int f = 0; f < 6; ++f) a.out[f] = (f == 0 || !scalar) ? reinterpret_cast<T*>(out6[f]) : nullptr;
-  a.push = (p.fuse && !scalar) ? p.push : nullptr;
-  a.push_off = (p.fuse && !scalar) ? p.push_off : nullptr;
-  if (p.ntxy == 0) {  // one launch per class of plane size (unbatched plans only)
-    for (int c = 0; c < p.nxyc; ++c) {
-      const XyClass& k = p.xyc[c];
-      a.items = p.itemsXYC + (scalar ? k.N : k.I);
-      const int n = scalar ? k.nN : k.nI;
-      const int g = grid_for(n, p.grid_cap[kPhaseInv]);
-      if (!g) continue;
-      const hipError_t e = xy_shape<T, SPL>(p, k.nt, InvGo<T>{p, a, g, k.lds, 0, n, st});
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
-  }
-  const int g = grid_for(b.nI, p.grid_cap[kPhaseInv]);
-  if (!g) return hipSuccess;
-  return xy_shape<T, SPL>(p, p.ntxy, InvGo<T>{p, a, g, p.ldsI, b.I0, b.nI, st});
+  a.sbias = sbias;
+  for (int f = 0; f < 6; ++f) a.out[f] = f < nf ? reinterpret_cast<T*>(out6[f]) : nullptr;
+  const bool fuse = p.fuse && nf == 6;
+  a.push = fuse ? p.push : nullptr;
+  a.push_off = fuse ? p.push_off : nullptr;
+  return xy_shape<T, SPL>(p, l.nt, InvGo<T>{p, a, g, l.lds, n, st});
 }
 
 template <typename T, int SPL>
-hipError_t heat_z_t(const DevPlan& p, void* spec, double D, double dt, hipStream_t st) {
+hipError_t heat_z_t(const DevPlan& p, const ZLaunch& l, int lds, void* spec, double D, double dt, hipStream_t st) {
+  const int g = grid_for(l.nu, p.grid_cap[kPhaseUpd]);
+  if (!g) return hipSuccess;
   HeatArgs<T> a;
   a.t = tables<T>(p);
-  a.items = p.itemsU;
+  a.items = p.tiles + l.u0;
   a.spec = reinterpret_cast<cx<T>*>(spec);
   a.D = D;
   a.dt = dt;
-  const int g = grid_for(p.nU, p.grid_cap[kPhaseUpd]);
-  if (!g) return hipSuccess;
   constexpr bool I = IncOf<T>::value;
   auto go = [&](auto pbc) -> hipError_t {
     constexpr int PB = decltype(pbc)::value;
     PSATD_MAXR_SWITCH(SPL, p.maxrz,
-                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsH, st,
-                                         a, p.nU, p.xcd),
-                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsH, st,
-                                         a, p.nU, p.xcd));
+                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 8, SPL>), dim3(g), dim3(kThreadsXY), lds, st, a, l.nu,
+                                         p.xcd),
+                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 16, SPL>), dim3(g), dim3(kThreadsXY), lds, st, a, l.nu,
+                                         p.xcd));
     return hipGetLastError();
   };
-  if (p.PB == 4) return go(std::integral_constant<int, 4>{});
-  if (p.PB == 6) return go(std::integral_constant<int, 6>{});
-  if (p.PB == 10) return go(std::integral_constant<int, 10>{});
-  if (p.PB == 8) return go(std::integral_constant<int, 8>{});
+  if (l.PB == 4) return go(std::integral_constant<int, 4>{});
+  if (l.PB == 6) return go(std::integral_constant<int, 6>{});
+  if (l.PB == 10) return go(std::integral_constant<int, 10>{});
+  if (l.PB == 8) return go(std::integral_constant<int, 8>{});
   return go(std::integral_constant<int, 16>{});
 }
 
 template <typename T>
-static SplitArgs<T> split_args(const DevPlan& p, void* spec) {
+static SplitArgs<T> split_args(const DevPlan& p, const PlaneRec* planes, int np, void* spec) {
   SplitArgs<T> a;
   a.t = tables<T>(p);
-  a.items = nullptr;
+  a.planes = planes;
+  a.np = make_fastdiv((uint32_t)np);
   for (int f = 0; f < 9; ++f) a.in[f] = nullptr;
   for (int f = 0; f < 6; ++f) a.out[f] = nullptr;
   a.spec = reinterpret_cast<cx<T>*>(spec);
-  a.sbias = 0;
   a.push = p.fuse ? p.push : nullptr;
   a.push_off = p.fuse ? p.push_off : nullptr;
   return a;
 }
 
 template <typename T, int SPL>
-hipError_t x_fwd_t(const DevPlan& p, void* const* in9, void* spec, hipStream_t st) {
-  SplitArgs<T> a = split_args<T>(p, spec);
-  a.items = p.itemsXF;
-  for (int f = 0; f < 9; ++f) a.in[f] = reinterpret_cast<const T*>(in9[f]);
-  const int g = grid_for(p.nXF, p.grid_cap[kPhaseFwd]);
+hipError_t x_fwd_t(const DevPlan& p, const XyLaunch& l, void* const* in9, int nf, void* spec, hipStream_t st) {
+  const int n = nf * l.nf;
+  const int g = grid_for(n, p.grid_cap[kPhaseFwd]);
   if (!g) return hipSuccess;
+  SplitArgs<T> a = split_args<T>(p, p.fwd + l.f0, l.nf, spec);
+  for (int f = 0; f < nf; ++f) a.in[f] = reinterpret_cast<const T*>(in9[f]);
   PSATD_MAXR_SWITCH(SPL, p.maxr,
-                    hipLaunchKernelGGL((k_x_fwd<T, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a,
-                                       p.nXF, p.xcd),
-                    hipLaunchKernelGGL((k_x_fwd<T, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a,
-                                       p.nXF, p.xcd));
+                    hipLaunchKernelGGL((k_x_fwd<T, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a, n, p.xcd),
+                    hipLaunchKernelGGL((k_x_fwd<T, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a, n, p.xcd));
   return hipGetLastError();
 }
 
 template <typename T, int SPL>
-hipError_t y_t(const DevPlan& p, int dir, void* spec, hipStream_t st) {
-  SplitArgs<T> a = split_args<T>(p, spec);
-  a.items = dir < 0 ? p.itemsYF : p.itemsYI;
-  const int n = dir < 0 ? p.nYF : p.nYI;
+hipError_t y_t(const DevPlan& p, const XyLaunch& l, int dir, int nf, void* spec, hipStream_t st) {
+  const int np = dir < 0 ? l.nc : l.nd;
+  const int n = nf * np;
   const int g = grid_for(n, p.grid_cap[dir < 0 ? kPhaseFwd : kPhaseInv]);
   if (!g) return hipSuccess;
+  SplitArgs<T> a = split_args<T>(p, dir < 0 ? p.fwd + l.c0 : p.inv + l.d0, np, spec);
   if (dir < 0)
     PSATD_MAXR_SWITCH(SPL, p.maxr,
-                      hipLaunchKernelGGL((k_y<T, -1, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
-                                         p.xcd),
-                      hipLaunchKernelGGL((k_y<T, -1, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
-                                         p.xcd));
+                      hipLaunchKernelGGL((k_y<T, -1, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n, p.xcd),
+                      hipLaunchKernelGGL((k_y<T, -1, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n, p.xcd));
   else
     PSATD_MAXR_SWITCH(SPL, p.maxr,
-                      hipLaunchKernelGGL((k_y<T, 1, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
-                                         p.xcd),
-                      hipLaunchKernelGGL((k_y<T, 1, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n,
-                                         p.xcd));
+                      hipLaunchKernelGGL((k_y<T, 1, 8, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n, p.xcd),
+                      hipLaunchKernelGGL((k_y<T, 1, 16, SPL>), dim3(g), dim3(kThreadsXY), p.ldsY, st, a, n, p.xcd));
   return hipGetLastError();
 }
 
 template <typename T, int SPL>
-hipError_t x_inv_t(const DevPlan& p, const void* spec, void* const* out6, hipStream_t st) {
-  SplitArgs<T> a = split_args<T>(p, const_cast<void*>(spec));
-  a.items = p.itemsXI;
-  for (int f = 0; f < 6; ++f) a.out[f] = reinterpret_cast<T*>(out6[f]);
-  const int g = grid_for(p.nXI, p.grid_cap[kPhaseInv]);
+hipError_t x_inv_t(const DevPlan& p, const XyLaunch& l, const void* spec, void* const* out6, hipStream_t st) {
+  const int n = 6 * l.ni;
+  const int g = grid_for(n, p.grid_cap[kPhaseInv]);
   if (!g) return hipSuccess;
+  SplitArgs<T> a = split_args<T>(p, p.inv + l.i0, l.ni, const_cast<void*>(spec));
+  for (int f = 0; f < 6; ++f) a.out[f] = reinterpret_cast<T*>(out6[f]);
   constexpr bool I = IncOf<T>::value;
   auto go = [&](auto pc) {
     constexpr bool PUSH = decltype(pc)::value;
-    PSATD_MAXR_SWITCH(SPL, p.maxr,
-                      hipLaunchKernelGGL((k_x_inv<T, I, 8, SPL, PUSH>), dim3(g), dim3(kThreadsXY), p.ldsX, st,
-                                         a, p.nXI, p.xcd),
-                      hipLaunchKernelGGL((k_x_inv<T, I, 16, SPL, PUSH>), dim3(g), dim3(kThreadsXY), p.ldsX, st,
-                                         a, p.nXI, p.xcd));
+    PSATD_MAXR_SWITCH(
+        SPL, p.maxr,
+        hipLaunchKernelGGL((k_x_inv<T, I, 8, SPL, PUSH>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a, n, p.xcd),
+        hipLaunchKernelGGL((k_x_inv<T, I, 16, SPL, PUSH>), dim3(g), dim3(kThreadsXY), p.ldsX, st, a, n, p.xcd));
   };
   if (a.push_off) go(std::true_type{});
   else go(std::false_type{});
@@ -509,16 +453,19 @@ hipError_t x_inv_t(const DevPlan& p, const void* spec, void* const* out6, hipStr
 // instantiation definitions, so that the library can be compiled as one
 // translation unit per form in parallel (PSATD_TU 1..4: FP64, FP32, BF16x3,
 // BF16x6; 0: the dispatch below) or, without PSATD_TU, as a whole.
-#define PSATD_FORM(KIND, T, SPL)                                                                              \
-  KIND template hipError_t fwd_t<T, SPL>(const DevPlan&, const Batch&, void* const*, void*, hipStream_t,      \
-                                         bool);                                                               \
-  KIND template hipError_t upd_t<T, SPL>(const DevPlan&, const Batch&, void*, hipStream_t);                   \
-  KIND template hipError_t inv_t<T, SPL>(const DevPlan&, const Batch&, const void*, void* const*, hipStream_t, \
-                                         bool);                                                               \
-  KIND template hipError_t heat_z_t<T, SPL>(const DevPlan&, void*, double, double, hipStream_t);              \
-  KIND template hipError_t x_fwd_t<T, SPL>(const DevPlan&, void* const*, void*, hipStream_t);                 \
-  KIND template hipError_t y_t<T, SPL>(const DevPlan&, int, void*, hipStream_t);                              \
-  KIND template hipError_t x_inv_t<T, SPL>(const DevPlan&, const void*, void* const*, hipStream_t);           \
+#define PSATD_FORM(KIND, T, SPL)                                                                                 \
+  KIND template hipError_t fwd_t<T, SPL>(const DevPlan&, const XyLaunch&, int64_t, void* const*, int, int,       \
+                                         void*, hipStream_t);                                                    \
+  KIND template hipError_t upd_t<T, SPL>(const DevPlan&, const ZLaunch&, int64_t, void*, hipStream_t);           \
+  KIND template hipError_t inv_t<T, SPL>(const DevPlan&, const XyLaunch&, int64_t, const void*, void* const*,    \
+                                         int, hipStream_t);                                                      \
+  KIND template hipError_t heat_z_t<T, SPL>(const DevPlan&, const ZLaunch&, int, void*, double, double,          \
+                                            hipStream_t);                                                        \
+  KIND template hipError_t x_fwd_t<T, SPL>(const DevPlan&, const XyLaunch&, void* const*, int, void*,            \
+                                           hipStream_t);                                                         \
+  KIND template hipError_t y_t<T, SPL>(const DevPlan&, const XyLaunch&, int, int, void*, hipStream_t);           \
+  KIND template hipError_t x_inv_t<T, SPL>(const DevPlan&, const XyLaunch&, const void*, void* const*,           \
+                                           hipStream_t);                                                         \
   KIND template hipError_t prepare_t<T, 16, SPL>(int, int, int, int, int);
 #define PSATD_FORM_VALU(KIND, T) \
   PSATD_FORM(KIND, T, 0)         \
@@ -569,34 +516,35 @@ hipError_t prepare_kernels(bool f64, int spl, int ldsF, int ldsI, int ldsU, int 
   return prepare_t<float, 16, 0>(ldsF, ldsI, ldsU, ldsX, ldsY);
 }
 
-hipError_t launch_fwd(const DevPlan& p, const Batch& b, void* const* in9, void* spec, hipStream_t st,
-                      bool scalar) {
-  PSATD_BY_FORM(fwd_t, p, b, in9, spec, st, scalar);
+hipError_t launch_fwd(const DevPlan& p, const XyLaunch& l, int64_t sbias, void* const* in9, int nf, int npull,
+                      void* spec, hipStream_t st) {
+  PSATD_BY_FORM(fwd_t, p, l, sbias, in9, nf, npull, spec, st);
 }
 
-hipError_t launch_upd(const DevPlan& p, const Batch& b, void* spec, hipStream_t st) {
-  PSATD_BY_FORM(upd_t, p, b, spec, st);
+hipError_t launch_upd(const DevPlan& p, const ZLaunch& l, int64_t sbias, void* spec, hipStream_t st) {
+  PSATD_BY_FORM(upd_t, p, l, sbias, spec, st);
 }
 
-hipError_t launch_inv(const DevPlan& p, const Batch& b, const void* spec, void* const* out6, hipStream_t st,
-                      bool scalar) {
-  PSATD_BY_FORM(inv_t, p, b, spec, out6, st, scalar);
+hipError_t launch_inv(const DevPlan& p, const XyLaunch& l, int64_t sbias, const void* spec, void* const* out6, int nf,
+                      hipStream_t st) {
+  PSATD_BY_FORM(inv_t, p, l, sbias, spec, out6, nf, st);
 }
 
-hipError_t launch_heat_z(const DevPlan& p, void* spec, double D, double dt, hipStream_t st) {
-  PSATD_BY_FORM(heat_z_t, p, spec, D, dt, st);
+hipError_t launch_heat_z(const DevPlan& p, const ZLaunch& l, int lds, void* spec, double D, double dt,
+                         hipStream_t st) {
+  PSATD_BY_FORM(heat_z_t, p, l, lds, spec, D, dt, st);
 }
 
-hipError_t launch_x_fwd(const DevPlan& p, void* const* in9, void* spec, hipStream_t st) {
-  PSATD_BY_FORM(x_fwd_t, p, in9, spec, st);
+hipError_t launch_x_fwd(const DevPlan& p, const XyLaunch& l, void* const* in9, int nf, void* spec, hipStream_t st) {
+  PSATD_BY_FORM(x_fwd_t, p, l, in9, nf, spec, st);
 }
 
-hipError_t launch_y(const DevPlan& p, int dir, void* spec, hipStream_t st) {
-  PSATD_BY_FORM(y_t, p, dir, spec, st);
+hipError_t launch_y(const DevPlan& p, const XyLaunch& l, int dir, int nf, void* spec, hipStream_t st) {
+  PSATD_BY_FORM(y_t, p, l, dir, nf, spec, st);
 }
 
-hipError_t launch_x_inv(const DevPlan& p, const void* spec, void* const* out6, hipStream_t st) {
-  PSATD_BY_FORM(x_inv_t, p, spec, out6, st);
+hipError_t launch_x_inv(const DevPlan& p, const XyLaunch& l, const void* spec, void* const* out6, hipStream_t st) {
+  PSATD_BY_FORM(x_inv_t, p, l, spec, out6, st);
 }
 
 template <typename T>
