@@ -17,6 +17,8 @@
 #pragma once
 #include <stdint.h>
 
+#include <type_traits>
+
 #include "dft_consts.h"
 
 #define PSATD_HD __host__ __device__ __forceinline__
@@ -177,7 +179,7 @@ struct FftPlanD {
   FastDiv rdiv[kMaxStages];     // division by r_s
   FastDiv sdiv[kMaxStages];     // division by ms_s
   int32_t tw;    // offset of the plan's twiddle table
-  int32_t pad_;
+  int32_t pos;   // offset of the plan's table of positions (plan_pos of 0 .. N-1)
 };
 
 // Position of index k in stage-digit order: k = t_0 + r_0 t_1 + ..., pos = sum t_s ms_s.
@@ -315,6 +317,65 @@ PSATD_HD void fft_dit(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, con
   }
 }
 
+// The first stage of a dif with its own loads: element e of transform m comes
+// from io.run<R>(m, j, ms, a) (elements j, j + ms, ... of a butterfly) instead
+// of the buffer, so that data read from memory makes one LDS round trip and one
+// barrier less.  Results at buf[m + e W]; the transform count M and W are
+// constants.  A length of 1 is one stage of radix 1.
+template <int R, int DIR, int M, int W, typename T, class IO>
+PSATD_HD void first_stage(cx<T>* buf, int ms, const cx<T>* tws, int tid, int nt, const IO& io) {
+  for (int b = tid; b < M * ms; b += nt) {
+    const int j = (int)((uint32_t)b / (uint32_t)M);
+    const int m = b - j * M;
+    cx<T>* p = buf + m + j * W;
+    const cx<T>* tb = tws + j * (R - 1) - 1;
+    cx<T> a[R];
+    io.template run<R>(m, j, ms, a);
+    if constexpr (R > 1) {
+      Dft<R, DIR, T>::run(a);
+      if (j) {
+#pragma unroll
+        for (int t = 1; t < R; ++t) a[t] = cmul(a[t], twid<DIR>(tb, t));
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) p[q * ms * W] = a[q];
+  }
+}
+
+template <int DIR, int MAXR, int M, int W, typename T, class IO>
+PSATD_HD void first_stage_dispatch(const FftPlanD* pl, cx<T>* buf, const cx<T>* tw, int tid, int nt, const IO& io) {
+  const int ms = pl->stride[0];
+  const cx<T>* tws = tw + pl->twoff[0];
+  switch (pl->radix[0]) {
+    case 1: first_stage<1, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 2: first_stage<2, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 3: first_stage<3, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 4: first_stage<4, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 5: first_stage<5, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 6: first_stage<6, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 7: first_stage<7, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 8: first_stage<8, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 10: if constexpr (MAXR >= 10) first_stage<10, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 11: first_stage<11, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 12: if constexpr (MAXR >= 12) first_stage<12, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    case 16: if constexpr (MAXR >= 16) first_stage<16, DIR, M, W>(buf, ms, tws, tid, nt, io); break;
+    default: break;
+  }
+}
+
+// The other stages (s >= 1) of such a dif.
+template <int DIR, int MAXR, typename T, class Bar>
+PSATD_HD void fft_dif_inner(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, const cx<T>* tw, int tid, int nt,
+                            Bar bar) {
+  const FastDiv dM = make_fastdiv((uint32_t)M);
+  for (int s = 1; s < pl->nstages; ++s) {
+    const int L = pl->stride[s] * pl->radix[s];
+    fft_stage_dispatch<DIR, true, MAXR, T>(pl->radix[s], buf, M, dM, ms, es, pl->N, L, pl->sdiv[s],
+                                           tw + pl->twoff[s], tid, nt);
+    bar();
+  }
+}
 // FFT engine of the kernel bodies: every stage as a VALU radix stage.
 struct FftValu {
   template <int DIR, int MAXR, typename T, class Bar>

@@ -23,13 +23,15 @@ namespace psatd {
 // their spectral addresses, the plane and tile lists, and the launches of each
 // batch (the lists' ranges).
 struct WorkLists {
-  std::vector<BoxD> box;
+  std::vector<BoxD> box;          // spectral planes at line-aligned, spread pitches
+  std::vector<BoxD> tight;        // the same boxes with planes back to back
   std::vector<PullPiece> pull;    // guard pieces per run of padded planes they cover
   std::vector<PlaneRec> fwd, inv;
   std::vector<ZItem> tiles;
+  ZLaunch heat{};                 // the heat pass's tiles (unbatched plans), after the field pass's
   std::vector<std::vector<XyLaunch>> xy;  // per batch
   std::vector<std::vector<ZLaunch>> z;
-  int64_t elems = 0;              // complex elements of the workspace
+  int64_t elems = 0, tight_elems = 0;  // complex elements of the workspace with either
 };
 
 struct HostTables {
@@ -42,6 +44,7 @@ struct HostTables {
   std::vector<BoxD> box;
   std::vector<FftPlanD> plans;
   std::vector<long double> twr, twi;  // all twiddle tables, forward sign
+  std::vector<int32_t> pos;           // position tables of the plans
   std::vector<KEntry> kent;
   int32_t kmod_len = 0;
   int32_t kmax_len = 0;
@@ -174,8 +177,8 @@ inline bool small_primes_only(int64_t n) {
   return n == 1;
 }
 
-// Writes the N-entry twiddle table of a plan (at pl.tw) for its current radix
-// schedule: by stage and butterfly, W_N^{j t prod_s} for j < stride_s,
+// Writes the N-entry position table (at pl.pos) and twiddle table (at pl.tw) of
+// a plan for its current radix schedule, the twiddles by stage and butterfly, W_N^{j t prod_s} for j < stride_s,
 // t = 1..radix_s-1, then ones up to N entries.  Sets pl.twoff.
 inline void write_plan_twiddles(HostTables& h, FftPlanD& pl) {
   const int N = pl.N;
@@ -195,6 +198,7 @@ inline void write_plan_twiddles(HostTables& h, FftPlanD& pl) {
     h.twr[pl.tw + o] = 1.0L;
     h.twi[pl.tw + o] = 0.0L;
   }
+  for (int k = 0; k < N; ++k) h.pos[pl.pos + k] = plan_pos(&pl, k);
 }
 
 // Adds (or finds) an FFT plan of length N for the x/y passes or (zp) the z
@@ -211,6 +215,8 @@ inline int add_plan(HostTables& h, int N, bool zp) {
   pl.tw = (int32_t)h.twr.size();
   h.twr.resize(h.twr.size() + N);
   h.twi.resize(h.twi.size() + N);
+  pl.pos = (int32_t)h.pos.size();
+  h.pos.resize(h.pos.size() + N);
   write_plan_twiddles(h, pl);
   h.plans.push_back(pl);
   h.plan_z.push_back(zp ? 1 : 0);
@@ -652,29 +658,53 @@ inline std::vector<Ring> build_rings(const HostTables& h, std::vector<BoxD>& box
   return rings;
 }
 
+// Pencils per heat z tile: the widest of 32, 16 and 8 of which four 256-thread
+// tiles (16 waves) fit a compute unit's LDS, else 4.
+inline int heat_pencils_for(int Pz, int real_bytes) {
+  for (int PB : {32, 16, 8})
+    if (4 * heat_tile_lds(Pz, PB, real_bytes) <= kMaxDynLds) return PB;
+  return 4;
+}
+
 // Fills h.lists for the current batches and z tile.  share: columns share
 // their planes (one batch only); xy_classes / z_classes: one launch per class.
 inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_classes) {
   WorkLists w;
   w.box = h.box;
   const std::vector<Ring> rings = build_rings(h, w.box, share);
-  // spectral addresses: the rings' 9 fields, then the shared planes' results
-  // (at most the guard planes saved: never more than 9 sum P[2] P[1] H)
-  for (const Ring& r : rings) {
-    const BoxD& b0 = w.box[r.boxes[0]];
-    const int64_t pl = (int64_t)b0.P[1] * b0.H;
-    for (int s : r.boxes) {
-      w.box[s].sb = w.elems;
-      w.box[s].sv = pl * (int64_t)r.slot.size();
+  w.tight = w.box;
+  // Spectral addresses: the rings' 9 fields, then the shared planes' results.
+  // Back to back the planes take at most 9 sum P[2] P[1] H (the results are at
+  // most the guard planes saved).  The z pass walks from plane to plane, so a
+  // pitch of many 1 KiB steps sends a tile to few memory channels: line-aligned
+  // pitches, one line longer where they would be a multiple of 8 lines, took
+  // the z pass of one 256^3 box (2064 lines) from 0.62 to 0.40 ms in FP32.
+  const int64_t line = 128 / (int64_t)(2 * real_size(h.prec));
+  auto spread = [&](int64_t pl) {
+    const int64_t lines = (pl + line - 1) / line;
+    return (lines % 8 ? lines : lines + 1) * line;
+  };
+  auto place = [&](std::vector<BoxD>& box, bool pitched) {
+    int64_t at = 0;
+    for (const Ring& r : rings) {
+      const BoxD& b0 = box[r.boxes[0]];
+      const int64_t pl = (int64_t)b0.P[1] * b0.H, pp = pitched ? spread(pl) : pl;
+      for (int s : r.boxes) {
+        box[s].pp = pp;
+        box[s].sb = at;
+        box[s].sv = pp * (int64_t)r.slot.size();
+      }
+      at += 9 * pp * (int64_t)r.slot.size();
+      for (int s : r.boxes) {
+        box[s].xb = at;
+        box[s].xv = pp * (box[s].slo + box[s].shi);
+        at += 6 * box[s].xv;
+      }
     }
-    w.elems += 9 * pl * (int64_t)r.slot.size();
-    for (int s : r.boxes) {
-      BoxD& b = w.box[s];
-      b.xb = w.elems;
-      b.xv = pl * (b.slo + b.shi);
-      w.elems += 6 * b.xv;
-    }
-  }
+    return at;
+  };
+  w.elems = place(w.box, share);
+  w.tight_elems = place(w.tight, false);
   // guard pieces per run of planes with the same ones
   std::vector<std::vector<std::array<int32_t, 2>>> runs(h.nsub);  // per plane [p0, p1)
   for (int s = 0; s < h.nsub; ++s) {
@@ -764,6 +794,12 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
       add_tiles(in, l);
       w.z.back().push_back(l);
     }
+  }
+  if (h.batches.size() == 1) {
+    std::vector<char> in(h.nsub, 1);
+    w.heat.PB = heat_pencils_for(max_padded_z(h), (int)real_size(h.prec));
+    w.heat.lds = (int32_t)heat_tile_lds(max_padded_z(h), w.heat.PB, (int)real_size(h.prec));
+    add_tiles(in, w.heat);
   }
   h.lists = std::move(w);
 }

@@ -71,6 +71,7 @@ struct psatd_plan_s {
   int device = 0;
   void* blob = nullptr;  // device tables
   void* lists = nullptr;  // device work lists (they depend on the knobs)
+  const BoxD* tight = nullptr;  // in lists: the boxes with their spectral planes back to back
   size_t lists_bytes = 0;
   int32_t tune[PSATD_NTUNE] = {0, 1, 0, 0, 0, 0, 0, 16, 256, 512, 0, 1, 0, 0};
   void* ws = nullptr;
@@ -125,6 +126,15 @@ void drop_graphs(psatd_plan_t p) {
   p->graphs.clear();
 }
 
+// The boxes for a workspace of `bytes`: with the pitched planes where they fit
+// (they may take a little more than workspace_need), else back to back.
+const BoxD* boxes_in(const psatd_plan_s* p, int64_t bytes) {
+  const int64_t pitched = p->h.lists.elems * (int64_t)(2 * real_size(p->h.prec));
+  return p->h.batches.size() == 1 && bytes >= pitched ? p->dp.box : p->tight;
+}
+
+// The plan's own workspace is allocated for the pitched planes, or with
+// workspace_need bytes where that is all there is.
 psatd_status ensure_workspace(psatd_plan_t p) {
   if (p->ws && p->ws_bytes >= workspace_need(p)) return PSATD_OK;
   if (p->ws && !p->ws_owned)
@@ -134,8 +144,14 @@ psatd_status ensure_workspace(psatd_plan_t p) {
     HIPCHK(p, hipFree(p->ws));
     p->ws = nullptr;
   }
-  const int64_t need = workspace_need(p);
-  HIPCHK(p, hipMalloc(&p->ws, (size_t)std::max<int64_t>(need, 256)));
+  int64_t need = std::max<int64_t>(workspace_need(p), 256);
+  const int64_t pitched = p->h.lists.elems * (int64_t)(2 * real_size(p->h.prec));
+  if (pitched > need && hipMalloc(&p->ws, (size_t)pitched) == hipSuccess) {
+    need = pitched;
+  } else {
+    if (pitched > need) (void)hipGetLastError();
+    HIPCHK(p, hipMalloc(&p->ws, (size_t)need));
+  }
   p->ws_bytes = need;
   p->ws_owned = true;
   return PSATD_OK;
@@ -148,7 +164,7 @@ psatd_status upload_lists(psatd_plan_t p) {
   HostTables& h = p->h;
   DevPlan& d = p->dp;
   std::vector<unsigned char> hb;
-  size_t off[5];
+  size_t off[6];
   try {
     const bool one = h.batches.size() == 1;
     build_lists(h, one && !d.zreg, d.ntxy == 0 && !h.split && one, d.zcl && one);
@@ -165,6 +181,7 @@ psatd_status upload_lists(psatd_plan_t p) {
     put(2, w.fwd.data(), w.fwd.size() * sizeof(PlaneRec));
     put(3, w.inv.data(), w.inv.size() * sizeof(PlaneRec));
     put(4, w.tiles.data(), w.tiles.size() * sizeof(ZItem));
+    put(5, w.tight.data(), w.tight.size() * sizeof(BoxD));
   } catch (...) {
     return fail(p, PSATD_E_NOMEM, "host allocation failed");
   }
@@ -182,6 +199,7 @@ psatd_status upload_lists(psatd_plan_t p) {
   d.fwd = reinterpret_cast<const PlaneRec*>(base + off[2]);
   d.inv = reinterpret_cast<const PlaneRec*>(base + off[3]);
   d.tiles = reinterpret_cast<const ZItem*>(base + off[4]);
+  p->tight = reinterpret_cast<const BoxD*>(base + off[5]);
   return PSATD_OK;
 }
 
@@ -211,9 +229,13 @@ psatd_status check_fields(psatd_plan_t p, void* const* v, int count, const char*
 psatd_status enqueue_step(psatd_plan_t p, void* const E[3], void* const B[3], void* const J[3],
                           hipStream_t st, bool first, bool keep_j, bool last,
                           std::vector<std::pair<int, std::pair<hipEvent_t, hipEvent_t>>>* prof = nullptr,
-                          void* ws = nullptr) {
-  const DevPlan& d = p->dp;
-  if (!ws) ws = p->ws;
+                          void* ws = nullptr, int64_t ws_bytes = 0) {
+  if (!ws) {
+    ws = p->ws;
+    ws_bytes = p->ws_bytes;
+  }
+  DevPlan d = p->dp;
+  d.box = boxes_in(p, ws_bytes);
   void* eb[6] = {E[0], E[1], E[2], B[0], B[1], B[2]};
   void* in9[9] = {E[0], E[1], E[2], B[0], B[1], B[2], J[0], J[1], J[2]};
   size_t ip = 0;
@@ -276,12 +298,6 @@ psatd_status enqueue_step(psatd_plan_t p, void* const E[3], void* const B[3], vo
   PSATD_MARK(kPhaseExchEB, false);
 #undef PSATD_MARK
   return PSATD_OK;
-}
-
-// LDS of a heat z tile of PB pencils: the staged field, the z twiddles and z indices.
-int32_t heat_lds(const HostTables& h, int PB) {
-  const int maxPz = max_padded_z(h);
-  return (int32_t)((int64_t)maxPz * (PB + 1) * (int64_t)(2 * real_size(h.prec)) + (int64_t)maxPz * 4);
 }
 
 psatd_status check_step_args(psatd_plan_t p, void* const E[3], void* const B[3], void* const J[3]) {
@@ -365,6 +381,7 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   };
   const size_t o_plan = reserve(h.plans.size() * sizeof(FftPlanD));
   const size_t o_tw = reserve(h.twr.size() * cs);
+  const size_t o_pos = reserve(h.pos.size() * 4);
   const size_t o_kmod = reserve((size_t)h.kmod_len * 8);
   const size_t o_kent = reserve(h.kent.size() * sizeof(KEntry));
   const size_t o_nbo = reserve(h.nbr_off.size() * 4);
@@ -386,6 +403,7 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
     const std::vector<unsigned char> t = device_twiddles(h);
     put(o_tw, t.data(), t.size());
   }
+  put(o_pos, h.pos.data(), h.pos.size() * 4);
   put(o_kent, h.kent.data(), h.kent.size() * sizeof(KEntry));
   put(o_nbo, h.nbr_off.data(), h.nbr_off.size() * 4);
   put(o_nbr, h.nbr.data(), h.nbr.size() * 4);
@@ -424,6 +442,7 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   for (int u = 0; u < 3; ++u) d.N[u] = (int32_t)h.N[u];
   d.plans = reinterpret_cast<const FftPlanD*>(B + o_plan);
   d.tw = B + o_tw;
+  d.pos = reinterpret_cast<const int32_t*>(B + o_pos);
   d.kmod = reinterpret_cast<const double*>(B + o_kmod);
   d.nbr_off = reinterpret_cast<const int32_t*>(B + o_nbo);
   d.nbr = reinterpret_cast<const int32_t*>(B + o_nbr);
@@ -531,7 +550,7 @@ psatd_status psatd_step_noalloc(psatd_plan_t p, void* const E[3], void* const B[
                     std::to_string(kScratchBytes) + " bytes; batch the boxes (PSATD_TUNE_BATCH_BOXES)");
   void* ws = scratch_of(p->device);
   if (!ws) return fail(p, PSATD_E_STATE, "static scratch not resolved on the plan's device");
-  return enqueue_step(p, E, B, J, p->stream, true, false, true, nullptr, ws);
+  return enqueue_step(p, E, B, J, p->stream, true, false, true, nullptr, ws, kScratchBytes);
 }
 
 psatd_status psatd_run(psatd_plan_t p, void* const E[3], void* const B[3], void* const J[3],
@@ -584,15 +603,17 @@ psatd_status psatd_heat_run(psatd_plan_t p, void* u, double diffusivity, int32_t
   if (p->dp.split) return fail(p, PSATD_E_UNSUPPORTED, "the heat step needs padded planes that fit the LDS");
   if (p->h.batches.size() != 1) return fail(p, PSATD_E_STATE, "the heat step needs all boxes in one batch");
   if ((r = ensure_workspace(p)) != PSATD_OK) return r;
-  const DevPlan& d = p->dp;
+  DevPlan d = p->dp;
+  d.box = boxes_in(p, p->ws_bytes);
   void* in9[9] = {u, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   void* out6[6] = {u, nullptr, nullptr, nullptr, nullptr, nullptr};
   for (int i = 0; i < nsteps; ++i) {
-    for (const XyLaunch& l : p->h.lists.xy[0]) HIPCHK(p, launch_fwd(d, l, 0, in9, 1, 0, p->ws, p->stream));
-    for (const ZLaunch& l : p->h.lists.z[0])
-      HIPCHK(p, launch_heat_z(d, l, heat_lds(p->h, l.PB), p->ws, diffusivity, d.dt, p->stream));
+    for (const XyLaunch& l : p->h.lists.xy[0]) HIPCHK(p, launch_fwd(d, l, 0, in9, 1, d.pull ? 1 : 0, p->ws, p->stream));
+    HIPCHK(p, launch_heat_z(d, p->h.lists.heat, p->ws, diffusivity, d.dt, p->stream));
     for (const XyLaunch& l : p->h.lists.xy[0]) HIPCHK(p, launch_inv(d, l, 0, p->ws, out6, 1, p->stream));
-    HIPCHK(p, launch_fill(d, out6, 1, p->stream));
+    // pulled as in the field step: guard cells are read from their owners
+    // until the last step leaves the copies consistent
+    if (!d.pull || i == nsteps - 1) HIPCHK(p, launch_fill(d, out6, 1, p->stream));
   }
   return PSATD_OK;
 }
@@ -789,9 +810,11 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
         const std::vector<unsigned char> t = device_twiddles(trial);
         HIPCHK(p, hipMemcpy(const_cast<void*>(d.tw), t.data(), t.size(), hipMemcpyHostToDevice));
       }
+      HIPCHK(p, hipMemcpy(const_cast<int32_t*>(d.pos), trial.pos.data(), trial.pos.size() * 4, hipMemcpyHostToDevice));
       p->h.plans = trial.plans;
       p->h.twr = trial.twr;
       p->h.twi = trial.twi;
+      p->h.pos = trial.pos;
       p->h.maxr = trial.maxr;
       p->h.maxrz = trial.maxrz;
       d.maxr = trial.maxr;

@@ -38,6 +38,7 @@ struct BoxD {
   int64_t soff;    // sum of the half-spectrum sizes of the boxes before it
   int64_t svol;    // half-spectrum size of one field of the box, P[2] P[1] H (complex)
   int64_t sb, sv;  // spectral ring: offset of field 0, field stride (complex)
+  int64_t pp;      // spectral plane pitch (complex), at least P[1] H
   int64_t xb, xv;  // results of the shared planes: offset of field 0, field stride
 };
 
@@ -48,7 +49,7 @@ struct BoxD {
 // of its distinct z-planes, each transformed once along x and y, and the z
 // pass of a box reads its P[2] consecutive slots zb, zb + 1, ... (mod ring).
 // A ring holds the 9 fields back to back, field f at sb + f sv, [slot][ky][kx]
-// each.  The z pass writes the E and B results over the spectra of the box's
+// each, planes pp elements apart.  The z pass writes the E and B results over the spectra of the box's
 // interior planes, except the planes that other boxes of the column still read:
 // those results go to the box's own slots after the ring's fields (slo planes
 // of the low end, then shi of the high end; 6 fields at xb + f xv).  A box that
@@ -68,13 +69,13 @@ PSATD_HD int ring_slot(const BoxD& bx, int z) {
   return s >= bx.ring ? s - bx.ring : s;
 }
 
-// Offset of the result of field f at interior plane i, nq = P[1] H elements
-// per plane (relative to the workspace's first element).
-PSATD_HD int64_t result_plane(const BoxD& bx, int64_t sbias, int f, int i, int nq) {
+// Offset of the result of field f at interior plane i (relative to the
+// workspace's first element).
+PSATD_HD int64_t result_plane(const BoxD& bx, int64_t sbias, int f, int i) {
   const int h = i - (bx.n[2] - bx.shi);
-  if (i < bx.slo) return bx.xb - sbias + f * bx.xv + (int64_t)i * nq;
-  if (h >= 0) return bx.xb - sbias + f * bx.xv + (int64_t)(bx.slo + h) * nq;
-  return bx.sb - sbias + f * bx.sv + (int64_t)ring_slot(bx, bx.g[2] + i) * nq;
+  if (i < bx.slo) return bx.xb - sbias + f * bx.xv + i * bx.pp;
+  if (h >= 0) return bx.xb - sbias + f * bx.xv + (bx.slo + h) * bx.pp;
+  return bx.sb - sbias + f * bx.sv + ring_slot(bx, bx.g[2] + i) * bx.pp;
 }
 
 // One (x, y) plane of the x/y passes' work lists.  Forward: padded plane z of
@@ -178,6 +179,7 @@ struct Tables {
   int32_t nsub;
   const FftPlanD* plans;
   const cx<T>* tw;        // twiddle tables (forward sign)
+  const int32_t* pos;     // position tables (stage-digit order)
   const double* kmod;     // modified wavenumbers (FP64)
 };
 
@@ -565,7 +567,7 @@ PSATD_HD void body_fwd_xy(const FwdArgs<T>& a, int item, int tid, int nt, cx<T>*
   pair_pass_rows<true>(lds, Py, ld, Nh, twr, tid, nt);
   bar();
   eng.template dif<-1, MAXR>(lds, H, 1, ld, ply, twy, tid, nt, bar);
-  cx<T>* dst = spec_at(a.spec, bx, a.sbias, f) + (int64_t)ring_slot(bx, z) * Py * H;
+  cx<T>* dst = spec_at(a.spec, bx, a.sbias, f) + ring_slot(bx, z) * bx.pp;
   copy_grid<8, cx<T>>(Py, H, tid, nt, [&](int, int ky, int kx) { return lds[posy[ky] * ld + kx]; },
                       [&](int i, int, int, cx<T> v) { dst[i] = v; });
 }
@@ -739,6 +741,32 @@ struct UpdArgs {
   UpdConst k;
 };
 
+// Writes the 6 results of a tile (LDS [z][f PB + p], rows of 9 PB) at the
+// interior z-planes only: the inverse pass reads nothing else (the guard planes
+// of E and B are rewritten by the exchange).  A full tile whose pencil runs
+// start at even offsets moves two neighbouring pencils per access.
+template <typename T, int PB>
+PSATD_HD void store_results(const BoxD& bx, cx<T>* dst, int64_t sbias, int q0, int np, const cx<T>* lds, int tid,
+                            int nt) {
+  constexpr int W = 9 * PB;
+  const cx<T>* res = lds + bx.g[2] * W;
+  if (PB % 2 == 0 && np == PB && ((bx.pp | bx.sv | (bx.sb - sbias + q0) | (bx.xb - sbias + q0) | bx.xv) & 1) == 0) {
+    copy_grid3<4, Pair<cx<T>>>(6, bx.n[2], PB / 2, tid, nt,
+        [&](int, int f, int z, int p2) {
+          return *reinterpret_cast<const Pair<cx<T>>*>(res + z * W + f * PB + 2 * p2);
+        },
+        [&](int, int f, int z, int p2, Pair<cx<T>> v) {
+          *reinterpret_cast<Pair<cx<T>>*>(dst + result_plane(bx, sbias, f, z) + 2 * p2) = v;
+        });
+    return;
+  }
+  copy_grid3<8, cx<T>>(6, bx.n[2], PB, tid, nt,
+                       [&](int, int f, int z, int p) { return res[z * W + f * PB + p]; },
+                       [&](int, int f, int z, int p, cx<T> v) {
+                         if (p < np) dst[result_plane(bx, sbias, f, z) + p] = v;
+                       });
+}
+
 // The 9 fields of PB consecutive (ky, kx) pencils are staged in LDS as
 // [z][f * PB + p] (W = 9 PB complex per z row), so that all 9 (then the 6
 // output) fields are transformed by one multi-transform pass with a uniform
@@ -762,13 +790,13 @@ PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
   const int ring = bx.ring, zb = bx.zb;
   auto plane = [&](int z) {
     const int v = zb + z;
-    return (int64_t)(v >= ring ? v - ring : v) * nq;
+    return (v >= ring ? v - ring : v) * bx.pp;
   };
   for (int i = tid; i < Pz; i += nt) twz[i] = gtz[i];
   // a full tile whose pencil runs start at even offsets moves two neighbouring
   // pencils per access
   const bool pairs = (PB % 2) == 0 && np == PB &&
-                     (((int64_t)nq | slab | (bx.sb - a.sbias + q0) | (bx.xb - a.sbias + q0) | bx.xv) & 1) == 0;
+                     ((bx.pp | slab | (bx.sb - a.sbias + q0)) & 1) == 0;
   if (pairs) {
     // up to 8 loads in flight per thread (a 96-plane FP32 tile of 8 pencils is
     // 6.75 pairs per thread of 512: one batch)
@@ -815,26 +843,95 @@ PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
   bar();
   eng.template dit<+1, MAXR>(lds, 6 * PB, 1, W, plz, twz, tid, nt, bar);
 
-  // only the interior z-planes: the inverse pass reads nothing else (the guard
-  // planes of E and B are rewritten by the exchange)
-  const int gz = bx.g[2];
-  const cx<T>* res = lds + gz * W;
-  cx<T>* dst = a.spec + q0;
-  if (pairs) {
-    copy_grid3<4, Pair<cx<T>>>(6, bx.n[2], PB / 2, tid, nt,
-        [&](int, int f, int z, int p2) {
-          return *reinterpret_cast<const Pair<cx<T>>*>(res + z * W + f * PB + 2 * p2);
-        },
-        [&](int, int f, int z, int p2, Pair<cx<T>> v) {
-          *reinterpret_cast<Pair<cx<T>>*>(dst + result_plane(bx, a.sbias, f, z, nq) + 2 * p2) = v;
-        });
-    return;
+  store_results<T, PB>(bx, a.spec + q0, a.sbias, q0, np, lds, tid, nt);
+}
+
+// Loads of the first z stage: element z of transform m = f PB + p is the plane
+// at ring slot zb + z.  The slot is a uniform part per q plus the lane's j; a
+// lane is checked against the end of the ring only in the one q it may fall in.
+template <typename T, int PB>
+struct ZLoad {
+  const cx<T>* src;  // field 0, slot 0, first pencil of the tile
+  const BoxD& bx;
+  int np;            // pencils in the tile
+  template <int R>
+  PSATD_HD void run(int m, int j, int ms, cx<T>* a) const {
+    const int f = m / PB, p = m - f * PB;
+    const int64_t pp = bx.pp;
+    const int ring = bx.ring, wrap = ring - bx.zb;
+    // the idle pencils of a box's last tile repeat its last one
+    const cx<T>* base = src + (f * bx.sv + j * pp + (p < np ? p : np - 1));
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+      const int z0 = q * ms;
+      const cx<T>* e = base + (z0 >= wrap ? z0 - wrap : z0 + bx.zb) * pp;
+      if (z0 < wrap && z0 + ms > wrap && j >= wrap - z0) e -= ring * pp;
+      a[q] = *e;
+    }
   }
-  copy_grid3<8, cx<T>>(6, bx.n[2], PB, tid, nt,
-                       [&](int, int f, int z, int p) { return res[z * W + f * PB + p]; },
-                       [&](int, int f, int z, int p, cx<T> v) {
-                         if (p < np) dst[result_plane(bx, a.sbias, f, z, nq) + p] = v;
-                       });
+};
+
+// The z pass of the vector-ALU forms.  Same tile as body_z_update, with the
+// first z stage reading the ring's planes straight into its butterflies, and
+// with the update taking the points kz and -kz of a pencil together: they share
+// |[k]| and so the FP64 coefficients.  The results go out through the LDS in
+// whole pencil runs: stores straight from the last stage's butterflies measured
+// 1.0 -> 1.5 ms (64 boxes of 96^3 padded, FP32).  Issue-bound (65 % of the time
+// is VALU busy); with the loads and pairs as here 1.03 -> 0.93 ms, FP64 2.32 ->
+// 2.03 ms, 8 boxes of 176^3 in FP64 2.44 -> 2.07 ms.
+template <typename T, int PB, bool INC, int MAXR, class Bar>
+PSATD_HD void body_z_direct(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar) {
+  const ZItem it = a.items[item];
+  const BoxD& bx = a.t.box[it.box];
+  const int Pz = bx.P[2], H = bx.H, nq = bx.P[1] * H, q0 = it.q0;
+  const FftPlanD* plz = a.t.plans + bx.planz;
+  constexpr int W = 9 * PB;
+  cx<T>* twz = lds + Pz * W;
+  int32_t* pos = reinterpret_cast<int32_t*>(twz + Pz);  // slot of each frequency
+  const cx<T>* gtz = a.t.tw + plz->tw;
+  const int32_t* gpos = a.t.pos + plz->pos;
+  for (int i = tid; i < Pz; i += nt) {
+    twz[i] = gtz[i];
+    pos[i] = gpos[i];
+  }
+  const int np = (nq - q0) < PB ? (nq - q0) : PB;
+  bar();
+  first_stage_dispatch<-1, MAXR, W, W>(plz, lds, twz, tid, nt,
+                                       ZLoad<T, PB>{spec_at(a.spec, bx, a.sbias, 0) + q0, bx, np});
+  bar();
+  fft_dif_inner<-1, MAXR>(lds, W, 1, W, plz, twz, tid, nt, bar);
+
+  const double* kxt = a.t.kmod + bx.kx;
+  const double* kyt = a.t.kmod + bx.ky;
+  const double* kzt = a.t.kmod + bx.kz;
+  const FastDiv dH = make_fastdiv((uint32_t)H);
+  const double rc = 1.0 / a.k.c;
+  for (int i = tid; i < (Pz / 2 + 1) * PB; i += nt) {
+    const int kz = (int)((uint32_t)i / (uint32_t)PB);
+    const int p = i - kz * PB;
+    if (p >= np) continue;
+    const int q = q0 + p;
+    const int ky = (int)fdiv((uint32_t)q, dH);
+    UpdCoef<T> u = update_coef<T, INC>(kxt[q - ky * H], kyt[ky], kzt[kz], a.k.c, rc, a.k.dt);
+    // [k](-kz) = -[k](kz), and both entries are 0 at kz = 0 and Nyquist
+    for (int k = kz;; k = Pz - kz, u.kz = -u.kz) {
+      cx<T>* row = lds + pos[k] * W + p;
+      T vr[9], vi[9];
+#pragma unroll
+      for (int f = 0; f < 9; ++f) {
+        const cx<T> v = row[f * PB];
+        vr[f] = v.x;
+        vi[f] = v.y;
+      }
+      update_apply<T>(vr, vi, u);
+#pragma unroll
+      for (int f = 0; f < 6; ++f) row[f * PB] = cx<T>{vr[f], vi[f]};
+      if (k != kz || kz == 0 || 2 * kz == Pz) break;
+    }
+  }
+  bar();
+  fft_dit<+1, MAXR>(lds, 6 * PB, 1, W, plz, twz, tid, nt, bar);
+  store_results<T, PB>(bx, a.spec + q0, a.sbias, q0, np, lds, tid, nt);
 }
 
 // ------------------------------------------------------- heat equation
@@ -850,61 +947,96 @@ struct HeatArgs {
   double D, dt;
 };
 
+// LDS of a heat z tile of PB pencils: the staged field, the z twiddles, the
+// propagator's z and (kx, ky) factors (FP64) and the positions of the frequencies.
+PSATD_HD int64_t heat_tile_lds(int Pz, int PB, int real_bytes) {
+  return (int64_t)Pz * (PB + 1) * 2 * real_bytes + (int64_t)(Pz + PB) * 8 + (int64_t)Pz * 4;
+}
+
 // PB consecutive (ky, kx) pencils staged as [z][p]: forward z transform,
-// multiply by g = exp(-D |[k]|^2 dt) in FP64 (INC: by g - 1 = expm1(...), the
-// increment's spectrum), inverse z transform.
+// multiply by g = exp(-D |[k]|^2 dt) in FP64 (INC: by g - 1, the increment's
+// spectrum), inverse z transform.  g is the product of a factor per kz and one
+// per (kx, ky), so a tile takes Pz + PB exponentials instead of Pz PB:
+// g1 g2, or (g1 - 1) + (g2 - 1) + (g1 - 1)(g2 - 1), whose terms the product
+// cannot cancel (both factors are in (0, 1]).  One field in LDS leaves room for
+// wide tiles: 32 pencils (256-byte runs) in place of the field pass's 10, with
+// the factors and the direct loads, 0.29 -> 0.15 ms on 64 boxes of 96^3 padded, FP32.
 template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_z_heat(const HeatArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar,
                           Eng eng = Eng{}) {
   const ZItem it = a.items[item];
   const BoxD& bx = a.t.box[it.box];
-  const int Py = bx.P[1], Pz = bx.P[2], H = bx.H;
-  const int nq = Py * H;
+  const int Pz = bx.P[2], H = bx.H;
+  const int nq = bx.P[1] * H;
   const int q0 = it.q0;
   const int np = (nq - q0) < PB ? (nq - q0) : PB;
   const FftPlanD* plz = a.t.plans + bx.planz;
   cx<T>* twz = lds + Pz * PB;
-  int32_t* kzi = reinterpret_cast<int32_t*>(twz + Pz);
+  double* gz1 = reinterpret_cast<double*>(twz + Pz);
+  double* gxy = gz1 + Pz;
+  int32_t* pos = reinterpret_cast<int32_t*>(gxy + PB);
   const cx<T>* gtz = a.t.tw + plz->tw;
-  for (int i = tid; i < Pz; i += nt) kzi[i] = plan_index(plz, i);
-  const cx<T>* col = spec_at(a.spec, bx, 0, 0) + q0;
-  const int ndata = Pz * PB;
-  copy_batched<8, cx<T>>(ndata + Pz, tid, nt,
-      [&](int i) {
-        if (i >= ndata) return gtz[i - ndata];
-        const int p = i % PB;
-        return (p < np) ? col[(int64_t)ring_slot(bx, i / PB) * nq + p] : cx<T>{T(0), T(0)};
-      },
-      [&](int i, cx<T> v) {
-        if (i >= ndata) twz[i - ndata] = v;
-        else lds[i] = v;
-      });
-  bar();
-  eng.template dif<-1, MAXR>(lds, PB, 1, PB, plz, twz, tid, nt, bar);
+  const int32_t* gpos = a.t.pos + plz->pos;
+  for (int i = tid; i < Pz; i += nt) {
+    twz[i] = gtz[i];
+    pos[i] = gpos[i];
+  }
+  const cx<T>* src = spec_at(a.spec, bx, 0, 0) + q0;
+  if constexpr (std::is_same<Eng, FftValu>::value) {
+    bar();
+    first_stage_dispatch<-1, MAXR, PB, PB>(plz, lds, twz, tid, nt, ZLoad<T, PB>{src, bx, np});
+  } else {  // the matrix-core first stage takes its elements from the LDS
+    copy_grid<8, cx<T>>(Pz, PB, tid, nt,
+                        [&](int, int z, int p) { return src[ring_slot(bx, z) * bx.pp + (p < np ? p : np - 1)]; },
+                        [&](int i, int, int, cx<T> v) { lds[i] = v; });
+  }
   const double* kxt = a.t.kmod + bx.kx;
   const double* kyt = a.t.kmod + bx.ky;
   const double* kzt = a.t.kmod + bx.kz;
   const FastDiv dH = make_fastdiv((uint32_t)H);
-  for (int i = tid; i < ndata; i += nt) {
-    const int p = i % PB;
-    if (p >= np) continue;
-    const int q = q0 + p;
-    const int ky = (int)fdiv((uint32_t)q, dH);
-    const int kx = q - ky * H;
-    const double k1 = kxt[kx], k2 = kyt[ky], k3 = kzt[kzi[i / PB]];
-    const double e = -a.D * (k1 * k1 + k2 * k2 + k3 * k3) * a.dt;
-    const T g = (T)(INC ? expm1(e) : exp(e));
-    lds[i] = cx<T>{lds[i].x * g, lds[i].y * g};
+  for (int i = tid; i < Pz + PB; i += nt) {
+    double k2;
+    if (i < Pz) {
+      k2 = kzt[i] * kzt[i];
+    } else {
+      const int q = q0 + (i - Pz < np ? i - Pz : np - 1);
+      const int ky = (int)fdiv((uint32_t)q, dH);
+      const double k1 = kxt[q - ky * H];
+      k2 = k1 * k1 + kyt[ky] * kyt[ky];
+    }
+    const double e = -a.D * k2 * a.dt;
+    gz1[i] = INC ? expm1(e) : exp(e);
+  }
+  bar();
+  if constexpr (std::is_same<Eng, FftValu>::value)
+    fft_dif_inner<-1, MAXR>(lds, PB, 1, PB, plz, twz, tid, nt, bar);
+  else
+    eng.template dif<-1, MAXR>(lds, PB, 1, PB, plz, twz, tid, nt, bar);
+  for (int i = tid; i < Pz * PB; i += nt) {
+    const int k = (int)((uint32_t)i / (uint32_t)PB);
+    const int p = i - k * PB;
+    const double ga = gz1[k], gb = gxy[p];
+    const T g = (T)(INC ? fma(ga, gb, ga + gb) : ga * gb);
+    cx<T>* v = lds + pos[k] * PB + p;
+    *v = cx<T>{v->x * g, v->y * g};
   }
   bar();
   eng.template dit<+1, MAXR>(lds, PB, 1, PB, plz, twz, tid, nt, bar);
   // interior z-planes only (all the inverse pass reads)
   const int gz = bx.g[2];
-  copy_batched<8, cx<T>>(bx.n[2] * PB, tid, nt, [&](int i) { return lds[gz * PB + i]; },
-                         [&](int i, cx<T> v) {
-                           const int p = i % PB;
-                           if (p < np) a.spec[result_plane(bx, 0, 0, i / PB, nq) + q0 + p] = v;
-                         });
+  cx<T>* dst = a.spec + q0;
+  if (np == PB && ((bx.pp | (bx.sb + q0) | (bx.xb + q0)) & 1) == 0) {
+    copy_grid<4, Pair<cx<T>>, true>(bx.n[2], PB / 2, tid, nt,
+        [&](int, int z, int p2) { return *reinterpret_cast<const Pair<cx<T>>*>(lds + (gz + z) * PB + 2 * p2); },
+        [&](int, int z, int p2, Pair<cx<T>> v) {
+          *reinterpret_cast<Pair<cx<T>>*>(dst + result_plane(bx, 0, 0, z) + 2 * p2) = v;
+        });
+    return;
+  }
+  copy_grid<8, cx<T>, true>(bx.n[2], PB, tid, nt, [&](int, int z, int p) { return lds[(gz + z) * PB + p]; },
+                            [&](int, int z, int p, cx<T> v) {
+                              if (p < np) dst[result_plane(bx, 0, 0, z) + p] = v;
+                            });
 }
 
 // ------------------------------------------------------------------ pass I
@@ -952,7 +1084,7 @@ PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>*
   bar();
 
   // half-spectrum rows (ky natural) -> LDS rows in stage-digit order along y
-  const cx<T>* src = a.spec + result_plane(bx, a.sbias, f, rec.z, Py * H);
+  const cx<T>* src = a.spec + result_plane(bx, a.sbias, f, rec.z);
   for (int i = tid; i < Py + Nh + Px; i += nt)  // twy, twx, twr are contiguous
     twy[i] = i < Py ? gty[i] : (i < Py + Nh ? gtx[i - Py] : gtr[i - Py - Nh]);
   // FP32: two spectrum entries per access (measured slower in FP64)
@@ -1111,7 +1243,7 @@ PSATD_HD void body_x_fwd(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>
   eng.template dit<-1, MAXR>(lds, ny, ld, 1, plx, twx, tid, nt, bar);
   pair_pass_rows<true>(lds, ny, ld, Nh, twr, tid, nt);
   bar();
-  cx<T>* dst = spec_at(a.spec, bx, 0, f) + ((int64_t)ring_slot(bx, z) * Py + y0) * H;
+  cx<T>* dst = spec_at(a.spec, bx, 0, f) + ring_slot(bx, z) * bx.pp + (int64_t)y0 * H;
   const FastDiv dH = make_fastdiv((uint32_t)H);
   copy_batched<8, cx<T>>(ny * H, tid, nt,
                          [&](int i) {
@@ -1137,8 +1269,8 @@ PSATD_HD void body_y(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>* ld
   int32_t* posy = reinterpret_cast<int32_t*>(twy + Py);
   for (int i = tid; i < Py; i += nt) posy[i] = plan_pos(ply, i);
   bar();
-  cx<T>* col = c0 + (DIR < 0 ? spec_at(a.spec, bx, 0, f) + (int64_t)ring_slot(bx, rec.z) * Py * H
-                             : a.spec + result_plane(bx, 0, f, rec.z, Py * H));
+  cx<T>* col = c0 + (DIR < 0 ? spec_at(a.spec, bx, 0, f) + ring_slot(bx, rec.z) * bx.pp
+                             : a.spec + result_plane(bx, 0, f, rec.z));
   const cx<T>* gty = a.t.tw + ply->tw;
   const int ntot = Py * kCB;
   copy_batched<8, cx<T>>(ntot + Py, tid, nt,
@@ -1192,7 +1324,7 @@ PSATD_HD void body_x_inv(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>
   cx<T>* twr = twx + Nh;
   int32_t* posx = reinterpret_cast<int32_t*>(twr + Px);
   for (int i = tid; i < Nh; i += nt) posx[i] = plan_pos(plx, i);
-  const cx<T>* src = a.spec + result_plane(bx, 0, f, zz, Py * H) + (int64_t)y0 * H;
+  const cx<T>* src = a.spec + result_plane(bx, 0, f, zz) + (int64_t)y0 * H;
   const cx<T>* gtx = a.t.tw + plx->tw;
   const cx<T>* gtr = a.t.tw + bx.twr;
   const int nrow = ny * H;

@@ -77,8 +77,10 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 1) void k_z_update(UpdArgs
                                                                           int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_z_update<T, PB, INC, MAXR>(a, it, threadIdx.x, NT, lds, BlockBarrier{},
-                                    typename EngOf<SPL>::type{});
+    if constexpr (SPL == 0)
+      body_z_direct<T, PB, INC, MAXR>(a, it, threadIdx.x, NT, lds, BlockBarrier{});
+    else
+      body_z_update<T, PB, INC, MAXR>(a, it, threadIdx.x, NT, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
     __syncthreads();
   }
 }
@@ -180,6 +182,7 @@ static Tables<T> tables(const DevPlan& p) {
   t.nsub = p.nsub;
   t.plans = p.plans;
   t.tw = reinterpret_cast<const cx<T>*>(p.tw);
+  t.pos = p.pos;
   t.kmod = p.kmod;
   return t;
 }
@@ -216,9 +219,8 @@ hipError_t prepare_t(int ldsF, int ldsI, int ldsU, int ldsX, int ldsY) {
     if (ldsI <= kMaxDynLds && (e = set_lds(f, ldsI)) != hipSuccess) return e;
   for (const void* f : upd)
     if ((e = set_lds(f, ldsU)) != hipSuccess) return e;
-  const void* heat[] = {(const void*)k_z_heat<T, 4, I, MAXR, SPL>, (const void*)k_z_heat<T, 6, I, MAXR, SPL>,
-                        (const void*)k_z_heat<T, 8, I, MAXR, SPL>, (const void*)k_z_heat<T, 10, I, MAXR, SPL>,
-                        (const void*)k_z_heat<T, 16, I, MAXR, SPL>};
+  const void* heat[] = {(const void*)k_z_heat<T, 4, I, MAXR, SPL>, (const void*)k_z_heat<T, 8, I, MAXR, SPL>,
+                        (const void*)k_z_heat<T, 16, I, MAXR, SPL>, (const void*)k_z_heat<T, 32, I, MAXR, SPL>};
   for (const void* f : heat)
     if ((e = set_lds(f, ldsU)) != hipSuccess) return e;
   if ((e = set_lds((const void*)k_x_fwd<T, MAXR, SPL>, ldsX)) != hipSuccess) return e;
@@ -356,7 +358,7 @@ hipError_t inv_t(const DevPlan& p, const XyLaunch& l, int64_t sbias, const void*
 }
 
 template <typename T, int SPL>
-hipError_t heat_z_t(const DevPlan& p, const ZLaunch& l, int lds, void* spec, double D, double dt, hipStream_t st) {
+hipError_t heat_z_t(const DevPlan& p, const ZLaunch& l, void* spec, double D, double dt, hipStream_t st) {
   const int g = grid_for(l.nu, p.grid_cap[kPhaseUpd]);
   if (!g) return hipSuccess;
   HeatArgs<T> a;
@@ -369,17 +371,16 @@ hipError_t heat_z_t(const DevPlan& p, const ZLaunch& l, int lds, void* spec, dou
   auto go = [&](auto pbc) -> hipError_t {
     constexpr int PB = decltype(pbc)::value;
     PSATD_MAXR_SWITCH(SPL, p.maxrz,
-                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 8, SPL>), dim3(g), dim3(kThreadsXY), lds, st, a, l.nu,
+                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 8, SPL>), dim3(g), dim3(kThreadsXY), l.lds, st, a, l.nu,
                                          p.xcd),
-                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 16, SPL>), dim3(g), dim3(kThreadsXY), lds, st, a, l.nu,
+                      hipLaunchKernelGGL((k_z_heat<T, PB, I, 16, SPL>), dim3(g), dim3(kThreadsXY), l.lds, st, a, l.nu,
                                          p.xcd));
     return hipGetLastError();
   };
-  if (l.PB == 4) return go(std::integral_constant<int, 4>{});
-  if (l.PB == 6) return go(std::integral_constant<int, 6>{});
-  if (l.PB == 10) return go(std::integral_constant<int, 10>{});
+  if (l.PB == 32) return go(std::integral_constant<int, 32>{});
+  if (l.PB == 16) return go(std::integral_constant<int, 16>{});
   if (l.PB == 8) return go(std::integral_constant<int, 8>{});
-  return go(std::integral_constant<int, 16>{});
+  return go(std::integral_constant<int, 4>{});
 }
 
 template <typename T>
@@ -459,7 +460,7 @@ hipError_t x_inv_t(const DevPlan& p, const XyLaunch& l, const void* spec, void* 
   KIND template hipError_t upd_t<T, SPL>(const DevPlan&, const ZLaunch&, int64_t, void*, hipStream_t);           \
   KIND template hipError_t inv_t<T, SPL>(const DevPlan&, const XyLaunch&, int64_t, const void*, void* const*,    \
                                          int, hipStream_t);                                                      \
-  KIND template hipError_t heat_z_t<T, SPL>(const DevPlan&, const ZLaunch&, int, void*, double, double,          \
+  KIND template hipError_t heat_z_t<T, SPL>(const DevPlan&, const ZLaunch&, void*, double, double,          \
                                             hipStream_t);                                                        \
   KIND template hipError_t x_fwd_t<T, SPL>(const DevPlan&, const XyLaunch&, void* const*, int, void*,            \
                                            hipStream_t);                                                         \
@@ -530,9 +531,9 @@ hipError_t launch_inv(const DevPlan& p, const XyLaunch& l, int64_t sbias, const 
   PSATD_BY_FORM(inv_t, p, l, sbias, spec, out6, nf, st);
 }
 
-hipError_t launch_heat_z(const DevPlan& p, const ZLaunch& l, int lds, void* spec, double D, double dt,
+hipError_t launch_heat_z(const DevPlan& p, const ZLaunch& l, void* spec, double D, double dt,
                          hipStream_t st) {
-  PSATD_BY_FORM(heat_z_t, p, l, lds, spec, D, dt, st);
+  PSATD_BY_FORM(heat_z_t, p, l, spec, D, dt, st);
 }
 
 hipError_t launch_x_fwd(const DevPlan& p, const XyLaunch& l, void* const* in9, int nf, void* spec, hipStream_t st) {

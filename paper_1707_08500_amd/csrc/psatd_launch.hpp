@@ -16,6 +16,7 @@ struct DevPlan {
   const BoxD* box;          // with the spectral addresses of the current lists
   const FftPlanD* plans;
   const void* tw;           // cx<double> or cx<float> twiddles
+  const int32_t* pos;       // position tables of the FFT plans
   const double* kmod;
   const int32_t* nbr_off;
   const int32_t* nbr;
@@ -64,8 +65,7 @@ hipError_t launch_upd_reg(const DevPlan& p, void* spec, hipStream_t st);
 hipError_t launch_inv(const DevPlan& p, const XyLaunch& l, int64_t sbias, const void* spec, void* const* out6, int nf,
                       hipStream_t st);
 // heat equation (Sec. 5): z pass of one field with the exp(-D |[k]|^2 dt) propagator
-hipError_t launch_heat_z(const DevPlan& p, const ZLaunch& l, int lds, void* spec, double D, double dt,
-                         hipStream_t st);
+hipError_t launch_heat_z(const DevPlan& p, const ZLaunch& l, void* spec, double D, double dt, hipStream_t st);
 // split x/y passes (whole plan, no batching)
 hipError_t launch_x_fwd(const DevPlan& p, const XyLaunch& l, void* const* in9, int nf, void* spec, hipStream_t st);
 hipError_t launch_y(const DevPlan& p, const XyLaunch& l, int dir, int nf, void* spec, hipStream_t st);

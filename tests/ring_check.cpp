@@ -32,6 +32,78 @@ struct Box {
   int32_t g[3];
 };
 
+void check_places(const char* name, const HostTables& h, const int64_t N[3], const std::vector<BoxD>& box,
+                  int64_t elems, bool shared) {
+  const WorkLists& w = h.lists;
+  const int nsub = h.nsub;
+  // what the forward pass leaves at each (field, plane) address: box and z
+  std::map<int64_t, PlaneRec> at;
+  int64_t planes = 0, nfwd = 0;
+  for (const auto& ls : w.xy)
+    for (const XyLaunch& l : ls) nfwd += l.nf;
+  CHECK(nfwd == (int64_t)w.fwd.size(), "%s: launches cover the planes", name);
+  for (const PlaneRec& r : w.fwd) {
+    const BoxD& b = box[r.box];
+    const int64_t nq = b.pp, used = (int64_t)b.P[1] * b.H;
+    for (int f = 0; f < 9; ++f) {
+      const int64_t o = b.sb + f * b.sv + ring_slot(b, r.z) * nq;
+      CHECK(ring_slot(b, r.z) < b.ring && !at.count(o), "%s: plane written once", name);
+      at[o] = r;
+    }
+    planes += used;
+  }
+  CHECK((planes < h.slab) == (shared), "%s: sharing", name);
+  std::set<int64_t> results;
+  for (int s = 0; s < nsub; ++s) {
+    const BoxD& b = box[s];
+    const int64_t nq = b.pp;
+    auto globz = [&](const BoxD& c, int z) { return ((c.lo[2] - c.g[2] + z) % N[2] + N[2]) % N[2]; };
+    for (int z = 0; z < b.P[2]; ++z)
+      for (int f = 0; f < 9; ++f) {
+        const auto it = at.find(b.sb + f * b.sv + ring_slot(b, z) * nq);
+        CHECK(it != at.end(), "%s: box %d plane %d has a source", name, s, z);
+        const BoxD& c = box[it->second.box];
+        CHECK(globz(c, it->second.z) == globz(b, z) && c.lo[0] == b.lo[0] && c.n[0] == b.n[0] &&
+                  c.g[0] == b.g[0] && c.lo[1] == b.lo[1] && c.n[1] == b.n[1] && c.g[1] == b.g[1],
+              "%s: box %d plane %d is the same plane", name, s, z);
+      }
+    for (int f = 0; f < 6; ++f)
+      for (int i = 0; i < b.n[2]; ++i) {
+        const int64_t o = result_plane(b, 0, f, i);
+        CHECK(o >= 0 && o + nq <= elems && results.insert(o).second, "%s: result planes distinct", name);
+        for (int t = 0; t < nsub; ++t) {
+          const BoxD& c = box[t];
+          if (t == s) continue;
+          for (int z = 0; z < c.P[2]; ++z)
+            CHECK(o != c.sb + f * c.sv + ring_slot(c, z) * c.pp,
+                  "%s: result of box %d over a plane box %d reads", name, s, t);
+        }
+      }
+    for (int f = 6; f < 9; ++f)  // the held current's spectra outlive the z pass
+      for (int z = 0; z < b.P[2]; ++z)
+        CHECK(!results.count(b.sb + f * b.sv + ring_slot(b, z) * nq), "%s: J kept", name);
+  }
+  // every tile of every box once, the guard pieces of each plane those that meet it
+  std::set<std::pair<int, int>> tiles;
+  for (const ZLaunch& l : w.z[0])
+    for (int i = l.u0; i < l.u0 + l.nu; ++i)
+      for (int q = w.tiles[i].q0; q < w.tiles[i].q0 + l.PB && q < box[w.tiles[i].box].P[1] * box[w.tiles[i].box].H; ++q)
+        CHECK(tiles.insert({w.tiles[i].box, q}).second, "%s: pencil once", name);
+  int64_t pencils = 0;
+  for (const BoxD& b : box) pencils += (int64_t)b.P[1] * b.H;
+  CHECK((int64_t)tiles.size() == pencils, "%s: every pencil", name);
+  for (const PlaneRec& r : w.fwd) {
+    const BoxD& b = box[r.box];
+    int64_t cells = 0;
+    for (int i = r.p0; i < r.p1; ++i) {
+      CHECK(r.z >= w.pull[i].qz && r.z < w.pull[i].qz + w.pull[i].lz, "%s: piece of the plane", name);
+      cells += (int64_t)w.pull[i].ly * w.pull[i].lx;
+    }
+    const bool inner = r.z >= b.g[2] && r.z < b.g[2] + b.n[2];
+    CHECK(cells == (int64_t)b.P[0] * b.P[1] - (inner ? (int64_t)b.n[0] * b.n[1] : 0), "%s: plane covered", name);
+  }
+}
+
 void check(const char* name, const int64_t N[3], const std::vector<Box>& bx, bool expect_shared) {
   std::vector<int64_t> lo, n;
   std::vector<int32_t> g;
@@ -49,78 +121,12 @@ void check(const char* name, const int64_t N[3], const std::vector<Box>& bx, boo
                    PSATD_J_REPLICATED) == PSATD_OK, "%s: %s", name, err.c_str());
   for (int share = 0; share < 2; ++share) {
     build_lists(h, share != 0, !h.xyc.empty(), !h.zcls.empty());
-    const WorkLists& w = h.lists;
-    CHECK(w.elems <= 9 * h.slab, "%s: workspace", name);
-    // what the forward pass leaves at each (field, plane) address: box and z
-    std::map<int64_t, PlaneRec> at;
-    int64_t planes = 0, nfwd = 0;
-    for (const auto& ls : w.xy)
-      for (const XyLaunch& l : ls) nfwd += l.nf;
-    CHECK(nfwd == (int64_t)w.fwd.size(), "%s: launches cover the planes", name);
-    for (const PlaneRec& r : w.fwd) {
-      const BoxD& b = w.box[r.box];
-      const int64_t nq = (int64_t)b.P[1] * b.H;
-      for (int f = 0; f < 9; ++f) {
-        const int64_t o = b.sb + f * b.sv + ring_slot(b, r.z) * nq;
-        CHECK(ring_slot(b, r.z) < b.ring && !at.count(o), "%s: plane written once", name);
-        at[o] = r;
-      }
-      planes += nq;
-    }
-    CHECK((planes < h.slab) == (share && expect_shared), "%s: sharing", name);
-    std::set<int64_t> results;
-    for (int s = 0; s < nsub; ++s) {
-      const BoxD& b = w.box[s];
-      const int64_t nq = (int64_t)b.P[1] * b.H;
-      auto globz = [&](const BoxD& c, int z) { return ((c.lo[2] - c.g[2] + z) % N[2] + N[2]) % N[2]; };
-      for (int z = 0; z < b.P[2]; ++z)
-        for (int f = 0; f < 9; ++f) {
-          const auto it = at.find(b.sb + f * b.sv + ring_slot(b, z) * nq);
-          CHECK(it != at.end(), "%s: box %d plane %d has a source", name, s, z);
-          const BoxD& c = w.box[it->second.box];
-          CHECK(globz(c, it->second.z) == globz(b, z) && c.lo[0] == b.lo[0] && c.n[0] == b.n[0] &&
-                    c.g[0] == b.g[0] && c.lo[1] == b.lo[1] && c.n[1] == b.n[1] && c.g[1] == b.g[1],
-                "%s: box %d plane %d is the same plane", name, s, z);
-        }
-      for (int f = 0; f < 6; ++f)
-        for (int i = 0; i < b.n[2]; ++i) {
-          const int64_t o = result_plane(b, 0, f, i, (int)nq);
-          CHECK(o >= 0 && o + nq <= w.elems && results.insert(o).second, "%s: result planes distinct", name);
-          for (int t = 0; t < nsub; ++t) {
-            const BoxD& c = w.box[t];
-            if (t == s) continue;
-            for (int z = 0; z < c.P[2]; ++z)
-              CHECK(o != c.sb + f * c.sv + (int64_t)ring_slot(c, z) * c.P[1] * c.H,
-                    "%s: result of box %d over a plane box %d reads", name, s, t);
-          }
-        }
-      for (int f = 6; f < 9; ++f)  // the held current's spectra outlive the z pass
-        for (int z = 0; z < b.P[2]; ++z)
-          CHECK(!results.count(b.sb + f * b.sv + ring_slot(b, z) * nq), "%s: J kept", name);
-    }
-    // every tile of every box once, the guard pieces of each plane those that meet it
-    std::set<std::pair<int, int>> tiles;
-    for (const ZLaunch& l : w.z[0])
-      for (int i = l.u0; i < l.u0 + l.nu; ++i)
-        for (int q = w.tiles[i].q0; q < w.tiles[i].q0 + l.PB && q < w.box[w.tiles[i].box].P[1] * w.box[w.tiles[i].box].H; ++q)
-          CHECK(tiles.insert({w.tiles[i].box, q}).second, "%s: pencil once", name);
-    int64_t pencils = 0;
-    for (const BoxD& b : w.box) pencils += (int64_t)b.P[1] * b.H;
-    CHECK((int64_t)tiles.size() == pencils, "%s: every pencil", name);
-    for (const PlaneRec& r : w.fwd) {
-      const BoxD& b = w.box[r.box];
-      int64_t cells = 0;
-      for (int i = r.p0; i < r.p1; ++i) {
-        CHECK(r.z >= w.pull[i].qz && r.z < w.pull[i].qz + w.pull[i].lz, "%s: piece of the plane", name);
-        cells += (int64_t)w.pull[i].ly * w.pull[i].lx;
-      }
-      const bool inner = r.z >= b.g[2] && r.z < b.g[2] + b.n[2];
-      CHECK(cells == (int64_t)b.P[0] * b.P[1] - (inner ? (int64_t)b.n[0] * b.n[1] : 0), "%s: plane covered", name);
-    }
+    CHECK(h.lists.tight_elems <= 9 * h.slab, "%s: workspace", name);
+    check_places(name, h, N, h.lists.tight, h.lists.tight_elems, share && expect_shared);
+    check_places(name, h, N, h.lists.box, h.lists.elems, share && expect_shared);
   }
   std::printf("%s ok\n", name);
 }
-
 std::vector<Box> column(std::vector<int64_t> nz, std::vector<int32_t> gz, int nx, int32_t gx) {
   std::vector<Box> out;
   int64_t z = 0;
