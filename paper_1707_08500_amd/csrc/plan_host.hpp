@@ -51,7 +51,9 @@ struct HostTables {
   std::vector<int32_t> cut[3];
   int32_t ncut[3];
   std::vector<int32_t> owner;
-  std::vector<int32_t> nbr_off, nbr;
+  std::vector<SumRegion> sumr;    // deposited currents: regions of equal copies, the
+  std::vector<SumCopy> sumc;      // copies, and the work list over their z-planes
+  std::vector<int32_t> itemsS, regionOf;
   std::vector<int32_t> itemsF, itemsU, itemsI, itemsP, itemsN;
   WorkLists lists;
   bool split = false;  // x/y pass split into x rows and y columns (large planes)
@@ -383,18 +385,13 @@ struct Run {
 inline void axis_runs(int64_t lo_s, int64_t n_s, int64_t lo_d, int64_t g_d, int64_t P_d, int64_t N,
                       std::vector<Run>& out) {
   out.clear();
-  for (int64_t q = 0; q < P_d; ++q) {
-    const int64_t G = ((lo_d - g_d + q) % N + N) % N;
-    const int64_t i = ((G - lo_s) % N + N) % N;
-    if (i >= n_s) continue;
-    if (!out.empty()) {
-      Run& r = out.back();
-      if (r.q0 + r.len == q && r.i0 + r.len == i) {
-        ++r.len;
-        continue;
-      }
-    }
-    out.push_back({(int32_t)i, (int32_t)q, 1});
+  // one run per period: the interior starts at padded position first + k N
+  const int64_t first = lo_s - (lo_d - g_d);
+  const int64_t back = first + n_s - 1;  // its last cell at k = 0
+  int64_t at = first - (back >= 0 ? back / N : -((-back + N - 1) / N)) * N;  // the first run that ends at 0 or after
+  for (; at < P_d; at += N) {
+    const int64_t q0 = std::max<int64_t>(at, 0), q1 = std::min(at + n_s, P_d);
+    out.push_back({(int32_t)(q0 - at), (int32_t)q0, (int32_t)(q1 - q0)});
   }
 }
 
@@ -804,14 +801,85 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
   h.lists = std::move(w);
 }
 
-// Does the circular interval [a, a+len) (len < N) meet [lo, lo+n) on Z_N?
-inline bool circ_meets(int64_t a, int64_t len, int64_t lo, int64_t n, int64_t N) {
-  if (len >= N) return true;
-  for (int k = -2; k <= 2; ++k) {
-    const int64_t s = a + k * N, e = s + len;
-    if (s < lo + n && lo < e) return true;
+// Deposited currents: every box interior cut, along each axis, where the set of
+// padded copies changes; the regions with more than one copy (boxes ascending,
+// then z, y, x positions ascending).
+inline void build_sum(HostTables& h) {
+  const int V = 16 / (int)real_size(h.prec);  // elements per 16-byte access
+  h.sumr.clear();
+  h.sumc.clear();
+  h.itemsS.assign(1, 0);
+  h.regionOf.clear();
+  struct Meet {
+    int d;
+    std::vector<Run> r[3];  // x, y, z
+  };
+  for (int s = 0; s < h.nsub; ++s) {
+    const BoxD& a = h.box[s];
+    std::vector<Meet> meets;
+    std::vector<int32_t> cut[3];
+    for (int u = 0; u < 3; ++u) cut[u] = {0, a.n[u]};
+    for (int d = 0; d < h.nsub; ++d) {
+      const BoxD& b = h.box[d];
+      Meet m;
+      m.d = d;
+      bool any = true;
+      for (int u = 2; u >= 0 && any; --u) {
+        axis_runs(a.lo[u], a.n[u], b.lo[u], b.g[u], b.P[u], h.N[u], m.r[u]);
+        any = !m.r[u].empty();
+      }
+      if (!any) continue;
+      for (int u = 0; u < 3; ++u)
+        for (const Run& r : m.r[u]) {
+          cut[u].push_back(r.i0);
+          cut[u].push_back(r.i0 + r.len);
+        }
+      meets.push_back(std::move(m));
+    }
+    for (int u = 0; u < 3; ++u) {
+      std::sort(cut[u].begin(), cut[u].end());
+      cut[u].erase(std::unique(cut[u].begin(), cut[u].end()), cut[u].end());
+    }
+    for (size_t iz = 0; iz + 1 < cut[2].size(); ++iz)
+      for (size_t iy = 0; iy + 1 < cut[1].size(); ++iy)
+        for (size_t ix = 0; ix + 1 < cut[0].size(); ++ix) {
+          const int x0 = cut[0][ix], y0 = cut[1][iy], z0 = cut[2][iz];
+          SumRegion g{};
+          g.c0 = (int32_t)h.sumc.size();
+          g.ly = cut[1][iy + 1] - y0;
+          g.lx = cut[0][ix + 1] - x0;
+          bool vec = g.lx % V == 0;
+          auto covers = [](const Run& r, int i) { return i >= r.i0 && i < r.i0 + r.len; };
+          for (const Meet& m : meets) {
+            const BoxD& b = h.box[m.d];
+            for (const Run& rz : m.r[2]) {
+              if (!covers(rz, z0)) continue;
+              for (const Run& ry : m.r[1]) {
+                if (!covers(ry, y0)) continue;
+                for (const Run& rx : m.r[0]) {
+                  if (!covers(rx, x0)) continue;
+                  SumCopy c;
+                  c.sP0 = b.P[0];
+                  c.sPl = b.P[0] * b.P[1];
+                  c.off = b.foff + ((int64_t)(rz.q0 + z0 - rz.i0) * b.P[1] + (ry.q0 + y0 - ry.i0)) * b.P[0] +
+                          (rx.q0 + x0 - rx.i0);
+                  vec = vec && c.off % V == 0 && c.sP0 % V == 0 && c.sPl % V == 0;
+                  h.sumc.push_back(c);
+                }
+              }
+            }
+          }
+          g.nc = (int32_t)h.sumc.size() - g.c0;
+          if (g.nc < 2) {  // the owner's cells alone
+            h.sumc.resize(g.c0);
+            continue;
+          }
+          g.vec = vec;
+          h.itemsS.push_back(h.itemsS.back() + cut[2][iz + 1] - z0);
+          h.regionOf.resize(h.itemsS.back(), (int32_t)h.sumr.size());
+          h.sumr.push_back(g);
+        }
   }
-  return false;
 }
 
 inline psatd_status build_host(HostTables& h, std::string& err, const int64_t grid_n[3],
@@ -970,22 +1038,6 @@ inline psatd_status build_host(HostTables& h, std::string& err, const int64_t gr
     h.PB = PB;
   }
 
-  // neighbours: boxes whose padded region meets the interior of s (for the
-  // deposited-current sum), ascending
-  h.nbr_off.assign(nsub + 1, 0);
-  h.nbr.clear();
-  if (jmode == PSATD_J_DEPOSITED) {
-    for (int s = 0; s < nsub; ++s) {
-      for (int s2 = 0; s2 < nsub; ++s2) {
-        bool meets = true;
-        for (int u = 0; u < 3 && meets; ++u)
-          meets = circ_meets((int64_t)h.box[s2].lo[u] - h.box[s2].g[u], h.box[s2].P[u], h.box[s].lo[u],
-                             h.box[s].n[u], grid_n[u]);
-        if (meets) h.nbr.push_back(s2);
-      }
-      h.nbr_off[s + 1] = (int32_t)h.nbr.size();
-    }
-  }
   // work lists
   auto prefix = [&](std::vector<int32_t>& v, auto count) {
     v.assign(nsub + 1, 0);
@@ -999,6 +1051,7 @@ inline psatd_status build_host(HostTables& h, std::string& err, const int64_t gr
   prefix(h.itemsP, [](const BoxD& b) { return (int64_t)b.P[2]; });
   prefix(h.itemsN, [](const BoxD& b) { return (int64_t)b.n[2]; });
   build_push(h);
+  if (jmode == PSATD_J_DEPOSITED) build_sum(h);
   build_zreg(h);
   set_batches(h, 0);
   // launch-shape defaults (measured on 96^3 and 176^3 boxes): x/y groups of

@@ -214,6 +214,12 @@ psatd_status check_fields(psatd_plan_t p, void* const* v, int count, const char*
   return PSATD_OK;
 }
 
+// The sum of the deposited currents writes every copy; replicated ones are
+// copied from their owners.
+hipError_t exchange_J(const DevPlan& d, int jmode, void* const J[3], hipStream_t st) {
+  return jmode == PSATD_J_DEPOSITED ? launch_sum(d, J, st) : launch_fill(d, J, 3, st);
+}
+
 // One step: exchange_J, every batch through F -> U -> I, exchange_EB.  If prof
 // is given, an event pair brackets every launch, tagged with its phase.
 // first: the first step since J was (re)deposited or changed.  J is read-only
@@ -256,8 +262,7 @@ psatd_status enqueue_step(psatd_plan_t p, void* const E[3], void* const B[3], vo
   if ((r = mark(ph, s0)) != PSATD_OK) return r
   if (first) {
     PSATD_MARK(kPhaseExchJ, true);
-    if (p->h.jmode == PSATD_J_DEPOSITED) HIPCHK(p, launch_sum(d, J, st));
-    HIPCHK(p, launch_fill(d, J, 3, st));
+    HIPCHK(p, exchange_J(d, p->h.jmode, J, st));
     PSATD_MARK(kPhaseExchJ, false);
   }
   const int npull = d.pull ? 6 : 0;
@@ -384,8 +389,10 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   const size_t o_pos = reserve(h.pos.size() * 4);
   const size_t o_kmod = reserve((size_t)h.kmod_len * 8);
   const size_t o_kent = reserve(h.kent.size() * sizeof(KEntry));
-  const size_t o_nbo = reserve(h.nbr_off.size() * 4);
-  const size_t o_nbr = reserve(std::max<size_t>(h.nbr.size(), 1) * 4);
+  const size_t o_sr = reserve(std::max<size_t>(h.sumr.size(), 1) * sizeof(SumRegion));
+  const size_t o_sc = reserve(std::max<size_t>(h.sumc.size(), 1) * sizeof(SumCopy));
+  const size_t o_iS = reserve(std::max<size_t>(h.itemsS.size(), 1) * 4);
+  const size_t o_rOf = reserve(std::max<size_t>(h.regionOf.size(), 1) * 4);
   const size_t o_iP = reserve(h.itemsP.size() * 4);
   const size_t o_iN = reserve(h.itemsN.size() * 4);
   const size_t o_push = reserve(std::max<size_t>(h.push.size(), 1) * sizeof(PushBlk));
@@ -405,8 +412,10 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   }
   put(o_pos, h.pos.data(), h.pos.size() * 4);
   put(o_kent, h.kent.data(), h.kent.size() * sizeof(KEntry));
-  put(o_nbo, h.nbr_off.data(), h.nbr_off.size() * 4);
-  put(o_nbr, h.nbr.data(), h.nbr.size() * 4);
+  put(o_sr, h.sumr.data(), h.sumr.size() * sizeof(SumRegion));
+  put(o_sc, h.sumc.data(), h.sumc.size() * sizeof(SumCopy));
+  put(o_iS, h.itemsS.data(), h.itemsS.size() * 4);
+  put(o_rOf, h.regionOf.data(), h.regionOf.size() * 4);
   put(o_iP, h.itemsP.data(), h.itemsP.size() * 4);
   put(o_iN, h.itemsN.data(), h.itemsN.size() * 4);
   put(o_push, h.push.data(), h.push.size() * sizeof(PushBlk));
@@ -444,8 +453,11 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   d.tw = B + o_tw;
   d.pos = reinterpret_cast<const int32_t*>(B + o_pos);
   d.kmod = reinterpret_cast<const double*>(B + o_kmod);
-  d.nbr_off = reinterpret_cast<const int32_t*>(B + o_nbo);
-  d.nbr = reinterpret_cast<const int32_t*>(B + o_nbr);
+  d.sumr = reinterpret_cast<const SumRegion*>(B + o_sr);
+  d.sumc = reinterpret_cast<const SumCopy*>(B + o_sc);
+  d.itemsS = reinterpret_cast<const int32_t*>(B + o_iS);
+  d.regionOf = reinterpret_cast<const int32_t*>(B + o_rOf);
+  d.nS = h.itemsS.empty() ? 0 : h.itemsS.back();
   d.itemsP = reinterpret_cast<const int32_t*>(B + o_iP);
   d.itemsN = reinterpret_cast<const int32_t*>(B + o_iN);
   d.ldsX = h.ldsX;
@@ -912,8 +924,7 @@ psatd_status psatd_autotune(psatd_plan_t p, void* const E[3], void* const B[3], 
   // trial steps then leave it alone, so deposited currents are summed exactly
   // once however many candidates are timed.
   HIPCHK(p, hipStreamSynchronize(p->stream));
-  if (p->h.jmode == PSATD_J_DEPOSITED) HIPCHK(p, launch_sum(p->dp, J, p->stream));
-  HIPCHK(p, launch_fill(p->dp, J, 3, p->stream));
+  HIPCHK(p, exchange_J(p->dp, p->h.jmode, J, p->stream));
   // Phases are separate kernels with radix limits of their own: the x/y
   // shape and radix and the z shape and radix are tuned independently.
   int best[nk] = {p->tune[PSATD_TUNE_MAX_RADIX], p->tune[PSATD_TUNE_XY_THREADS], p->tune[PSATD_TUNE_Z_PENCILS],

@@ -143,8 +143,8 @@ __global__ __launch_bounds__(kThreadsXY) void k_fill(FillArgs<T> a, int nitems, 
 }
 
 template <typename T>
-__global__ __launch_bounds__(kThreadsXY) void k_sum(SumArgs<T> a, int nitems) {
-  for (int item = blockIdx.x; item < nitems; item += gridDim.x)
+__global__ __launch_bounds__(kThreadsXY) void k_sum(SumArgs<T> a, int nitems, int remap) {
+  for (int item = first_item(remap); item < nitems; item += gridDim.x)
     body_sum(a, item, threadIdx.x, blockDim.x);
 }
 
@@ -569,16 +569,14 @@ hipError_t launch_fill(const DevPlan& p, void* const* comps, int ncomp, hipStrea
 template <typename T>
 static hipError_t sum_t(const DevPlan& p, void* const* J, hipStream_t st) {
   SumArgs<T> a;
-  a.box = p.box;
-  a.nsub = p.nsub;
-  a.items = p.itemsN;
-  a.nbr_off = p.nbr_off;
-  a.nbr = p.nbr;
-  for (int u = 0; u < 3; ++u) a.N[u] = p.N[u];
+  a.region = p.sumr;
+  a.copy = p.sumc;
+  a.items = p.itemsS;
+  a.region_of = p.regionOf;
   for (int c = 0; c < 3; ++c) a.comp[c] = reinterpret_cast<T*>(J[c]);
-  const int g = grid_for(p.nN, p.grid_cap[kPhaseExchJ]);
+  const int g = grid_for(p.nS, p.grid_cap[kPhaseExchJ]);
   if (!g) return hipSuccess;
-  hipLaunchKernelGGL(k_sum<T>, dim3(g), dim3(kThreadsXY), 0, st, a, p.nN);
+  hipLaunchKernelGGL(k_sum<T>, dim3(g), dim3(kThreadsXY), 0, st, a, p.nS, p.xcd);
   return hipGetLastError();
 }
 

@@ -18,13 +18,16 @@ struct DevPlan {
   const void* tw;           // cx<double> or cx<float> twiddles
   const int32_t* pos;       // position tables of the FFT plans
   const double* kmod;
-  const int32_t* nbr_off;
-  const int32_t* nbr;
+  const SumRegion* sumr;    // deposited currents
+  const SumCopy* sumc;
+  const int32_t* itemsS;
+  const int32_t* regionOf;
+  int32_t nS;
   const PlaneRec* fwd;      // work lists of the x/y and z passes (see WorkLists)
   const PlaneRec* inv;
   const ZItem* tiles;
   const int32_t* itemsP;    // scatter: P[2]
-  const int32_t* itemsN;    // gather, sum: n[2]
+  const int32_t* itemsN;    // gather: n[2]
   int32_t ldsX, ldsY;
   int32_t split;
   const PushBlk* push;       // guard pieces (guard fill, fused E,B exchange)

@@ -104,6 +104,40 @@ void check_places(const char* name, const HostTables& h, const int64_t N[3], con
   }
 }
 
+// Every padded cell in exactly one copy list or alone; the copies of a region are
+// the same global cells, in the order of boxes and positions.
+void check_sums(const char* name, const HostTables& h, const int64_t N[3]) {
+  std::map<int64_t, std::array<int64_t, 3>> cell;  // element -> global cell
+  std::map<std::array<int64_t, 3>, std::vector<int64_t>> want;
+  for (const BoxD& b : h.box)
+    for (int z = 0; z < b.P[2]; ++z)
+      for (int y = 0; y < b.P[1]; ++y)
+        for (int x = 0; x < b.P[0]; ++x) {
+          const int q[3] = {x, y, z};
+          std::array<int64_t, 3> G;
+          for (int u = 0; u < 3; ++u) G[u] = ((b.lo[u] - b.g[u] + q[u]) % N[u] + N[u]) % N[u];
+          const int64_t o = b.foff + ((int64_t)z * b.P[1] + y) * b.P[0] + x;
+          cell[o] = G;
+          want[G].push_back(o);
+        }
+  std::set<int64_t> seen;
+  for (size_t r = 0; r < h.sumr.size(); ++r) {
+    const SumRegion& g = h.sumr[r];
+    for (int z = 0; z < h.itemsS[r + 1] - h.itemsS[r]; ++z)
+      for (int y = 0; y < g.ly; ++y)
+        for (int x = 0; x < g.lx; ++x) {
+          std::vector<int64_t> got;
+          for (int c = g.c0; c < g.c0 + g.nc; ++c)
+            got.push_back(h.sumc[c].off + (int64_t)z * h.sumc[c].sPl + (int64_t)y * h.sumc[c].sP0 + x);
+          CHECK(cell.count(got[0]) && want[cell[got[0]]] == got, "%s: copies of a cell", name);
+          for (int64_t o : got) CHECK(seen.insert(o).second, "%s: cell in one region", name);
+        }
+  }
+  for (const auto& w : want)
+    CHECK(w.second.size() == 1 || seen.count(w.second[0]), "%s: every shared cell summed", name);
+  CHECK((int64_t)h.regionOf.size() == h.itemsS.back(), "%s: sum work list", name);
+}
+
 void check(const char* name, const int64_t N[3], const std::vector<Box>& bx, bool expect_shared) {
   std::vector<int64_t> lo, n;
   std::vector<int32_t> g;
@@ -125,6 +159,10 @@ void check(const char* name, const int64_t N[3], const std::vector<Box>& bx, boo
     check_places(name, h, N, h.lists.tight, h.lists.tight_elems, share && expect_shared);
     check_places(name, h, N, h.lists.box, h.lists.elems, share && expect_shared);
   }
+  HostTables dep;
+  CHECK(build_host(dep, err, N, d, nsub, lo.data(), n.data(), g.data(), 16, 0.5, 1.0, PSATD_F32_VALU,
+                   PSATD_J_DEPOSITED) == PSATD_OK, "%s: %s", name, err.c_str());
+  check_sums(name, dep, N);
   std::printf("%s ok\n", name);
 }
 std::vector<Box> column(std::vector<int64_t> nz, std::vector<int32_t> gz, int nx, int32_t gx) {
