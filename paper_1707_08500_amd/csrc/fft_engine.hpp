@@ -182,6 +182,39 @@ struct FftPlanD {
   int32_t pos;   // offset of the plan's table of positions (plan_pos of 0 .. N-1)
 };
 
+// The plan tables (boxes, schedules, work lists) do not change while a kernel
+// runs, but a kernel that also stores through other pointers cannot know that,
+// and would fetch what every lane shares into vector registers and compute with
+// it there.  Read through the constant address space it stays in scalar
+// registers: uniform_load copies one record, PlanRef is a pointer to a schedule.
+#ifdef __HIP_DEVICE_COMPILE__
+#define PSATD_CONST __attribute__((address_space(4)))
+#else
+#define PSATD_CONST
+#endif
+typedef const PSATD_CONST FftPlanD* PlanRef;
+
+PSATD_HD PlanRef plan_ref(const FftPlanD* p) { return (PlanRef)(uintptr_t)p; }
+
+template <typename V>
+PSATD_HD V uniform_load(const V* p) {
+#ifdef __HIP_DEVICE_COMPILE__
+  static_assert(sizeof(V) % 4 == 0 && alignof(V) >= 4, "whole words");
+  const PSATD_CONST uint32_t* q = (const PSATD_CONST uint32_t*)(uintptr_t)p;
+  uint32_t w[sizeof(V) / 4];
+#pragma unroll
+  for (unsigned i = 0; i < sizeof(V) / 4; ++i) w[i] = q[i];
+  V v;
+  __builtin_memcpy(&v, w, sizeof(V));
+  return v;
+#else
+  return *p;
+#endif
+}
+
+// Division by the stage's stride.
+PSATD_HD FastDiv plan_sdiv(PlanRef pl, int s) { return FastDiv{pl->sdiv[s].d, pl->sdiv[s].m}; }
+
 // Position of index k in stage-digit order: k = t_0 + r_0 t_1 + ..., pos = sum t_s ms_s.
 PSATD_HD int plan_pos(const FftPlanD* pl, int k) {
   int pos = 0;
@@ -287,7 +320,7 @@ PSATD_HD void fft_stage_dispatch(int R, cx<T>* buf, int M, FastDiv dM, int ms, i
 // natural -> stage-digit order; ends with a barrier.  tw: this plan's twiddle
 // table (global or LDS).  The plan is read from uniform memory.
 template <int DIR, int MAXR, typename T, class Bar>
-PSATD_HD void fft_dif(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, const cx<T>* tw,
+PSATD_HD void fft_dif(cx<T>* buf, int M, int ms, int es, PlanRef pl, const cx<T>* tw,
                       int tid, int nt, Bar bar) {
   const int N = pl->N;
   const int ns = pl->nstages;
@@ -295,7 +328,7 @@ PSATD_HD void fft_dif(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, con
   int L = N;
   for (int s = 0; s < ns; ++s) {
     const int R = pl->radix[s];
-    fft_stage_dispatch<DIR, true, MAXR, T>(R, buf, M, dM, ms, es, N, L, pl->sdiv[s], tw + pl->twoff[s], tid,
+    fft_stage_dispatch<DIR, true, MAXR, T>(R, buf, M, dM, ms, es, N, L, plan_sdiv(pl, s), tw + pl->twoff[s], tid,
                                            nt);
     bar();
     L /= R;
@@ -304,14 +337,14 @@ PSATD_HD void fft_dif(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, con
 
 // stage-digit -> natural order; ends with a barrier
 template <int DIR, int MAXR, typename T, class Bar>
-PSATD_HD void fft_dit(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, const cx<T>* tw,
+PSATD_HD void fft_dit(cx<T>* buf, int M, int ms, int es, PlanRef pl, const cx<T>* tw,
                       int tid, int nt, Bar bar) {
   const int N = pl->N;
   const int ns = pl->nstages;
   const FastDiv dM = make_fastdiv((uint32_t)M);
   for (int s = ns - 1; s >= 0; --s) {
     const int L = pl->stride[s] * pl->radix[s];
-    fft_stage_dispatch<DIR, false, MAXR, T>(pl->radix[s], buf, M, dM, ms, es, N, L, pl->sdiv[s],
+    fft_stage_dispatch<DIR, false, MAXR, T>(pl->radix[s], buf, M, dM, ms, es, N, L, plan_sdiv(pl, s),
                                             tw + pl->twoff[s], tid, nt);
     bar();
   }
@@ -344,7 +377,7 @@ PSATD_HD void first_stage(cx<T>* buf, int ms, const cx<T>* tws, int tid, int nt,
 }
 
 template <int DIR, int MAXR, int M, int W, typename T, class IO>
-PSATD_HD void first_stage_dispatch(const FftPlanD* pl, cx<T>* buf, const cx<T>* tw, int tid, int nt, const IO& io) {
+PSATD_HD void first_stage_dispatch(PlanRef pl, cx<T>* buf, const cx<T>* tw, int tid, int nt, const IO& io) {
   const int ms = pl->stride[0];
   const cx<T>* tws = tw + pl->twoff[0];
   switch (pl->radix[0]) {
@@ -366,12 +399,12 @@ PSATD_HD void first_stage_dispatch(const FftPlanD* pl, cx<T>* buf, const cx<T>* 
 
 // The other stages (s >= 1) of such a dif.
 template <int DIR, int MAXR, typename T, class Bar>
-PSATD_HD void fft_dif_inner(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, const cx<T>* tw, int tid, int nt,
+PSATD_HD void fft_dif_inner(cx<T>* buf, int M, int ms, int es, PlanRef pl, const cx<T>* tw, int tid, int nt,
                             Bar bar) {
   const FastDiv dM = make_fastdiv((uint32_t)M);
   for (int s = 1; s < pl->nstages; ++s) {
     const int L = pl->stride[s] * pl->radix[s];
-    fft_stage_dispatch<DIR, true, MAXR, T>(pl->radix[s], buf, M, dM, ms, es, pl->N, L, pl->sdiv[s],
+    fft_stage_dispatch<DIR, true, MAXR, T>(pl->radix[s], buf, M, dM, ms, es, pl->N, L, plan_sdiv(pl, s),
                                            tw + pl->twoff[s], tid, nt);
     bar();
   }
@@ -379,12 +412,12 @@ PSATD_HD void fft_dif_inner(cx<T>* buf, int M, int ms, int es, const FftPlanD* p
 // FFT engine of the kernel bodies: every stage as a VALU radix stage.
 struct FftValu {
   template <int DIR, int MAXR, typename T, class Bar>
-  PSATD_HD void dif(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, const cx<T>* tw, int tid,
+  PSATD_HD void dif(cx<T>* buf, int M, int ms, int es, PlanRef pl, const cx<T>* tw, int tid,
                     int nt, Bar bar) const {
     fft_dif<DIR, MAXR>(buf, M, ms, es, pl, tw, tid, nt, bar);
   }
   template <int DIR, int MAXR, typename T, class Bar>
-  PSATD_HD void dit(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, const cx<T>* tw, int tid,
+  PSATD_HD void dit(cx<T>* buf, int M, int ms, int es, PlanRef pl, const cx<T>* tw, int tid,
                     int nt, Bar bar) const {
     fft_dit<DIR, MAXR>(buf, M, ms, es, pl, tw, tid, nt, bar);
   }

@@ -154,7 +154,7 @@ PSATD_HD void dft16_mfma(cx<float>* buf, int M, FastDiv dM, int ms, int es, int 
 // Transforms whose first stage has radix 16 run it on the matrix cores; the
 // other stages (and plans without a radix-16 first stage) as VALU stages.
 template <int DIR, int MAXR, int SPL, class Bar, class Mma>
-PSATD_HD void fft_dif_mfma(cx<float>* buf, int M, int ms, int es, const FftPlanD* pl,
+PSATD_HD void fft_dif_mfma(cx<float>* buf, int M, int ms, int es, PlanRef pl,
                            const cx<float>* tw, int tid, int nt, Bar bar, const Mma& mma) {
   const int N = pl->N;
   const int ns = pl->nstages;
@@ -169,7 +169,7 @@ PSATD_HD void fft_dif_mfma(cx<float>* buf, int M, int ms, int es, const FftPlanD
   }
   for (; s < ns; ++s) {
     const int R = pl->radix[s];
-    fft_stage_dispatch<DIR, true, MAXR, float>(R, buf, M, dM, ms, es, N, L, pl->sdiv[s], tw + pl->twoff[s],
+    fft_stage_dispatch<DIR, true, MAXR, float>(R, buf, M, dM, ms, es, N, L, plan_sdiv(pl, s), tw + pl->twoff[s],
                                                tid, nt);
     bar();
     L /= R;
@@ -177,7 +177,7 @@ PSATD_HD void fft_dif_mfma(cx<float>* buf, int M, int ms, int es, const FftPlanD
 }
 
 template <int DIR, int MAXR, int SPL, class Bar, class Mma>
-PSATD_HD void fft_dit_mfma(cx<float>* buf, int M, int ms, int es, const FftPlanD* pl,
+PSATD_HD void fft_dit_mfma(cx<float>* buf, int M, int ms, int es, PlanRef pl,
                            const cx<float>* tw, int tid, int nt, Bar bar, const Mma& mma) {
   const int N = pl->N;
   const int ns = pl->nstages;
@@ -185,7 +185,7 @@ PSATD_HD void fft_dit_mfma(cx<float>* buf, int M, int ms, int es, const FftPlanD
   const bool gemm = ns > 0 && pl->radix[0] == 16;
   for (int s = ns - 1; s >= (gemm ? 1 : 0); --s) {
     const int L = pl->stride[s] * pl->radix[s];
-    fft_stage_dispatch<DIR, false, MAXR, float>(pl->radix[s], buf, M, dM, ms, es, N, L, pl->sdiv[s],
+    fft_stage_dispatch<DIR, false, MAXR, float>(pl->radix[s], buf, M, dM, ms, es, N, L, plan_sdiv(pl, s),
                                                 tw + pl->twoff[s], tid, nt);
     bar();
   }
@@ -200,12 +200,12 @@ template <int SPL, class Mma>
 struct FftMfma {
   Mma mma;
   template <int DIR, int MAXR, typename T, class Bar>
-  PSATD_HD void dif(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, const cx<T>* tw, int tid,
+  PSATD_HD void dif(cx<T>* buf, int M, int ms, int es, PlanRef pl, const cx<T>* tw, int tid,
                     int nt, Bar bar) const {
     fft_dif_mfma<DIR, MAXR, SPL>(buf, M, ms, es, pl, tw, tid, nt, bar, mma);
   }
   template <int DIR, int MAXR, typename T, class Bar>
-  PSATD_HD void dit(cx<T>* buf, int M, int ms, int es, const FftPlanD* pl, const cx<T>* tw, int tid,
+  PSATD_HD void dit(cx<T>* buf, int M, int ms, int es, PlanRef pl, const cx<T>* tw, int tid,
                     int nt, Bar bar) const {
     fft_dit_mfma<DIR, MAXR, SPL>(buf, M, ms, es, pl, tw, tid, nt, bar, mma);
   }

@@ -758,6 +758,16 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
           if (in[s]) w.tiles.push_back({s, q});
     }
     l.nu = (int32_t)w.tiles.size() - l.u0;
+    // Short z: 512-thread tiles are two per compute unit in FP32 and one in FP64
+    // (registers) however small they are, and a short tile has no work for all
+    // their waves.  256 threads where that puts more tiles on a compute unit (the
+    // LDS holds three FP32 or two FP64 ones) and the launch takes more than one
+    // round of 512-thread tiles.  Measured, 512 -> 256 threads: 512 boxes of 48^3
+    // padded 1.23 -> 0.87 ms FP32, 2.90 -> 1.88 FP64; 216 of 64^3 1.01 -> 0.95,
+    // 2.35 -> 1.68; 80^3 (two and one tile) 0.60 -> 0.74, 1.31 -> 1.61 ms, so not
+    // there; one round of 68 FP64 tiles of 32-long z 9.8 -> 11.1 us, nor there.
+    const bool f64 = is_f64(h.prec);
+    l.narrow = kMaxDynLds / l.lds >= (f64 ? 2 : 3) && l.nu > (f64 ? 256 : 512);
   };
   for (const Batch& bt : h.batches) {
     w.xy.emplace_back();
@@ -781,13 +791,13 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
       for (const ZClass& k : h.zcls) {
         const int32_t* U = h.itemsZC.data() + k.U;
         for (int s = 0; s < h.nsub; ++s) in[s] = U[s + 1] > U[s];
-        ZLaunch l{k.PB, k.lds, 0, 0};
+        ZLaunch l{k.PB, k.lds};
         add_tiles(in, l);
         w.z.back().push_back(l);
       }
     } else {
       for (int s = 0; s < h.nsub; ++s) in[s] = s >= bt.b0 && s < bt.b1;
-      ZLaunch l{h.PB, h.ldsU, 0, 0};
+      ZLaunch l{h.PB, h.ldsU};
       add_tiles(in, l);
       w.z.back().push_back(l);
     }

@@ -98,6 +98,7 @@ struct XyLaunch {
 };
 struct ZLaunch {
   int32_t PB, lds, u0, nu;
+  int32_t narrow;  // 1: tiles of 256 threads instead of 512
 };
 
 // A batch of boxes [b0, b1) for the FFT/update passes and the spectral offset
@@ -182,6 +183,26 @@ struct Tables {
   const int32_t* pos;     // position tables (stage-digit order)
   const double* kmod;     // modified wavenumbers (FP64)
 };
+
+// Buffer resource over `bytes` bytes at base (raw, untyped; the third word
+// selects 32-bit elements on this GPU family).  Accesses at or beyond `bytes`
+// read zeros and write nothing.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), (short)0, (int)bytes, 0x00020000);
+}
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+
+// One complex value at byte offset voff + soff (soff wave-uniform).
+__device__ __forceinline__ void buf_load(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, cx<float>* v) {
+  const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)voff, (int)soff, 0);
+  __builtin_memcpy(v, &w, sizeof(w));
+}
+__device__ __forceinline__ void buf_load(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, cx<double>* v) {
+  const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, 0);
+  __builtin_memcpy(v, &w, sizeof(w));
+}
 
 // Copies total elements i -> dst(i, src(i)) with U loads in flight per
 // thread (all U loads are issued before the first store).
@@ -410,12 +431,12 @@ template <typename T, class Val>
 PSATD_HD void push_guards(const PushBlk* blk, int b0, int b1, const BoxD* boxes, T* out, int zi,
                           int ya, int yb, Val val, int tid, int nt) {
   for (int b = b0; b < b1; ++b) {
-    const PushBlk k = blk[b];
+    const PushBlk k = uniform_load(blk + b);
     if (zi < k.z0 || zi >= k.z0 + k.lz) continue;
     const int y_lo = ya > k.y0 ? ya : k.y0;
     const int y_hi = yb < k.y0 + k.ly ? yb : k.y0 + k.ly;
     if (y_lo >= y_hi) continue;
-    const BoxD& d = boxes[k.dst];
+    const BoxD d = uniform_load(boxes + k.dst);
     T* base = out + d.foff + ((int64_t)(k.qz + zi - k.z0) * d.P[1] + (k.qy + y_lo - k.y0)) * d.P[0] + k.qx;
     const int n = (y_hi - y_lo) * k.lx;
     const FastDiv dl = make_fastdiv((uint32_t)k.lx);
@@ -498,13 +519,13 @@ PSATD_HD void copy_rect_to_plane(const T* src, int sP0, int ly, int lx, int y0, 
 template <typename T, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_fwd_xy(const FwdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
   const int f = (int)fdiv((uint32_t)item, a.np);
-  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
-  const BoxD& bx = a.t.box[rec.box];
+  const PlaneRec rec = uniform_load(a.planes + (item - f * (int)a.np.d));
+  const BoxD bx = uniform_load(a.t.box + rec.box);
   const int z = rec.z;
   const int Px = bx.P[0], Py = bx.P[1];
   const int Nh = Px >> 1, H = bx.H, ld = bx.ld;
-  const FftPlanD* plx = a.t.plans + bx.planx;
-  const FftPlanD* ply = a.t.plans + bx.plany;
+  const PlanRef plx = plan_ref(a.t.plans + bx.planx);
+  const PlanRef ply = plan_ref(a.t.plans + bx.plany);
   cx<T>* twx = lds + Py * ld;
   cx<T>* twy = twx + Nh;
   cx<T>* twr = twy + Py;
@@ -515,10 +536,9 @@ PSATD_HD void body_fwd_xy(const FwdArgs<T>& a, int item, int tid, int nt, cx<T>*
   const cx<T>* gtr = a.t.tw + bx.twr;
 
   // stage-digit positions along x (input of the dit) and y (output of the dif)
-  for (int i = tid; i < Nh + Py; i += nt) {
-    if (i < Nh) posx[i] = plan_pos(plx, i);
-    else posy[i - Nh] = plan_pos(ply, i - Nh);
-  }
+  const int32_t* gpx = a.t.pos + plx->pos;
+  const int32_t* gpy = a.t.pos + ply->pos;
+  for (int i = tid; i < Nh + Py; i += nt) posx[i] = i < Nh ? gpx[i] : gpy[i - Nh];  // posx, posy are contiguous
   bar();
   // packed real rows (x natural) -> LDS rows in stage-digit order along x,
   // together with the three twiddle tables
@@ -545,7 +565,7 @@ PSATD_HD void body_fwd_xy(const FwdArgs<T>& a, int item, int tid, int nt, cx<T>*
     }
     for (int b = rec.p0; b < rec.p1; ++b) {
       if (dealt++ % nw != wave) continue;
-      const PullPiece k = a.pull[b];
+      const PullPiece k = uniform_load(a.pull + b);
       copy_rect_to_plane<T>(inf + k.so + (int64_t)(z - k.qz) * k.sPl, k.sP0, k.ly, k.lx, k.qy, k.qx, lds, ld, posx,
                             lane, 64);
     }
@@ -689,38 +709,37 @@ PSATD_HD UpdCoef<T> update_coef(double kx, double ky, double kz, double c, doubl
 }
 
 // The update's multiply-adds in the state's type T (FP64 path: double; FP32
-// path: float, where they act on increments).
+// path: float, where they act on increments).  The factors i leave two real
+// problems of the same form, (Re E, Im B, Re J) with SG = +1 and (Im E, Re B,
+// Im J) with SG = -1:
+//   E' = C E - SG c^2 (S/ck) [k]xB - (S/ck) J + [k] (X1 [k].E + X2 [k].J)
+//   B' = C B - SG [k] x ((S/ck) E - (X1/c^2) J)
+template <int SG, typename T>
+PSATD_HD void update_half(T* e, T* b, const T* j, const UpdCoef<T>& u) {
+  const T k[3] = {u.kx, u.ky, u.kz};
+  const T ak[3] = {SG * u.a1 * u.kx, SG * u.a1 * u.ky, SG * u.a1 * u.kz};
+  const T kE = k[0] * e[0] + k[1] * e[1] + k[2] * e[2];
+  const T kJ = k[0] * j[0] + k[1] * j[1] + k[2] * j[2];
+  const T s = u.X1 * kE + u.X2 * kJ;
+  T f[3], en[3];
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int p = (a + 1) % 3, q = (a + 2) % 3;
+    f[a] = SG * (u.S * e[a] - u.x1c * j[a]);
+    en[a] = u.C * e[a] - u.S * j[a] - ak[p] * b[q] + ak[q] * b[p] + k[a] * s;
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    const int p = (a + 1) % 3, q = (a + 2) % 3;
+    b[a] = u.C * b[a] - k[p] * f[q] + k[q] * f[p];
+    e[a] = en[a];
+  }
+}
+
 template <typename T>
 PSATD_HD void update_apply(T* vr, T* vi /* E0 E1 E2 B0 B1 B2 J0 J1 J2 */, const UpdCoef<T>& u) {
-  T er[3], ei[3], br[3], bi[3], jr[3], ji[3];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    er[a] = vr[a]; ei[a] = vi[a];
-    br[a] = vr[3 + a]; bi[a] = vi[3 + a];
-    jr[a] = vr[6 + a]; ji[a] = vi[6 + a];
-  }
-  const T tkx = u.kx, tky = u.ky, tkz = u.kz;
-  const T K[3] = {tkx, tky, tkz};
-  const T tC = u.C, tS = u.S, tX1 = u.X1, tX2 = u.X2, a1 = u.a1, x1c = u.x1c;
-  const T kEr = tkx * er[0] + tky * er[1] + tkz * er[2];
-  const T kEi = tkx * ei[0] + tky * ei[1] + tkz * ei[2];
-  const T kJr = tkx * jr[0] + tky * jr[1] + tkz * jr[2];
-  const T kJi = tkx * ji[0] + tky * ji[1] + tkz * ji[2];
-  // cross products [k] x F, real and imaginary parts
-  const T kxBr[3] = {tky * br[2] - tkz * br[1], tkz * br[0] - tkx * br[2], tkx * br[1] - tky * br[0]};
-  const T kxBi[3] = {tky * bi[2] - tkz * bi[1], tkz * bi[0] - tkx * bi[2], tkx * bi[1] - tky * bi[0]};
-  const T kxEr[3] = {tky * er[2] - tkz * er[1], tkz * er[0] - tkx * er[2], tkx * er[1] - tky * er[0]};
-  const T kxEi[3] = {tky * ei[2] - tkz * ei[1], tkz * ei[0] - tkx * ei[2], tkx * ei[1] - tky * ei[0]};
-  const T kxJr[3] = {tky * jr[2] - tkz * jr[1], tkz * jr[0] - tkx * jr[2], tkx * jr[1] - tky * jr[0]};
-  const T kxJi[3] = {tky * ji[2] - tkz * ji[1], tkz * ji[0] - tkx * ji[2], tkx * ji[1] - tky * ji[0]};
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    // i * z = (-z.i, z.r)
-    vr[a] = tC * er[a] - a1 * kxBi[a] - tS * jr[a] + tX1 * K[a] * kEr + tX2 * K[a] * kJr;
-    vi[a] = tC * ei[a] + a1 * kxBr[a] - tS * ji[a] + tX1 * K[a] * kEi + tX2 * K[a] * kJi;
-    vr[3 + a] = tC * br[a] + tS * kxEi[a] - x1c * kxJi[a];
-    vi[3 + a] = tC * bi[a] - tS * kxEr[a] + x1c * kxJr[a];
-  }
+  update_half<1>(vr, vi + 3, vr + 6, u);
+  update_half<-1>(vi, vr + 3, vi + 6, u);
 }
 
 // Eqs. PSATD_1 / PSATD_2 at one k-point: the coefficients (FP64, rounded to T
@@ -773,18 +792,18 @@ PSATD_HD void store_results(const BoxD& bx, cx<T>* dst, int64_t sbias, int q0, i
 // element stride W.  Pencils past the end of the box (last block) are zeros.
 template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
-  const ZItem it = a.items[item];
-  const BoxD& bx = a.t.box[it.box];
+  const ZItem it = uniform_load(a.items + item);
+  const BoxD bx = uniform_load(a.t.box + it.box);
   const int Py = bx.P[1], Pz = bx.P[2], H = bx.H;
   const int nq = Py * H;
   const int q0 = it.q0;
   const int np = (nq - q0) < PB ? (nq - q0) : PB;
-  const FftPlanD* plz = a.t.plans + bx.planz;
+  const PlanRef plz = plan_ref(a.t.plans + bx.planz);
   constexpr int W = 9 * PB;
   cx<T>* twz = lds + Pz * W;
   int32_t* kzi = reinterpret_cast<int32_t*>(twz + Pz);  // frequency at each z slot
   const cx<T>* gtz = a.t.tw + plz->tw;
-  for (int i = tid; i < Pz; i += nt) kzi[i] = plan_index(plz, i);
+  for (int i = tid; i < Pz; i += nt) kzi[a.t.pos[plz->pos + i]] = i;
   const cx<T>* src = spec_at(a.spec, bx, a.sbias, 0) + q0;
   const int64_t slab = bx.sv;  // field stride
   const int ring = bx.ring, zb = bx.zb;
@@ -846,27 +865,55 @@ PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
   store_results<T, PB>(bx, a.spec + q0, a.sbias, q0, np, lds, tid, nt);
 }
 
-// Loads of the first z stage: element z of transform m = f PB + p is the plane
-// at ring slot zb + z.  The slot is a uniform part per q plus the lane's j; a
-// lane is checked against the end of the ring only in the one q it may fall in.
+// Loads of the first z stage: element z = j + q ms of transform m = f PB + p is
+// the plane at ring slot zb + z.  FP32 rings whose 9 fields lie within 4 GiB are
+// read by buffer loads: a 32-bit lane offset (field, j, pencil) and a uniform
+// offset per q, so that a load costs the vector ALU one select (the one q whose
+// lanes fall on both sides of the ring's end takes its whole offset from the
+// lane).  The FP64 pass is slower that way (64 boxes of 96^3 padded: 2.14 against
+// 2.08 ms; FP32 0.90 against 0.93) and adds its lane offsets itself.
 template <typename T, int PB>
 struct ZLoad {
   const cx<T>* src;  // field 0, slot 0, first pencil of the tile
-  const BoxD& bx;
-  int np;            // pencils in the tile
+  int64_t sv;
+  int32_t pp, ring, zb, np;  // np: pencils in the tile
+  PSATD_HD ZLoad(const cx<T>* s, const BoxD& bx, int n)
+      : src(s), sv(bx.sv), pp((int32_t)bx.pp), ring(bx.ring), zb(bx.zb), np(n) {}
   template <int R>
   PSATD_HD void run(int m, int j, int ms, cx<T>* a) const {
-    const int f = m / PB, p = m - f * PB;
-    const int64_t pp = bx.pp;
-    const int ring = bx.ring, wrap = ring - bx.zb;
-    // the idle pencils of a box's last tile repeat its last one
-    const cx<T>* base = src + (f * bx.sv + j * pp + (p < np ? p : np - 1));
+    const int f = m / PB;
+    int p = m - f * PB;
+    p = p < np ? p : np - 1;  // the idle pencils of a box's last tile repeat its last one
+    const int wrap = ring - zb;
+#ifdef __HIP_DEVICE_COMPILE__
+    if constexpr (sizeof(T) == 4) {
+      constexpr uint32_t B = sizeof(cx<T>);
+      if (9 * sv * B <= 0xFFFFFFFFll) {
+        const int qm = wrap / ms, jm = wrap - qm * ms;
+        const uint32_t plane = (uint32_t)pp * B, back = (uint32_t)ring * plane;
+        const auto rs = buffer_rsrc(src, (uint32_t)(9 * sv * B));
+        const uint32_t lane = ((uint32_t)f * (uint32_t)sv + (uint32_t)p) * B + (uint32_t)j * plane;
+        const uint32_t mixed = lane + (uint32_t)(zb + qm * ms) * plane - (j >= jm ? back : 0u);
+        uint32_t o = (uint32_t)zb * plane;  // of slot zb + q ms
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+          const bool mix = q == qm;
+          buf_load(rs, mix ? mixed : lane, mix ? 0u : o - (q > qm ? back : 0u), &a[q]);
+          o += (uint32_t)ms * plane;
+        }
+        return;
+      }
+    }
+#endif
+    // element offsets within one field's ring fit 32 bits: 2^32 elements of one
+    // field, and the state they belong to, are more than the device's memory
+    const cx<T>* base = src + (f * sv + p);
+    uint32_t o = (uint32_t)(zb + j) * (uint32_t)pp;
+    const uint32_t step = (uint32_t)ms * (uint32_t)pp, back = (uint32_t)ring * (uint32_t)pp;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-      const int z0 = q * ms;
-      const cx<T>* e = base + (z0 >= wrap ? z0 - wrap : z0 + bx.zb) * pp;
-      if (z0 < wrap && z0 + ms > wrap && j >= wrap - z0) e -= ring * pp;
-      a[q] = *e;
+      a[q] = base[j + q * ms >= wrap ? o - back : o];
+      o += step;
     }
   }
 };
@@ -877,14 +924,14 @@ struct ZLoad {
 // |[k]| and so the FP64 coefficients.  The results go out through the LDS in
 // whole pencil runs: stores straight from the last stage's butterflies measured
 // 1.0 -> 1.5 ms (64 boxes of 96^3 padded, FP32).  Issue-bound (65 % of the time
-// is VALU busy); with the loads and pairs as here 1.03 -> 0.93 ms, FP64 2.32 ->
-// 2.03 ms, 8 boxes of 176^3 in FP64 2.44 -> 2.07 ms.
+// is VALU busy); with the loads and pairs as here 1.03 -> 0.90 ms, FP64 2.32 ->
+// 2.08 ms, 8 boxes of 176^3 in FP64 2.44 -> 2.03 ms.
 template <typename T, int PB, bool INC, int MAXR, class Bar>
 PSATD_HD void body_z_direct(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar) {
-  const ZItem it = a.items[item];
-  const BoxD& bx = a.t.box[it.box];
+  const ZItem it = uniform_load(a.items + item);
+  const BoxD bx = uniform_load(a.t.box + it.box);
   const int Pz = bx.P[2], H = bx.H, nq = bx.P[1] * H, q0 = it.q0;
-  const FftPlanD* plz = a.t.plans + bx.planz;
+  const PlanRef plz = plan_ref(a.t.plans + bx.planz);
   constexpr int W = 9 * PB;
   cx<T>* twz = lds + Pz * W;
   int32_t* pos = reinterpret_cast<int32_t*>(twz + Pz);  // slot of each frequency
@@ -964,13 +1011,13 @@ PSATD_HD int64_t heat_tile_lds(int Pz, int PB, int real_bytes) {
 template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_z_heat(const HeatArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar,
                           Eng eng = Eng{}) {
-  const ZItem it = a.items[item];
-  const BoxD& bx = a.t.box[it.box];
+  const ZItem it = uniform_load(a.items + item);
+  const BoxD bx = uniform_load(a.t.box + it.box);
   const int Pz = bx.P[2], H = bx.H;
   const int nq = bx.P[1] * H;
   const int q0 = it.q0;
   const int np = (nq - q0) < PB ? (nq - q0) : PB;
-  const FftPlanD* plz = a.t.plans + bx.planz;
+  const PlanRef plz = plan_ref(a.t.plans + bx.planz);
   cx<T>* twz = lds + Pz * PB;
   double* gz1 = reinterpret_cast<double*>(twz + Pz);
   double* gxy = gz1 + Pz;
@@ -1059,14 +1106,14 @@ struct InvArgs {
 template <typename T, bool INC, int MAXR, bool PUSH = false, class Bar, class Eng = FftValu>
 PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
   const int f = (int)fdiv((uint32_t)item, a.np);
-  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
+  const PlaneRec rec = uniform_load(a.planes + (item - f * (int)a.np.d));
   const int s = rec.box;
-  const BoxD& bx = a.t.box[s];
+  const BoxD bx = uniform_load(a.t.box + s);
   const int z = bx.g[2] + rec.z;
   const int Px = bx.P[0], Py = bx.P[1], Pz = bx.P[2];
   const int Nh = Px >> 1, H = bx.H, ld = bx.ld;
-  const FftPlanD* plx = a.t.plans + bx.planx;
-  const FftPlanD* ply = a.t.plans + bx.plany;
+  const PlanRef plx = plan_ref(a.t.plans + bx.planx);
+  const PlanRef ply = plan_ref(a.t.plans + bx.plany);
   cx<T>* twy = lds + Py * ld;
   cx<T>* twx = twy + Py;
   cx<T>* twr = twx + Nh;
@@ -1077,10 +1124,9 @@ PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>*
   const cx<T>* gtr = a.t.tw + bx.twr;
 
   // stage-digit positions along y (input of the dit) and x (output of the dif)
-  for (int i = tid; i < Py + Nh; i += nt) {
-    if (i < Py) posy[i] = plan_pos(ply, i);
-    else posx[i - Py] = plan_pos(plx, i - Py);
-  }
+  const int32_t* gpx = a.t.pos + plx->pos;
+  const int32_t* gpy = a.t.pos + ply->pos;
+  for (int i = tid; i < Py + Nh; i += nt) posy[i] = i < Py ? gpy[i] : gpx[i - Py];  // posy, posx are contiguous
   bar();
 
   // half-spectrum rows (ky natural) -> LDS rows in stage-digit order along y
@@ -1174,7 +1220,7 @@ PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>*
                   });
   if constexpr (push) {
     bar();
-    push_guards<T>(a.push, a.push_off[s], a.push_off[s + 1], a.t.box, a.out[f], z - bx.g[2], 0, ny,
+    push_guards<T>(a.push, uniform_load(a.push_off + s), uniform_load(a.push_off + s + 1), a.t.box, a.out[f], z - bx.g[2], 0, ny,
                    [&](int yi, int xi) {
                      const int x = gx + xi;
                      return ldsT[2 * ((gy + yi) * ld + posx[x >> 1]) + (x & 1)];
@@ -1207,18 +1253,18 @@ struct SplitArgs {
 template <typename T, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_x_fwd(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
   const int f = (int)fdiv((uint32_t)item, a.np);
-  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
-  const BoxD& bx = a.t.box[rec.box];
+  const PlaneRec rec = uniform_load(a.planes + (item - f * (int)a.np.d));
+  const BoxD bx = uniform_load(a.t.box + rec.box);
   const int Px = bx.P[0], Py = bx.P[1];
   const int z = rec.z;
   const int y0 = rec.p0;
   const int ny = (Py - y0) < kRB ? (Py - y0) : kRB;
   const int Nh = Px >> 1, H = bx.H, ld = bx.ld;
-  const FftPlanD* plx = a.t.plans + bx.planx;
+  const PlanRef plx = plan_ref(a.t.plans + bx.planx);
   cx<T>* twx = lds + kRB * ld;
   cx<T>* twr = twx + Nh;
   int32_t* posx = reinterpret_cast<int32_t*>(twr + Px);
-  for (int i = tid; i < Nh; i += nt) posx[i] = plan_pos(plx, i);
+  for (int i = tid; i < Nh; i += nt) posx[i] = a.t.pos[plx->pos + i];
   bar();
   const cx<T>* src = reinterpret_cast<const cx<T>*>(a.in[f] + bx.foff + ((int64_t)z * Py + y0) * Px);
   const cx<T>* gtx = a.t.tw + plx->tw;
@@ -1259,15 +1305,15 @@ PSATD_HD void body_x_fwd(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>
 template <typename T, int DIR, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_y(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
   const int f = (int)fdiv((uint32_t)item, a.np);
-  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
-  const BoxD& bx = a.t.box[rec.box];
+  const PlaneRec rec = uniform_load(a.planes + (item - f * (int)a.np.d));
+  const BoxD bx = uniform_load(a.t.box + rec.box);
   const int Py = bx.P[1], H = bx.H;
   const int c0 = rec.p0;
   const int nc = (H - c0) < kCB ? (H - c0) : kCB;
-  const FftPlanD* ply = a.t.plans + bx.plany;
+  const PlanRef ply = plan_ref(a.t.plans + bx.plany);
   cx<T>* twy = lds + Py * kCB;
   int32_t* posy = reinterpret_cast<int32_t*>(twy + Py);
-  for (int i = tid; i < Py; i += nt) posy[i] = plan_pos(ply, i);
+  for (int i = tid; i < Py; i += nt) posy[i] = a.t.pos[ply->pos + i];
   bar();
   cx<T>* col = c0 + (DIR < 0 ? spec_at(a.spec, bx, 0, f) + ring_slot(bx, rec.z) * bx.pp
                              : a.spec + result_plane(bx, 0, f, rec.z));
@@ -1308,9 +1354,9 @@ PSATD_HD void body_y(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>* ld
 template <typename T, bool INC, int MAXR, bool PUSH = false, class Bar, class Eng = FftValu>
 PSATD_HD void body_x_inv(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
   const int f = (int)fdiv((uint32_t)item, a.np);
-  const PlaneRec rec = a.planes[item - f * (int)a.np.d];
+  const PlaneRec rec = uniform_load(a.planes + (item - f * (int)a.np.d));
   const int s = rec.box;
-  const BoxD& bx = a.t.box[s];
+  const BoxD bx = uniform_load(a.t.box + s);
   const int Px = bx.P[0], Py = bx.P[1], Pz = bx.P[2];
   const int nyi = bx.n[1];
   const int zz = rec.z;
@@ -1319,11 +1365,11 @@ PSATD_HD void body_x_inv(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>
   const int ny = (nyi - yy0) < kRB ? (nyi - yy0) : kRB;
   const int y0 = bx.g[1] + yy0;
   const int Nh = Px >> 1, H = bx.H, ld = bx.ld;
-  const FftPlanD* plx = a.t.plans + bx.planx;
+  const PlanRef plx = plan_ref(a.t.plans + bx.planx);
   cx<T>* twx = lds + kRB * ld;
   cx<T>* twr = twx + Nh;
   int32_t* posx = reinterpret_cast<int32_t*>(twr + Px);
-  for (int i = tid; i < Nh; i += nt) posx[i] = plan_pos(plx, i);
+  for (int i = tid; i < Nh; i += nt) posx[i] = a.t.pos[plx->pos + i];
   const cx<T>* src = a.spec + result_plane(bx, 0, f, zz) + (int64_t)y0 * H;
   const cx<T>* gtx = a.t.tw + plx->tw;
   const cx<T>* gtr = a.t.tw + bx.twr;
@@ -1370,7 +1416,7 @@ PSATD_HD void body_x_inv(const SplitArgs<T>& a, int item, int tid, int nt, cx<T>
                      });
   if constexpr (push) {
     bar();
-    push_guards<T>(a.push, a.push_off[s], a.push_off[s + 1], a.t.box, a.out[f], zz, yy0, yy0 + ny,
+    push_guards<T>(a.push, uniform_load(a.push_off + s), uniform_load(a.push_off + s + 1), a.t.box, a.out[f], zz, yy0, yy0 + ny,
                    [&](int yi, int xi) {
                      const int x = gx + xi;
                      return ldsT[2 * ((yi - yy0) * ld + posx[x >> 1]) + (x & 1)];
@@ -1415,9 +1461,9 @@ struct alignas(16) Vec16 {
 // are 16-byte aligned).
 template <typename T>
 PSATD_HD void body_fill(const FillArgs<T>& a, int item, int tid, int nt) {
-  const int b = a.piece_of[item];
-  const FillPiece k = a.piece[b];
-  const int zi = item - a.items[b];
+  const int b = uniform_load(a.piece_of + item);
+  const FillPiece k = uniform_load(a.piece + b);
+  const int zi = item - uniform_load(a.items + b);
   const int sP0 = k.sP0, dP0 = k.dP0;
   const int64_t so = k.so + (int64_t)zi * k.sPl;
   const int64_t dof = k.dof + (int64_t)zi * k.dPl;
@@ -1499,7 +1545,10 @@ PSATD_HD void sum_plane(const SumArgs<T>& a, const SumRegion& r, int zi, int tid
   for (int i = tid; i < r.ly * lw; i += nt) {
     const int y = (int)fdiv((uint32_t)i, dl);
     const int x = (i - y * lw) * E;
-    auto at = [&](int c) { return cs[c].off + (int64_t)zi * cs[c].sPl + (int64_t)y * cs[c].sP0 + x; };
+    auto at = [&](int c) {
+      const SumCopy k = uniform_load(cs + c);
+      return k.off + (int64_t)zi * k.sPl + (int64_t)y * k.sP0 + x;
+    };
     T acc[3][E];
     for (int u = 0; u < 3; ++u)
       for (int e = 0; e < E; ++e) acc[u][e] = T(0);
@@ -1540,9 +1589,9 @@ PSATD_HD void sum_plane(const SumArgs<T>& a, const SumRegion& r, int zi, int tid
 
 template <typename T>
 PSATD_HD void body_sum(const SumArgs<T>& a, int item, int tid, int nt) {
-  const int b = a.region_of[item];
-  const SumRegion r = a.region[b];
-  const int zi = item - a.items[b];
+  const int b = uniform_load(a.region_of + item);
+  const SumRegion r = uniform_load(a.region + b);
+  const int zi = item - uniform_load(a.items + b);
   if (r.vec) sum_plane<T, Vec16<T>>(a, r, zi, tid, nt);
   else sum_plane<T, T>(a, r, zi, tid, nt);
 }

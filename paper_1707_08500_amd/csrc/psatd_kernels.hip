@@ -51,11 +51,20 @@ __device__ __forceinline__ int first_item(int remap) {
   return b;
 }
 
+// The thread's index, opaque to the compiler: the persistent loops of the
+// kernels below would otherwise hoist what depends on it alone out of the loop
+// and hold it in registers through every phase.
+__device__ __forceinline__ int fresh_tid() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 template <typename T, int NT, int MAXR, int SPL>
 __global__ __launch_bounds__(NT) void k_fwd_xy(FwdArgs<T> a, int nitems, int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_fwd_xy<T, MAXR>(a, it, threadIdx.x, NT, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
+    body_fwd_xy<T, MAXR>(a, it, fresh_tid(), NT, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
     __syncthreads();
   }
 }
@@ -64,7 +73,7 @@ template <typename T, bool INC, int NT, int MAXR, int SPL, bool PUSH>
 __global__ __launch_bounds__(NT) void k_inv_xy(InvArgs<T> a, int nitems, int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_inv_xy<T, INC, MAXR, PUSH>(a, it, threadIdx.x, NT, lds, BlockBarrier{},
+    body_inv_xy<T, INC, MAXR, PUSH>(a, it, fresh_tid(), NT, lds, BlockBarrier{},
                                     typename EngOf<SPL>::type{});
     __syncthreads();
   }
@@ -78,9 +87,9 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 1) void k_z_update(UpdArgs
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
     if constexpr (SPL == 0)
-      body_z_direct<T, PB, INC, MAXR>(a, it, threadIdx.x, NT, lds, BlockBarrier{});
+      body_z_direct<T, PB, INC, MAXR>(a, it, fresh_tid(), NT, lds, BlockBarrier{});
     else
-      body_z_update<T, PB, INC, MAXR>(a, it, threadIdx.x, NT, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
+      body_z_update<T, PB, INC, MAXR>(a, it, fresh_tid(), NT, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
     __syncthreads();
   }
 }
@@ -102,7 +111,7 @@ template <typename T, int PB, bool INC, int MAXR, int SPL>
 __global__ __launch_bounds__(kThreadsXY) void k_z_heat(HeatArgs<T> a, int nitems, int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_z_heat<T, PB, INC, MAXR>(a, it, threadIdx.x, kThreadsXY, lds, BlockBarrier{},
+    body_z_heat<T, PB, INC, MAXR>(a, it, fresh_tid(), kThreadsXY, lds, BlockBarrier{},
                                   typename EngOf<SPL>::type{});
     __syncthreads();
   }
@@ -112,7 +121,7 @@ template <typename T, int MAXR, int SPL>
 __global__ __launch_bounds__(kThreadsXY) void k_x_fwd(SplitArgs<T> a, int nitems, int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_x_fwd<T, MAXR>(a, it, threadIdx.x, kThreadsXY, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
+    body_x_fwd<T, MAXR>(a, it, fresh_tid(), kThreadsXY, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
     __syncthreads();
   }
 }
@@ -121,7 +130,7 @@ template <typename T, int DIR, int MAXR, int SPL>
 __global__ __launch_bounds__(kThreadsXY) void k_y(SplitArgs<T> a, int nitems, int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_y<T, DIR, MAXR>(a, it, threadIdx.x, kThreadsXY, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
+    body_y<T, DIR, MAXR>(a, it, fresh_tid(), kThreadsXY, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
     __syncthreads();
   }
 }
@@ -130,7 +139,7 @@ template <typename T, bool INC, int MAXR, int SPL, bool PUSH>
 __global__ __launch_bounds__(kThreadsXY) void k_x_inv(SplitArgs<T> a, int nitems, int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    body_x_inv<T, INC, MAXR, PUSH>(a, it, threadIdx.x, kThreadsXY, lds, BlockBarrier{},
+    body_x_inv<T, INC, MAXR, PUSH>(a, it, fresh_tid(), kThreadsXY, lds, BlockBarrier{},
                                    typename EngOf<SPL>::type{});
     __syncthreads();
   }
@@ -295,6 +304,10 @@ static hipError_t upd_launch(const DevPlan& p, const ZLaunch& l, int g, const Up
 
 template <typename T, int MAXR, int SPL>
 static hipError_t upd_shape(const DevPlan& p, const ZLaunch& l, int g, const UpdArgs<T>& a, hipStream_t st) {
+  if constexpr (SPL == 0) {
+    if (l.narrow && p.ntu == 512 && l.PB == 8) return upd_launch<T, 256, 8, MAXR, SPL>(p, l, g, a, st);
+    if (l.narrow && p.ntu == 512 && l.PB == 10) return upd_launch<T, 256, 10, MAXR, SPL>(p, l, g, a, st);
+  }
   if (l.PB == 4) return upd_launch<T, 512, 4, MAXR, SPL>(p, l, g, a, st);
   if (l.PB == 6) return upd_launch<T, 512, 6, MAXR, SPL>(p, l, g, a, st);
   if (l.PB == 10) return upd_launch<T, 512, 10, MAXR, SPL>(p, l, g, a, st);

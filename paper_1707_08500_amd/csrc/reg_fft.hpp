@@ -18,7 +18,7 @@
 // offset register and a wave-uniform offset per element.
 #pragma once
 
-#include "fft_engine.hpp"
+#include "psatd_device.hpp"
 
 namespace psatd {
 
@@ -108,20 +108,7 @@ __device__ __forceinline__ cx<float> xlane(cx<float> v, float sgn) {
   return {fmaf(sgn, v.x, wr), fmaf(sgn, v.y, wi)};
 }
 
-// Buffer resource over `bytes` bytes at base (raw, untyped; the third word
-// selects 32-bit elements on this GPU family).  Accesses at or beyond `bytes`
-// read zeros and write nothing.
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(void* base, uint32_t bytes) {
-  return __builtin_amdgcn_make_buffer_rsrc(base, (short)0, (int)bytes, 0x00020000);
-}
-
-typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-
 // One complex FP32 value at byte offset voff + soff (soff wave-uniform).
-__device__ __forceinline__ cx<float> buf_load(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff) {
-  const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)voff, (int)soff, 0);
-  return {__uint_as_float(w.x), __uint_as_float(w.y)};
-}
 __device__ __forceinline__ void buf_store(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, cx<float> v) {
   const u32x2 w = {__float_as_uint(v.x), __float_as_uint(v.y)};
   __builtin_amdgcn_raw_buffer_store_b64(w, rs, (int)voff, (int)soff, 0);

@@ -109,7 +109,7 @@ __device__ __forceinline__ void body_z_reg(const UpdArgs<float>& a, const int32_
 
   cx<float> v[E];
 #pragma unroll
-  for (int e = 0; e < E; ++e) v[e] = buf_load(rs, lane_off, e * zstep);
+  for (int e = 0; e < E; ++e) buf_load(rs, lane_off, e * zstep, &v[e]);
 
   // forward transform along z
   RegFft<E, -1, float>::run(v);
