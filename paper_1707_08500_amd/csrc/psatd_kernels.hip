@@ -228,6 +228,10 @@ hipError_t prepare_t(int ldsF, int ldsI, int ldsU, int ldsX, int ldsY) {
     if (ldsI <= kMaxDynLds && (e = set_lds(f, ldsI)) != hipSuccess) return e;
   for (const void* f : upd)
     if ((e = set_lds(f, ldsU)) != hipSuccess) return e;
+  if constexpr (SPL == 0) {
+    if ((e = set_lds((const void*)k_z_update<T, 256, 8, I, MAXR, SPL>, ldsU)) != hipSuccess) return e;
+    if ((e = set_lds((const void*)k_z_update<T, 256, 10, I, MAXR, SPL>, ldsU)) != hipSuccess) return e;
+  }
   const void* heat[] = {(const void*)k_z_heat<T, 4, I, MAXR, SPL>, (const void*)k_z_heat<T, 8, I, MAXR, SPL>,
                         (const void*)k_z_heat<T, 16, I, MAXR, SPL>, (const void*)k_z_heat<T, 32, I, MAXR, SPL>};
   for (const void* f : heat)
