@@ -720,7 +720,22 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
       }
     }
   }
+  // The inverse pass in two halves: FP32 planes beyond the LDS of which half fits
+  // it and a quarter fits the registers set aside for it.
+  auto halve = [&](const std::vector<char>& in) {
+    if (h.prec != PSATD_F32_VALU || h.fuse_eb || h.ldsF <= kMaxDynLds) return 0;
+    int half = 0, quarter = 0;
+    for (int s = 0; s < h.nsub; ++s) {
+      if (!in[s]) continue;
+      const BoxD& b = h.box[s];
+      half = std::max(half, (half_elems(b.P[1], b.ld, b.H) + b.P[0] / 2 + b.P[1] + b.P[0]) * 8 +
+                                (b.P[0] / 2 + b.P[1]) * 4);
+      quarter = std::max(quarter, (b.P[1] + 1) / 2 * half_cols(b.H));
+    }
+    return half <= kMaxDynLds && quarter <= kHalfHold * kThreadsHalf ? half : 0;
+  };
   auto add_planes = [&](const std::vector<char>& in, XyLaunch& l) {
+    l.half = halve(in);
     std::vector<PlaneRec> fwd, inv;
     for (const Ring& r : rings) {
       if (!in[r.boxes[0]]) continue;  // the boxes of a ring have the same plane size
@@ -731,21 +746,21 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
       if (in[s])
         for (int z = 0; z < h.box[s].n[2]; ++z) inv.push_back({s, z, 0, 0});
     // the planes, or (split passes) their blocks of `per` of len(box) rows or columns
-    auto put = [&](std::vector<PlaneRec>& to, const std::vector<PlaneRec>& v, int32_t& at, int32_t& count, int per,
-                   auto len) {
+    auto put = [&](std::vector<PlaneRec>& to, const std::vector<PlaneRec>& v, int32_t& at, int32_t& count, bool blocks,
+                   int per, auto len) {
       at = (int32_t)to.size();
       for (PlaneRec r : v) {
-        if (!h.split) to.push_back(r);
+        if (!blocks) to.push_back(r);
         else
           for (r.p0 = 0; r.p0 < len(h.box[r.box]); r.p0 += per) to.push_back(r);
       }
       count = (int32_t)to.size() - at;
     };
-    put(w.fwd, fwd, l.f0, l.nf, kRB, [](const BoxD& b) { return b.P[1]; });
-    put(w.inv, inv, l.i0, l.ni, kRB, [](const BoxD& b) { return b.n[1]; });
+    put(w.fwd, fwd, l.f0, l.nf, h.split, kRB, [](const BoxD& b) { return b.P[1]; });
+    put(w.inv, inv, l.i0, l.ni, h.split && !l.half, kRB, [](const BoxD& b) { return b.n[1]; });
     if (!h.split) return;
-    put(w.fwd, fwd, l.c0, l.nc, kCB, [](const BoxD& b) { return b.H; });
-    put(w.inv, inv, l.d0, l.nd, kCB, [](const BoxD& b) { return b.H; });
+    put(w.fwd, fwd, l.c0, l.nc, true, kCB, [](const BoxD& b) { return b.H; });
+    if (!l.half) put(w.inv, inv, l.d0, l.nd, true, kCB, [](const BoxD& b) { return b.H; });
   };
   // tiles of a column side by side at the same pencils, so that the planes
   // its boxes share are read by neighbouring work-groups

@@ -289,7 +289,7 @@ psatd_status enqueue_step(psatd_plan_t p, void* const E[3], void* const B[3], vo
     PSATD_MARK(kPhaseUpd, false);
     PSATD_MARK(kPhaseInv, true);
     for (const XyLaunch& l : w.xy[bi]) {
-      if (d.split) {
+      if (d.split && !l.half) {
         HIPCHK(p, launch_y(d, l, 1, 6, ws, st));
         HIPCHK(p, launch_x_inv(d, l, ws, eb, st));
       } else {
@@ -781,6 +781,7 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
       if (value != 0 && value != 1) return fail(p, PSATD_E_INVALID, "fuse must be 0 or 1");
       if (value && p->h.batches.size() > 1)
         return fail(p, PSATD_E_INVALID, "the fused E,B exchange needs all boxes in one batch");
+      relist = p->h.fuse_eb != (value != 0);  // planes in halves have no fused exchange
       p->h.fuse_eb = value != 0;
       d.fuse = value;
       if (value) {  // the inverse pass keeps every guard copy current

@@ -15,6 +15,7 @@ namespace psatd {
 
 // Launch shapes (gfx950: 64-wide waves, 160 KiB LDS per compute unit).
 constexpr int kThreadsXY = 256;   // x/y plane passes, exchange, scatter/gather
+constexpr int kThreadsHalf = 1024;  // x/y passes over planes in two halves
 constexpr int kMaxR = 16;         // largest radix codelet (radix 11 is always available)
 constexpr int kMaxDynLds = 160 * 1024;
 
@@ -94,6 +95,7 @@ struct ZItem {
 // their group size or tile width and their dynamic LDS.
 struct XyLaunch {
   int32_t nt, lds, f0, nf, i0, ni;  // forward planes [f0, f0 + nf), inverse [i0, i0 + ni)
+  int32_t half;                     // LDS of the inverse pass in two halves (0: not taken)
   int32_t c0, nc, d0, nd;           // split passes: forward and inverse column blocks
 };
 struct ZLaunch {
@@ -514,6 +516,56 @@ PSATD_HD void copy_rect_to_plane(const T* src, int sP0, int ly, int lx, int y0, 
   }
 }
 
+// Rows [y0, y1) of a padded plane into LDS rows 0, 1, ...
+template <typename T>
+PSATD_HD void load_rows(const FwdArgs<T>& a, const PlaneRec& rec, const BoxD& bx, int f, int y0, int y1, cx<T>* lds,
+                        const int32_t* posx, int tid, int nt) {
+  const int Px = bx.P[0], Py = bx.P[1], Nh = Px >> 1, ld = bx.ld, z = rec.z;
+  if (f < a.npull) {
+    // The box's own interior cells, then every guard region of this plane
+    // from the box that owns it (Fig. 3 step 3 fused into the next push).
+    // The waves share the rectangles (the interior in one row band per wave,
+    // the pieces that meet the plane dealt round-robin), each copying its own
+    // with its 64 lanes, so their memory round trips overlap.
+    const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
+    const int gx = bx.g[0], gy = bx.g[1], gz = bx.g[2];
+    const T* inf = a.in[f];
+    int dealt = 0;
+    if (z >= gz && z < gz + bx.n[2]) {
+      const int lo = y0 > gy ? y0 : gy, hi = y1 < gy + bx.n[1] ? y1 : gy + bx.n[1];  // interior rows among them
+      const int ny = hi > lo ? hi - lo : 0;
+      const int r0 = (int)(((int64_t)ny * wave) / nw), r1 = (int)(((int64_t)ny * (wave + 1)) / nw);
+      if (r1 > r0)
+        copy_rect_to_plane<T>(inf + bx.foff + ((int64_t)z * Py + lo + r0) * Px + gx, Px, r1 - r0, bx.n[0],
+                              lo + r0 - y0, gx, lds, ld, posx, lane, 64);
+      dealt = nw;
+    }
+    for (int b = rec.p0; b < rec.p1; ++b) {
+      if (dealt++ % nw != wave) continue;
+      const PullPiece k = uniform_load(a.pull + b);
+      const int lo = y0 > k.qy ? y0 : k.qy, hi = y1 < k.qy + k.ly ? y1 : k.qy + k.ly;
+      if (hi <= lo) continue;
+      copy_rect_to_plane<T>(inf + k.so + (int64_t)(z - k.qz) * k.sPl + (int64_t)(lo - k.qy) * k.sP0, k.sP0, hi - lo,
+                            k.lx, lo - y0, k.qx, lds, ld, posx, lane, 64);
+    }
+    return;
+  }
+  const cx<T>* src = reinterpret_cast<const cx<T>*>(a.in[f] + bx.foff + ((int64_t)z * Py + y0) * Px);
+  if ((Nh & 1) == 0 && (reinterpret_cast<uintptr_t>(src) % sizeof(Pair<cx<T>>)) == 0) {
+    // two neighbouring complex values per access (rows of even length)
+    const Pair<cx<T>>* src2 = reinterpret_cast<const Pair<cx<T>>*>(src);
+    copy_grid<4, Pair<cx<T>>>(y1 - y0, Nh >> 1, tid, nt, [&](int i, int, int) { return src2[i]; },
+                              [&](int, int y, int x2, Pair<cx<T>> v) {
+                                cx<T>* row = lds + y * ld;
+                                row[posx[2 * x2]] = v.a;
+                                row[posx[2 * x2 + 1]] = v.b;
+                              });
+  } else {
+    copy_grid<8, cx<T>>(y1 - y0, Nh, tid, nt, [&](int i, int, int) { return src[i]; },
+                        [&](int, int y, int x, cx<T> v) { lds[y * ld + posx[x]] = v; });
+  }
+}
+
 // LDS: the plane [y][x] with row stride ld, then the twiddles of the x plan
 // (Nh), the y plan (Py) and W_Px (real <-> half spectrum).
 template <typename T, int MAXR, class Bar, class Eng = FftValu>
@@ -542,46 +594,9 @@ PSATD_HD void body_fwd_xy(const FwdArgs<T>& a, int item, int tid, int nt, cx<T>*
   bar();
   // packed real rows (x natural) -> LDS rows in stage-digit order along x,
   // together with the three twiddle tables
-  const cx<T>* src = reinterpret_cast<const cx<T>*>(a.in[f] + bx.foff + (int64_t)z * Py * Px);
   for (int i = tid; i < Nh + Py + Px; i += nt)  // twx, twy, twr are contiguous
     twx[i] = i < Nh ? gtx[i] : (i < Nh + Py ? gty[i - Nh] : gtr[i - Nh - Py]);
-  if (f < a.npull) {
-    // The box's own interior cells, then every guard region of this plane
-    // from the box that owns it (Fig. 3 step 3 fused into the next push).
-    // The waves share the rectangles (the interior in one row band per wave,
-    // the pieces that meet the plane dealt round-robin), each copying its own
-    // with its 64 lanes, so their memory round trips overlap.
-    const int lane = tid & 63, wave = tid >> 6, nw = nt >> 6;
-    const int gx = bx.g[0], gy = bx.g[1], gz = bx.g[2];
-    const T* inf = a.in[f];
-    int dealt = 0;
-    if (z >= gz && z < gz + bx.n[2]) {
-      const int ny = bx.n[1];
-      const int r0 = (int)(((int64_t)ny * wave) / nw), r1 = (int)(((int64_t)ny * (wave + 1)) / nw);
-      if (r1 > r0)
-        copy_rect_to_plane<T>(inf + bx.foff + ((int64_t)z * Py + gy + r0) * Px + gx, Px, r1 - r0, bx.n[0], gy + r0,
-                              gx, lds, ld, posx, lane, 64);
-      dealt = nw;
-    }
-    for (int b = rec.p0; b < rec.p1; ++b) {
-      if (dealt++ % nw != wave) continue;
-      const PullPiece k = uniform_load(a.pull + b);
-      copy_rect_to_plane<T>(inf + k.so + (int64_t)(z - k.qz) * k.sPl, k.sP0, k.ly, k.lx, k.qy, k.qx, lds, ld, posx,
-                            lane, 64);
-    }
-  } else if ((Nh & 1) == 0 && (reinterpret_cast<uintptr_t>(src) % sizeof(Pair<cx<T>>)) == 0) {
-    // two neighbouring complex values per access (rows of even length)
-    const Pair<cx<T>>* src2 = reinterpret_cast<const Pair<cx<T>>*>(src);
-    copy_grid<4, Pair<cx<T>>>(Py, Nh >> 1, tid, nt, [&](int i, int, int) { return src2[i]; },
-                              [&](int, int y, int x2, Pair<cx<T>> v) {
-                                cx<T>* row = lds + y * ld;
-                                row[posx[2 * x2]] = v.a;
-                                row[posx[2 * x2 + 1]] = v.b;
-                              });
-  } else {
-    copy_grid<8, cx<T>>(Py, Nh, tid, nt, [&](int i, int, int) { return src[i]; },
-                        [&](int, int y, int x, cx<T> v) { lds[y * ld + posx[x]] = v; });
-  }
+  load_rows(a, rec, bx, f, 0, Py, lds, posx, tid, nt);
   bar();
   eng.template dit<-1, MAXR>(lds, Py, ld, 1, plx, twx, tid, nt, bar);
   pair_pass_rows<true>(lds, Py, ld, Nh, twr, tid, nt);
@@ -1101,6 +1116,68 @@ struct InvArgs {
   const int32_t* push_off;   // pieces of box s: [push_off[s], push_off[s+1])
 };
 
+// Interior cells gx, gx + 1, ... of ny transformed LDS rows, scaled, to rows of
+// dst0 (INC: added).
+template <typename T, bool INC>
+PSATD_HD void store_rows(T* dst0, int Px, int ny, int nx, int gx, double sc, const cx<T>* lds, int ld,
+                         const int32_t* posx, int tid, int nt) {
+  if (sizeof(T) == 4 && (gx & 1) == 0 && (nx & 3) == 0 && (Px & 3) == 0 &&
+      (reinterpret_cast<uintptr_t>(dst0) % sizeof(Pair<Pair<T>>)) == 0) {
+    // FP32: four cells (two complex LDS entries, 16 bytes) per access
+    const int hx = gx >> 1;
+    using Q = Pair<Pair<T>>;
+    copy_grid<4, Q>(ny, nx >> 2, tid, nt,
+                    [&](int, int yy, int x4) {
+                      const cx<T>* row = lds + yy * ld;
+                      const cx<T> v0 = row[posx[hx + 2 * x4]], v1 = row[posx[hx + 2 * x4 + 1]];
+                      return Q{{(T)((double)v0.x * sc), (T)((double)v0.y * sc)},
+                               {(T)((double)v1.x * sc), (T)((double)v1.y * sc)}};
+                    },
+                    [&](int, int yy, int x4, Q v) {
+                      Q* q = reinterpret_cast<Q*>(dst0 + (int64_t)yy * Px) + x4;
+                      if (INC) {  // v is the increment
+                        const Q o = *q;
+                        v.a.a = o.a.a + v.a.a;
+                        v.a.b = o.a.b + v.a.b;
+                        v.b.a = o.b.a + v.b.a;
+                        v.b.b = o.b.b + v.b.b;
+                      }
+                      *q = v;
+                    });
+    return;
+  }
+  if (((gx | nx) & 1) == 0 && (reinterpret_cast<uintptr_t>(dst0) % sizeof(Pair<T>)) == 0) {
+    // cells x, x+1 (x even) are the two halves of one complex LDS entry: one
+    // LDS read and one 2-wide access per pair
+    const int hx = gx >> 1;
+    copy_grid<8, Pair<T>>(ny, nx >> 1, tid, nt,
+                          [&](int, int yy, int x2) {
+                            const cx<T> v = lds[yy * ld + posx[hx + x2]];
+                            return Pair<T>{(T)((double)v.x * sc), (T)((double)v.y * sc)};
+                          },
+                          [&](int, int yy, int x2, Pair<T> v) {
+                            Pair<T>* q = reinterpret_cast<Pair<T>*>(dst0 + (int64_t)yy * Px) + x2;
+                            if (INC) {  // v is the increment
+                              const Pair<T> o = *q;
+                              v.a = o.a + v.a;
+                              v.b = o.b + v.b;
+                            }
+                            *q = v;
+                          });
+    return;
+  }
+  copy_grid<8, T>(ny, nx, tid, nt,
+                  [&](int, int yy, int xi) {
+                    const int x = gx + xi;
+                    const cx<T> v = lds[yy * ld + posx[x >> 1]];
+                    return (T)((double)((x & 1) ? v.y : v.x) * sc);
+                  },
+                  [&](int, int yy, int xi, T v) {
+                    T* q = dst0 + (int64_t)yy * Px + xi;
+                    *q = INC ? *q + v : v;  // INC: v is the increment
+                  });
+}
+
 // LDS: the plane with row stride ld, then the twiddles of the y plan (Py),
 // the x plan (Nh) and W_Px.
 template <typename T, bool INC, int MAXR, bool PUSH = false, class Bar, class Eng = FftValu>
@@ -1158,50 +1235,8 @@ PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>*
   T* dst = a.out[f] + bx.foff + (int64_t)z * Py * Px;
   [[maybe_unused]] T* ldsT = reinterpret_cast<T*>(lds);
   constexpr bool push = PUSH;  // the fused E,B exchange (compiled only where used)
-  T* dst0 = dst + (int64_t)gy * Px + gx;  // first interior cell of the plane
-  if (!push && sizeof(T) == 4 && (gx & 1) == 0 && (nx & 3) == 0 && (Px & 3) == 0 &&
-      (reinterpret_cast<uintptr_t>(dst0) % sizeof(Pair<Pair<T>>)) == 0) {
-    // FP32: four cells (two complex LDS entries, 16 bytes) per access
-    const int hx = gx >> 1;
-    using Q = Pair<Pair<T>>;
-    copy_grid<4, Q>(ny, nx >> 2, tid, nt,
-                    [&](int, int yy, int x4) {
-                      const cx<T>* row = lds + (gy + yy) * ld;
-                      const cx<T> v0 = row[posx[hx + 2 * x4]], v1 = row[posx[hx + 2 * x4 + 1]];
-                      return Q{{(T)((double)v0.x * sc), (T)((double)v0.y * sc)},
-                               {(T)((double)v1.x * sc), (T)((double)v1.y * sc)}};
-                    },
-                    [&](int, int yy, int x4, Q v) {
-                      Q* q = reinterpret_cast<Q*>(dst0 + (int64_t)yy * Px) + x4;
-                      if (INC) {  // v is the increment
-                        const Q o = *q;
-                        v.a.a = o.a.a + v.a.a;
-                        v.a.b = o.a.b + v.a.b;
-                        v.b.a = o.b.a + v.b.a;
-                        v.b.b = o.b.b + v.b.b;
-                      }
-                      *q = v;
-                    });
-    return;
-  }
-  if (!push && ((gx | nx) & 1) == 0 && (reinterpret_cast<uintptr_t>(dst0) % sizeof(Pair<T>)) == 0) {
-    // cells x, x+1 (x even) are the two halves of one complex LDS entry: one
-    // LDS read and one 2-wide access per pair
-    const int hx = gx >> 1;
-    copy_grid<8, Pair<T>>(ny, nx >> 1, tid, nt,
-                          [&](int, int yy, int x2) {
-                            const cx<T> v = lds[(gy + yy) * ld + posx[hx + x2]];
-                            return Pair<T>{(T)((double)v.x * sc), (T)((double)v.y * sc)};
-                          },
-                          [&](int, int yy, int x2, Pair<T> v) {
-                            Pair<T>* q = reinterpret_cast<Pair<T>*>(dst0 + (int64_t)yy * Px) + x2;
-                            if (INC) {  // v is the increment
-                              const Pair<T> o = *q;
-                              v.a = o.a + v.a;
-                              v.b = o.b + v.b;
-                            }
-                            *q = v;
-                          });
+  if (!push) {
+    store_rows<T, INC>(dst + (int64_t)gy * Px + gx, Px, ny, nx, gx, sc, lds + gy * ld, ld, posx, tid, nt);
     return;
   }
   copy_grid<8, T>(ny, nx, tid, nt,
@@ -1226,6 +1261,120 @@ PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>*
                      return ldsT[2 * ((gy + yi) * ld + posx[x >> 1]) + (x & 1)];
                    },
                    tid, nt);
+  }
+}
+
+// ------------------------------------------------ planes in two halves
+// The inverse pass over FP32 planes beyond the LDS of which half fits: the y
+// columns are transformed in two halves of ceil(H/2), the interior x rows in two
+// halves, with what is not being transformed in registers (the vector registers
+// of a compute unit hold three times its LDS).  That saves the passes of their
+// own for y and x and the round trip through the workspace between them: one
+// 256^3 box 0.55 -> 0.39 ms; planes of 200^2 to 360 x 176 8 to 30 % faster (300 x
+// 144, in three stages each way, 4 % slower).  The forward pass keeps the split
+// passes: 256^2 0.40 -> 0.35 ms in halves, but 200^2 to 240 x 216 0.21 -> 0.24 and
+// 0.12 -> 0.15 (a lone group per compute unit exposes every stage).  So do FP64
+// planes (176^2, 8 boxes: inverse 1.19 -> 1.36 ms), and FP32 planes that fit the
+// LDS once stay whole (176^2 as two 512-thread groups per compute unit, 64 boxes:
+// 3.5 -> 4.3 ms).
+constexpr int kHalfHold = 10;  // values held per thread and quarter plane
+
+// LDS elements of half a plane: ceil(Py/2) rows, or Py rows of half the columns.
+PSATD_HD int half_cols(int H) { return (H + 1) >> 1; }
+PSATD_HD int half_ld(int H) { return half_cols(H) | 1; }
+PSATD_HD int half_elems(int Py, int ld, int H) {
+  const int rows = ((Py + 1) >> 1) * ld, cols = Py * half_ld(H);
+  return rows > cols ? rows : cols;
+}
+
+// Moves an R x C block between the LDS (rows of pitch ld) and the threads'
+// registers, element i = tid + k nt in v[k] (R C <= K nt, checked at plan time).
+template <int K, bool SAVE, typename T>
+PSATD_HD void hold_block(cx<T>* v, cx<T>* lds, int R, int C, int ld, int tid, int nt) {
+  const FastDiv dC = make_fastdiv((uint32_t)C);
+  int r = (int)fdiv((uint32_t)tid, dC);
+  int c = tid - r * C;
+  const int dr = (int)fdiv((uint32_t)nt, dC);
+  const int dc = nt - dr * C;
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    if (tid + k * nt < R * C) {
+      if (SAVE) v[k] = lds[r * ld + c];
+      else lds[r * ld + c] = v[k];
+    }
+    c += dc;
+    r += dr;
+    if (c >= C) {
+      c -= C;
+      ++r;
+    }
+  }
+}
+
+template <typename T, bool INC, int MAXR, class Bar>
+PSATD_HD void body_inv_half(const InvArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar) {
+  constexpr int K = kHalfHold;
+  const int f = (int)fdiv((uint32_t)item, a.np);
+  const PlaneRec rec = uniform_load(a.planes + (item - f * (int)a.np.d));
+  const BoxD bx = uniform_load(a.t.box + rec.box);
+  const int z = bx.g[2] + rec.z;
+  const int Px = bx.P[0], Py = bx.P[1], Pz = bx.P[2];
+  const int Nh = Px >> 1, H = bx.H, ld = bx.ld;
+  const int ny = bx.n[1], gy = bx.g[1];
+  const int Ra = (ny + 1) >> 1, Hl = half_cols(H), Hr = H - Hl, ldc = half_ld(H);
+  const PlanRef plx = plan_ref(a.t.plans + bx.planx);
+  const PlanRef ply = plan_ref(a.t.plans + bx.plany);
+  cx<T>* twy = lds + half_elems(Py, ld, H);
+  cx<T>* twx = twy + Py;
+  cx<T>* twr = twx + Nh;
+  int32_t* posy = reinterpret_cast<int32_t*>(twr + Px);
+  int32_t* posx = posy + Py;
+  const cx<T>* gty = a.t.tw + ply->tw;
+  const cx<T>* gtx = a.t.tw + plx->tw;
+  const cx<T>* gtr = a.t.tw + bx.twr;
+  const int32_t* gpx = a.t.pos + plx->pos;
+  const int32_t* gpy = a.t.pos + ply->pos;
+  for (int i = tid; i < Py + Nh; i += nt) posy[i] = i < Py ? gpy[i] : gpx[i - Py];  // posy, posx are contiguous
+  for (int i = tid; i < Py + Nh + Px; i += nt)  // twy, twx, twr are contiguous
+    twy[i] = i < Py ? gty[i] : (i < Py + Nh ? gtx[i - Py] : gtr[i - Py - Nh]);
+  bar();
+  const cx<T>* src = a.spec + result_plane(bx, a.sbias, f, rec.z);
+  cx<T> al[K], bl[K], br[K];  // interior rows: first half (left columns), second half (left, right)
+#pragma unroll 1
+  for (int side = 0; side < 2; ++side) {
+    const int C = side ? Hr : Hl, c0 = side ? Hl : 0;
+    copy_grid<8, cx<T>>(Py, C, tid, nt, [&](int, int ky, int c) { return src[ky * H + c0 + c]; },
+                        [&](int, int ky, int c, cx<T> v) { lds[posy[ky] * ldc + c] = v; });
+    bar();
+    fft_dit<+1, MAXR>(lds, C, 1, ldc, ply, twy, tid, nt, bar);
+    if (side) break;
+    hold_block<K, true>(al, lds + gy * ldc, Ra, Hl, ldc, tid, nt);
+    hold_block<K, true>(bl, lds + (gy + Ra) * ldc, ny - Ra, Hl, ldc, tid, nt);
+    bar();
+  }
+  {
+    cx<T> ar[K];
+    hold_block<K, true>(ar, lds + gy * ldc, Ra, Hr, ldc, tid, nt);
+    hold_block<K, true>(br, lds + (gy + Ra) * ldc, ny - Ra, Hr, ldc, tid, nt);
+    bar();
+    hold_block<K, false>(al, lds, Ra, Hl, ld, tid, nt);
+    hold_block<K, false>(ar, lds + Hl, Ra, Hr, ld, tid, nt);
+  }
+  const double sc = 1.0 / ((double)Px * (double)Py * (double)Pz);  // in FP64, rounded once (see body_inv_xy)
+  const int nx = bx.n[0], gx = bx.g[0];
+  T* dst0 = a.out[f] + bx.foff + ((int64_t)z * Py + gy) * Px + gx;
+#pragma unroll 1
+  for (int part = 0; part < 2; ++part) {
+    const int R = part ? ny - Ra : Ra;
+    bar();
+    pair_pass_rows<false>(lds, R, ld, Nh, twr, tid, nt);
+    bar();
+    fft_dif<+1, MAXR>(lds, R, ld, 1, plx, twx, tid, nt, bar);
+    store_rows<T, INC>(dst0 + (part ? (int64_t)Ra * Px : 0), Px, R, nx, gx, sc, lds, ld, posx, tid, nt);
+    if (part) return;
+    bar();
+    hold_block<K, false>(bl, lds, ny - Ra, Hl, ld, tid, nt);
+    hold_block<K, false>(br, lds + Hl, ny - Ra, Hr, ld, tid, nt);
   }
 }
 

@@ -79,6 +79,16 @@ __global__ __launch_bounds__(NT) void k_inv_xy(InvArgs<T> a, int nitems, int rem
   }
 }
 
+// Planes in two halves.
+template <typename T, bool INC, int MAXR>
+__global__ __launch_bounds__(kThreadsHalf) void k_inv_half(InvArgs<T> a, int nitems, int remap) {
+  cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
+  for (int it = first_item(remap); it < nitems; it += gridDim.x) {
+    body_inv_half<T, INC, MAXR>(a, it, fresh_tid(), kThreadsHalf, lds, BlockBarrier{});
+    __syncthreads();
+  }
+}
+
 // FP32: at most 128 VGPRs, so that two 512-thread tiles share a CU (four
 // waves per SIMD); FP64 tiles measured slower when held to that budget.
 template <typename T, int NT, int PB, bool INC, int MAXR, int SPL>
@@ -229,6 +239,9 @@ hipError_t prepare_t(int ldsF, int ldsI, int ldsU, int ldsX, int ldsY) {
   for (const void* f : upd)
     if ((e = set_lds(f, ldsU)) != hipSuccess) return e;
   if constexpr (SPL == 0) {
+    if constexpr (sizeof(T) == 4) {
+      if ((e = set_lds((const void*)k_inv_half<T, I, MAXR>, kMaxDynLds)) != hipSuccess) return e;
+    }
     if ((e = set_lds((const void*)k_z_update<T, 256, 8, I, MAXR, SPL>, ldsU)) != hipSuccess) return e;
     if ((e = set_lds((const void*)k_z_update<T, 256, 10, I, MAXR, SPL>, ldsU)) != hipSuccess) return e;
   }
@@ -280,6 +293,15 @@ struct FwdGo {
     return hipGetLastError();
   }
 };
+
+// The same for planes in two halves (FP32 vector-ALU form).
+static hipError_t inv_half(const DevPlan& p, const InvArgs<float>& a, int g, int lds, int n, hipStream_t st) {
+  PSATD_MAXR_SWITCH(
+      0, p.maxr,
+      hipLaunchKernelGGL((k_inv_half<float, true, 8>), dim3(g), dim3(kThreadsHalf), lds, st, a, n, p.xcd),
+      hipLaunchKernelGGL((k_inv_half<float, true, 16>), dim3(g), dim3(kThreadsHalf), lds, st, a, n, p.xcd));
+  return hipGetLastError();
+}
 
 template <typename T, int SPL>
 hipError_t fwd_t(const DevPlan& p, const XyLaunch& l, int64_t sbias, void* const* in9, int nf, int npull, void* spec,
@@ -371,6 +393,9 @@ hipError_t inv_t(const DevPlan& p, const XyLaunch& l, int64_t sbias, const void*
   const bool fuse = p.fuse && nf == 6;
   a.push = fuse ? p.push : nullptr;
   a.push_off = fuse ? p.push_off : nullptr;
+  if constexpr (SPL == 0 && sizeof(T) == 4) {
+    if (l.half) return inv_half(p, a, g, l.half, n, st);
+  }
   return xy_shape<T, SPL>(p, l.nt, InvGo<T>{p, a, g, l.lds, n, st});
 }
 
