@@ -53,7 +53,8 @@ constexpr float bf16_value(uint16_t h) { return __builtin_bit_cast(float, (uint3
 // split into SPL BF16 terms, made by the compiler: w[term][re, im][lane][v].  Split
 // at run time they cost each wave some 250 instructions and a gather of FP64
 // constants per transform, as much as one or two of the five chunks that a wave then
-// multiplies with them.
+// multiplies with them.  8 boxes of 96^3 padded, six products, per pass: z 0.22 ->
+// 0.17 ms, forward x/y of 6 fields 0.102 -> 0.089 ms, inverse 0.092 -> 0.076 ms.
 template <int DIR, int SPL>
 struct Dft16Table {
   alignas(16) uint16_t w[SPL][2][64][8];
@@ -111,7 +112,8 @@ PSATD_HD Dft16Operand<SPL> dft16_operand(int lane) {
 // chunk iterations (idle lanes repeat the last column and store nothing), so a
 // model of the instruction that synchronises the work-group sees uniform calls.
 // The loads of a chunk (4 elements, 4 twiddles; 1 where there is none) stand
-// together before its products, without branches.
+// together before its products, without branches: 0.168 -> 0.161, 0.089 -> 0.085
+// and 0.076 -> 0.074 ms on the same boxes.
 template <int DIR, bool DIF, int SPL, class Mma>
 PSATD_HD void dft16_mfma(cx<float>* buf, int M, FastDiv dM, int ms, int es, int N,
                          const cx<float>* tw, int tid, int nt, const Mma& mma) {

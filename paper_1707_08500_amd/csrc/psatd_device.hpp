@@ -881,7 +881,8 @@ PSATD_HD void stage_tile(const BoxD& bx, const cx<T>* src, int64_t sbias, int q0
 // stores straight from the last stage's butterflies measured 1.0 -> 1.5 ms (64 boxes
 // of 96^3 padded, FP32).  Issue-bound (65 % of the time is VALU busy); with the
 // loads and pairs as here 1.03 -> 0.90 ms, FP64 2.32 -> 2.08 ms, 8 boxes of 176^3 in
-// FP64 2.44 -> 2.03 ms.
+// FP64 2.44 -> 2.03 ms; the pairs in the matrix-core forms 0.220 -> 0.211 ms on 8
+// boxes of 96^3.
 template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
   constexpr bool VALU = std::is_same<Eng, FftValu>::value;
