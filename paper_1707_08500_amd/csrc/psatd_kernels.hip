@@ -117,8 +117,11 @@ void k_z_reg(UpdArgs<float> a, const int32_t* items, int nitems, int remap) {
   }
 }
 
+// FP32: at most 128 VGPRs (4 waves per SIMD); the compiler's own choice of 130 left
+// three resident: 0.155 -> 0.134 ms on 64 boxes of 96^3 padded.  Budgets for 5 and 6
+// waves spill: 0.187 and 0.269 ms.
 template <typename T, int PB, bool INC, int MAXR, int SPL>
-__global__ __launch_bounds__(kThreadsXY) void k_z_heat(HeatArgs<T> a, int nitems, int remap) {
+__global__ __launch_bounds__(kThreadsXY, sizeof(T) == 4 && SPL == 0 ? 4 : 1) void k_z_heat(HeatArgs<T> a, int nitems, int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
     body_z_heat<T, PB, INC, MAXR>(a, it, fresh_tid(), kThreadsXY, lds, BlockBarrier{},
