@@ -757,15 +757,6 @@ PSATD_HD void update_apply(T* vr, T* vi /* E0 E1 E2 B0 B1 B2 J0 J1 J2 */, const 
   update_half<-1>(vi, vr + 3, vi + 6, u);
 }
 
-// Eqs. PSATD_1 / PSATD_2 at one k-point: the coefficients (FP64, rounded to T
-// once), then the multiply-adds in T.
-template <typename T, bool INC = false>
-PSATD_HD void psatd_point(T* vr, T* vi /* E0 E1 E2 B0 B1 B2 J0 J1 J2 */, double kx, double ky,
-                          double kz, double c, double dt) {
-  const double rc = 1.0 / c;  // uniform: hoisted out of the k-point loop
-  update_apply<T>(vr, vi, update_coef<T, INC>(kx, ky, kz, c, rc, dt));
-}
-
 template <typename T>
 struct UpdArgs {
   Tables<T> t;
@@ -799,85 +790,6 @@ PSATD_HD void store_results(const BoxD& bx, cx<T>* dst, int64_t sbias, int q0, i
                        [&](int, int f, int z, int p, cx<T> v) {
                          if (p < np) dst[result_plane(bx, sbias, f, z) + p] = v;
                        });
-}
-
-// The 9 fields of PB consecutive (ky, kx) pencils are staged in LDS as
-// [z][f * PB + p] (W = 9 PB complex per z row), so that all 9 (then the 6
-// output) fields are transformed by one multi-transform pass with a uniform
-// element stride W.  Pencils past the end of the box (last block) are zeros.
-template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
-PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
-  const ZItem it = uniform_load(a.items + item);
-  const BoxD bx = uniform_load(a.t.box + it.box);
-  const int Py = bx.P[1], Pz = bx.P[2], H = bx.H;
-  const int nq = Py * H;
-  const int q0 = it.q0;
-  const int np = (nq - q0) < PB ? (nq - q0) : PB;
-  const PlanRef plz = plan_ref(a.t.plans + bx.planz);
-  constexpr int W = 9 * PB;
-  cx<T>* twz = lds + Pz * W;
-  int32_t* kzi = reinterpret_cast<int32_t*>(twz + Pz);  // frequency at each z slot
-  const cx<T>* gtz = a.t.tw + plz->tw;
-  for (int i = tid; i < Pz; i += nt) kzi[a.t.pos[plz->pos + i]] = i;
-  const cx<T>* src = spec_at(a.spec, bx, a.sbias, 0) + q0;
-  const int64_t slab = bx.sv;  // field stride
-  const int ring = bx.ring, zb = bx.zb;
-  auto plane = [&](int z) {
-    const int v = zb + z;
-    return (v >= ring ? v - ring : v) * bx.pp;
-  };
-  for (int i = tid; i < Pz; i += nt) twz[i] = gtz[i];
-  // a full tile whose pencil runs start at even offsets moves two neighbouring
-  // pencils per access
-  const bool pairs = (PB % 2) == 0 && np == PB &&
-                     ((bx.pp | slab | (bx.sb - a.sbias + q0)) & 1) == 0;
-  if (pairs) {
-    // up to 8 loads in flight per thread (a 96-plane FP32 tile of 8 pencils is
-    // 6.75 pairs per thread of 512: one batch)
-    copy_grid3<8, Pair<cx<T>>>(9, Pz, PB / 2, tid, nt,
-        [&](int, int f, int z, int p2) {
-          return *reinterpret_cast<const Pair<cx<T>>*>(src + f * slab + plane(z) + 2 * p2);
-        },
-        [&](int, int f, int z, int p2, Pair<cx<T>> v) {
-          *reinterpret_cast<Pair<cx<T>>*>(lds + z * W + f * PB + 2 * p2) = v;
-        });
-  } else {
-    copy_grid3<8, cx<T>>(9, Pz, PB, tid, nt,
-        [&](int, int f, int z, int p) {
-          return (p < np) ? src[f * slab + plane(z) + p] : cx<T>{T(0), T(0)};
-        },
-        [&](int, int f, int z, int p, cx<T> v) { lds[z * W + f * PB + p] = v; });
-  }
-  bar();
-  eng.template dif<-1, MAXR>(lds, 9 * PB, 1, W, plz, twz, tid, nt, bar);
-
-  const double* kxt = a.t.kmod + bx.kx;
-  const double* kyt = a.t.kmod + bx.ky;
-  const double* kzt = a.t.kmod + bx.kz;
-  const FastDiv dH = make_fastdiv((uint32_t)H);
-  for (int i = tid; i < Pz * PB; i += nt) {
-    const int slot = i / PB;
-    const int p = i % PB;
-    if (p >= np) continue;
-    cx<T>* row = lds + slot * W + p;
-    T vr[9], vi[9];
-#pragma unroll
-    for (int f = 0; f < 9; ++f) {
-      const cx<T> v = row[f * PB];
-      vr[f] = v.x;
-      vi[f] = v.y;
-    }
-    const int q = q0 + p;
-    const int ky = (int)fdiv((uint32_t)q, dH);
-    const int kx = q - ky * H;
-    psatd_point<T, INC>(vr, vi, kxt[kx], kyt[ky], kzt[kzi[slot]], a.k.c, a.k.dt);
-#pragma unroll
-    for (int f = 0; f < 6; ++f) row[f * PB] = cx<T>{vr[f], vi[f]};
-  }
-  bar();
-  eng.template dit<+1, MAXR>(lds, 6 * PB, 1, W, plz, twz, tid, nt, bar);
-
-  store_results<T, PB>(bx, a.spec + q0, a.sbias, q0, np, lds, tid, nt);
 }
 
 // Loads of the first z stage: element z = j + q ms of transform m = f PB + p is
@@ -933,16 +845,47 @@ struct ZLoad {
   }
 };
 
-// The z pass of the vector-ALU forms.  Same tile as body_z_update, with the
-// first z stage reading the ring's planes straight into its butterflies, and
-// with the update taking the points kz and -kz of a pencil together: they share
-// |[k]| and so the FP64 coefficients.  The results go out through the LDS in
-// whole pencil runs: stores straight from the last stage's butterflies measured
-// 1.0 -> 1.5 ms (64 boxes of 96^3 padded, FP32).  Issue-bound (65 % of the time
-// is VALU busy); with the loads and pairs as here 1.03 -> 0.90 ms, FP64 2.32 ->
-// 2.08 ms, 8 boxes of 176^3 in FP64 2.44 -> 2.03 ms.
-template <typename T, int PB, bool INC, int MAXR, class Bar>
-PSATD_HD void body_z_direct(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar) {
+// The 9 fields of a tile's pencils into the LDS as [z][f PB + p]; those past np are
+// zeros.  A full tile whose pencil runs start at even offsets moves two neighbouring
+// pencils per access.
+template <typename T, int PB>
+PSATD_HD void stage_tile(const BoxD& bx, const cx<T>* src, int64_t sbias, int q0, int np, cx<T>* lds, int tid,
+                         int nt) {
+  constexpr int W = 9 * PB;
+  const int Pz = bx.P[2];
+  const int64_t slab = bx.sv;  // field stride
+  if (PB % 2 == 0 && np == PB && ((bx.pp | slab | (bx.sb - sbias + q0)) & 1) == 0) {
+    copy_grid3<8, Pair<cx<T>>>(9, Pz, PB / 2, tid, nt,
+        [&](int, int f, int z, int p2) {
+          return *reinterpret_cast<const Pair<cx<T>>*>(src + f * slab + ring_slot(bx, z) * bx.pp + 2 * p2);
+        },
+        [&](int, int f, int z, int p2, Pair<cx<T>> v) {
+          *reinterpret_cast<Pair<cx<T>>*>(lds + z * W + f * PB + 2 * p2) = v;
+        });
+    return;
+  }
+  copy_grid3<8, cx<T>>(9, Pz, PB, tid, nt,
+      [&](int, int f, int z, int p) {
+        return (p < np) ? src[f * slab + ring_slot(bx, z) * bx.pp + p] : cx<T>{T(0), T(0)};
+      },
+      [&](int, int f, int z, int p, cx<T> v) { lds[z * W + f * PB + p] = v; });
+}
+
+// The z pass.  The 9 fields of PB consecutive (ky, kx) pencils are held in the LDS
+// as [z][f PB + p] (W = 9 PB complex per z row), so that all 9 (then the 6 output)
+// fields are transformed by one multi-transform pass with a uniform element stride.
+// The vector-ALU forms read the ring's planes straight into the butterflies of the
+// first z stage; the matrix-core stages take theirs from a staged tile.  The update
+// takes the points kz and -kz of a pencil together: they share |[k]| and so the
+// FP64 coefficients.  The results go out through the LDS in whole pencil runs:
+// stores straight from the last stage's butterflies measured 1.0 -> 1.5 ms (64 boxes
+// of 96^3 padded, FP32).  Issue-bound (65 % of the time is VALU busy); with the
+// loads and pairs as here 1.03 -> 0.90 ms, FP64 2.32 -> 2.08 ms, 8 boxes of 176^3 in
+// FP64 2.44 -> 2.03 ms; the pairs in the matrix-core forms 0.220 -> 0.211 ms on 8
+// boxes of 96^3.
+template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
+PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
+  constexpr bool VALU = std::is_same<Eng, FftValu>::value;
   const ZItem it = uniform_load(a.items + item);
   const BoxD bx = uniform_load(a.t.box + it.box);
   const int Pz = bx.P[2], H = bx.H, nq = bx.P[1] * H, q0 = it.q0;
@@ -957,11 +900,17 @@ PSATD_HD void body_z_direct(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
     pos[i] = gpos[i];
   }
   const int np = (nq - q0) < PB ? (nq - q0) : PB;
-  bar();
-  first_stage_dispatch<-1, MAXR, W, W>(plz, lds, twz, tid, nt,
-                                       ZLoad<T, PB>{spec_at(a.spec, bx, a.sbias, 0) + q0, bx, np});
-  bar();
-  fft_dif_inner<-1, MAXR>(lds, W, 1, W, plz, twz, tid, nt, bar);
+  const cx<T>* src = spec_at(a.spec, bx, a.sbias, 0) + q0;
+  if constexpr (VALU) {
+    bar();
+    first_stage_dispatch<-1, MAXR, W, W>(plz, lds, twz, tid, nt, ZLoad<T, PB>{src, bx, np});
+    bar();
+    fft_dif_inner<-1, MAXR>(lds, W, 1, W, plz, twz, tid, nt, bar);
+  } else {
+    stage_tile<T, PB>(bx, src, a.sbias, q0, np, lds, tid, nt);
+    bar();
+    eng.template dif<-1, MAXR>(lds, W, 1, W, plz, twz, tid, nt, bar);
+  }
 
   const double* kxt = a.t.kmod + bx.kx;
   const double* kyt = a.t.kmod + bx.ky;
@@ -992,7 +941,7 @@ PSATD_HD void body_z_direct(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
     }
   }
   bar();
-  fft_dit<+1, MAXR>(lds, 6 * PB, 1, W, plz, twz, tid, nt, bar);
+  eng.template dit<+1, MAXR>(lds, 6 * PB, 1, W, plz, twz, tid, nt, bar);
   store_results<T, PB>(bx, a.spec + q0, a.sbias, q0, np, lds, tid, nt);
 }
 

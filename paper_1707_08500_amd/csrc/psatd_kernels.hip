@@ -96,10 +96,7 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 1) void k_z_update(UpdArgs
                                                                           int remap) {
   cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
   for (int it = first_item(remap); it < nitems; it += gridDim.x) {
-    if constexpr (SPL == 0)
-      body_z_direct<T, PB, INC, MAXR>(a, it, fresh_tid(), NT, lds, BlockBarrier{});
-    else
-      body_z_update<T, PB, INC, MAXR>(a, it, fresh_tid(), NT, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
+    body_z_update<T, PB, INC, MAXR>(a, it, fresh_tid(), NT, lds, BlockBarrier{}, typename EngOf<SPL>::type{});
     __syncthreads();
   }
 }
