@@ -784,6 +784,25 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
     const bool f64 = is_f64(h.prec);
     l.narrow = kMaxDynLds / l.lds >= (f64 ? 2 : 3) && l.nu > (f64 ? 256 : 512);
   };
+  // FP64 tiles of which one fills the LDS: with J's transform in registers two
+  // 256-thread tiles share a compute unit, where they fit and every pair +-kz has its
+  // thread (8 pencils to padded z 103, 4 to 202).  Measured, nine fields in the LDS ->
+  // held: 64 boxes of 96^3 padded 2.07 -> 1.71 ms, 8 of 176^3 2.02 -> 1.57, 16 of
+  // 96 96 80 0.51 -> 0.42, 28 of 96 96 144 1.75 -> 1.46, 32 of 96 96 192 2.72 -> 2.16;
+  // one box of 264 tiles 34 -> 29 us, 588 54 -> 49.  One round of 512-thread tiles
+  // (256) keeps its nine fields.  For 112- and 128-long z, where held tiles have 6 or 4
+  // pencils, the full tiles of 8 are faster (0.76 against 0.85 ms, 0.97 against
+  // 1.13).  FP32 has no registers left for it: 0.89 -> 1.10 ms.
+  auto hold_j = [&](const std::vector<char>& in, ZLaunch& l) {
+    if (!is_f64(h.prec) || h.ntu != 512 || l.narrow || (l.PB != 4 && l.PB != 8)) return;
+    int Pz = 0;
+    for (int s = 0; s < h.nsub; ++s)
+      if (in[s]) Pz = std::max(Pz, (int)h.box[s].P[2]);
+    const int64_t lds = held_tile_lds(Pz, l.PB, (int)real_size(h.prec));
+    if (2 * lds > kMaxDynLds || (Pz / 2 + 1) * l.PB > kHeldPairs * kThreadsHeld || l.nu <= 256) return;
+    l.held = 1;
+    l.lds = (int32_t)lds;
+  };
   for (const Batch& bt : h.batches) {
     w.xy.emplace_back();
     w.z.emplace_back();
@@ -808,12 +827,14 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
         for (int s = 0; s < h.nsub; ++s) in[s] = U[s + 1] > U[s];
         ZLaunch l{k.PB, k.lds};
         add_tiles(in, l);
+        hold_j(in, l);
         w.z.back().push_back(l);
       }
     } else {
       for (int s = 0; s < h.nsub; ++s) in[s] = s >= bt.b0 && s < bt.b1;
       ZLaunch l{h.PB, h.ldsU};
       add_tiles(in, l);
+      hold_j(in, l);
       w.z.back().push_back(l);
     }
   }

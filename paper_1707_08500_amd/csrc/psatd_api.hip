@@ -848,6 +848,7 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
       if (value != 512 && value != 1024) return fail(p, PSATD_E_INVALID, "z threads must be 512 or 1024");
       p->h.ntu = value;
       d.ntu = value;
+      relist = true;
       break;
     default: {
       if (value < 0) return fail(p, PSATD_E_INVALID, "grid size must be >= 0");

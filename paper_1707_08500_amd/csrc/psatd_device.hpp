@@ -101,6 +101,7 @@ struct XyLaunch {
 struct ZLaunch {
   int32_t PB, lds, u0, nu;
   int32_t narrow;  // 1: tiles of 256 threads instead of 512
+  int32_t held;    // 1: tiles that hold J's transform in registers (body_z_held)
 };
 
 // A batch of boxes [b0, b1) for the FFT/update passes and the spectral offset
@@ -651,6 +652,9 @@ PSATD_HD void sincos_cw(double h, double* sh, double* ch) {
   *ch = q == 0 ? c : (q == 1 ? -s : (q == 2 ? -c : s));
 }
 
+PSATD_HD float madd(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+PSATD_HD double madd(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // The FP64 coefficients of Eqs. PSATD_1 / PSATD_2 at |[k]|^2 = k2 (Sec. 3.1):
 // th = c |[k]| dt, C - 1 = -2 sin^2(th/2) (no cancellation), S/(ck),
 // X1 = (1 - C)/|[k]|^2 = 2 sin^2(th/2)/|[k]|^2, X2 = (S/(ck) - dt)/|[k]|^2 (by
@@ -661,6 +665,7 @@ struct Coef64 {
 };
 
 PSATD_HD Coef64 psatd_coef(double k2, double c, double rc, double dt) {
+#pragma clang fp contract(off)
   Coef64 r;
   const double c2 = c * c;
   if (k2 == 0.0) {
@@ -683,7 +688,8 @@ PSATD_HD Coef64 psatd_coef(double k2, double c, double rc, double dt) {
   const double t2 = 4.0 * h * h;
   if (t2 < 1e-2) {
     r.x2 = -c2 * dt * dt * dt *
-           (1.0 / 6.0 - t2 * (1.0 / 120.0 - t2 * (1.0 / 5040.0 - t2 * (1.0 / 362880.0 - t2 / 39916800.0))));
+           fma(-t2, fma(-t2, fma(-t2, fma(-t2, 1.0 / 39916800.0, 1.0 / 362880.0), 1.0 / 5040.0), 1.0 / 120.0),
+               1.0 / 6.0);
   } else {
     r.x2 = (r.sck - dt) * rk2;
   }
@@ -709,7 +715,8 @@ struct UpdCoef {
 
 template <typename T, bool INC>
 PSATD_HD UpdCoef<T> update_coef(double kx, double ky, double kz, double c, double rc, double dt) {
-  const Coef64 cf = psatd_coef(kx * kx + ky * ky + kz * kz, c, rc, dt);
+#pragma clang fp contract(off)
+  const Coef64 cf = psatd_coef(madd(kz, kz, madd(ky, ky, kx * kx)), c, rc, dt);
   UpdCoef<T> u;
   u.C = (T)(INC ? cf.cm1 : 1.0 + cf.cm1);
   u.S = (T)cf.sck;
@@ -729,24 +736,29 @@ PSATD_HD UpdCoef<T> update_coef(double kx, double ky, double kz, double c, doubl
 // Im J) with SG = -1:
 //   E' = C E - SG c^2 (S/ck) [k]xB - (S/ck) J + [k] (X1 [k].E + X2 [k].J)
 //   B' = C B - SG [k] x ((S/ck) E - (X1/c^2) J)
+//
+// Its roundings are written out (fma, contraction off), as are those of the
+// coefficients: kernels of different shape that share this text then agree in every
+// bit, whatever products the compiler finds in common around it.
 template <int SG, typename T>
 PSATD_HD void update_half(T* e, T* b, const T* j, const UpdCoef<T>& u) {
+#pragma clang fp contract(off)
   const T k[3] = {u.kx, u.ky, u.kz};
   const T ak[3] = {SG * u.a1 * u.kx, SG * u.a1 * u.ky, SG * u.a1 * u.kz};
-  const T kE = k[0] * e[0] + k[1] * e[1] + k[2] * e[2];
-  const T kJ = k[0] * j[0] + k[1] * j[1] + k[2] * j[2];
-  const T s = u.X1 * kE + u.X2 * kJ;
+  const T kE = madd(k[2], e[2], madd(k[1], e[1], k[0] * e[0]));
+  const T kJ = madd(k[2], j[2], madd(k[1], j[1], k[0] * j[0]));
+  const T s = madd(u.X2, kJ, u.X1 * kE);
   T f[3], en[3];
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     const int p = (a + 1) % 3, q = (a + 2) % 3;
-    f[a] = SG * (u.S * e[a] - u.x1c * j[a]);
-    en[a] = u.C * e[a] - u.S * j[a] - ak[p] * b[q] + ak[q] * b[p] + k[a] * s;
+    f[a] = SG * madd(u.S, e[a], -(u.x1c * j[a]));
+    en[a] = madd(k[a], s, madd(ak[q], b[p], madd(-ak[p], b[q], madd(-u.S, j[a], u.C * e[a]))));
   }
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
     const int p = (a + 1) % 3, q = (a + 2) % 3;
-    b[a] = u.C * b[a] - k[p] * f[q] + k[q] * f[p];
+    b[a] = madd(k[q], f[p], madd(-k[p], f[q], u.C * b[a]));
     e[a] = en[a];
   }
 }
@@ -766,14 +778,13 @@ struct UpdArgs {
   UpdConst k;
 };
 
-// Writes the 6 results of a tile (LDS [z][f PB + p], rows of 9 PB) at the
+// Writes the 6 results of a tile (LDS [z][f PB + p], rows of W) at the
 // interior z-planes only: the inverse pass reads nothing else (the guard planes
 // of E and B are rewritten by the exchange).  A full tile whose pencil runs
 // start at even offsets moves two neighbouring pencils per access.
-template <typename T, int PB>
+template <typename T, int PB, int W>
 PSATD_HD void store_results(const BoxD& bx, cx<T>* dst, int64_t sbias, int q0, int np, const cx<T>* lds, int tid,
                             int nt) {
-  constexpr int W = 9 * PB;
   const cx<T>* res = lds + bx.g[2] * W;
   if (PB % 2 == 0 && np == PB && ((bx.pp | bx.sv | (bx.sb - sbias + q0) | (bx.xb - sbias + q0) | bx.xv) & 1) == 0) {
     copy_grid3<4, Pair<cx<T>>>(6, bx.n[2], PB / 2, tid, nt,
@@ -942,7 +953,100 @@ PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T
   }
   bar();
   eng.template dit<+1, MAXR>(lds, 6 * PB, 1, W, plz, twz, tid, nt, bar);
-  store_results<T, PB>(bx, a.spec + q0, a.sbias, q0, np, lds, tid, nt);
+  store_results<T, PB, W>(bx, a.spec + q0, a.sbias, q0, np, lds, tid, nt);
+}
+
+constexpr int kThreadsHeld = 256;
+constexpr int kHeldPairs = 2;  // pairs +-kz per thread
+
+// LDS of a held tile of PB pencils of padded z length Pz.
+PSATD_HD int64_t held_tile_lds(int Pz, int PB, int real_bytes) {
+  return (int64_t)Pz * ((6 * PB + 1) * 2 * real_bytes + 4);
+}
+
+// The same pass with 6 fields of a tile in the LDS: J is transformed first and its
+// points are held in registers, each by the thread that updates it, while E and B
+// take J's place.  Two tiles then share a compute unit where the nine fields of one
+// filled its LDS, so that one tile's loads and barriers overlap the other's
+// transforms: 2.07 -> 1.71 ms on 64 boxes of 96^3 padded in FP64, 2.02 -> 1.57 ms on
+// 8 of 176^3.  Still issue-bound; 215 VGPRs.
+template <typename T, int PB, bool INC, int MAXR, class Bar>
+PSATD_HD void body_z_held(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar) {
+  const ZItem it = uniform_load(a.items + item);
+  const BoxD bx = uniform_load(a.t.box + it.box);
+  const int Pz = bx.P[2], H = bx.H, nq = bx.P[1] * H, q0 = it.q0;
+  const PlanRef plz = plan_ref(a.t.plans + bx.planz);
+  constexpr int W = 6 * PB, WJ = 3 * PB;
+  cx<T>* twz = lds + Pz * W;
+  int32_t* pos = reinterpret_cast<int32_t*>(twz + Pz);
+  const cx<T>* gtz = a.t.tw + plz->tw;
+  const int32_t* gpos = a.t.pos + plz->pos;
+  for (int i = tid; i < Pz; i += nt) {
+    twz[i] = gtz[i];
+    pos[i] = gpos[i];
+  }
+  const int np = (nq - q0) < PB ? (nq - q0) : PB;
+  const cx<T>* src = spec_at(a.spec, bx, a.sbias, 0) + q0;
+  bar();
+  first_stage_dispatch<-1, MAXR, WJ, WJ>(plz, lds, twz, tid, nt, ZLoad<T, PB>{src + 6 * bx.sv, bx, np});
+  bar();
+  fft_dif_inner<-1, MAXR>(lds, WJ, 1, WJ, plz, twz, tid, nt, bar);
+  const int n = (Pz / 2 + 1) * PB;
+  cx<T> jh[kHeldPairs][2][3];
+#pragma unroll
+  for (int h = 0; h < kHeldPairs; ++h) {
+    const int i = tid + h * nt;
+    if (i < n) {
+      const int kz = (int)((uint32_t)i / (uint32_t)PB);
+      const int p = i - kz * PB;
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        const cx<T>* row = lds + pos[s && kz ? Pz - kz : kz] * WJ + p;
+#pragma unroll
+        for (int f = 0; f < 3; ++f) jh[h][s][f] = row[f * PB];
+      }
+    }
+  }
+  bar();
+  first_stage_dispatch<-1, MAXR, W, W>(plz, lds, twz, tid, nt, ZLoad<T, PB>{src, bx, np});
+  bar();
+  fft_dif_inner<-1, MAXR>(lds, W, 1, W, plz, twz, tid, nt, bar);
+
+  const double* kxt = a.t.kmod + bx.kx;
+  const double* kyt = a.t.kmod + bx.ky;
+  const double* kzt = a.t.kmod + bx.kz;
+  const FastDiv dH = make_fastdiv((uint32_t)H);
+  const double rc = 1.0 / a.k.c;
+#pragma unroll
+  for (int h = 0; h < kHeldPairs; ++h) {
+    const int i = tid + h * nt;
+    const int kz = (int)((uint32_t)i / (uint32_t)PB);
+    const int p = i - kz * PB;
+    if (i < n && p < np) {
+      const int q = q0 + p;
+      const int ky = (int)fdiv((uint32_t)q, dH);
+      UpdCoef<T> u = update_coef<T, INC>(kxt[q - ky * H], kyt[ky], kzt[kz], a.k.c, rc, a.k.dt);
+#pragma unroll
+      for (int s = 0; s < 2; ++s) {
+        if (s && (kz == 0 || 2 * kz == Pz)) continue;
+        cx<T>* row = lds + pos[s ? Pz - kz : kz] * W + p;
+        T vr[9], vi[9];
+#pragma unroll
+        for (int f = 0; f < 9; ++f) {
+          const cx<T> v = f < 6 ? row[f * PB] : jh[h][s][f - 6];
+          vr[f] = v.x;
+          vi[f] = v.y;
+        }
+        update_apply<T>(vr, vi, u);
+#pragma unroll
+        for (int f = 0; f < 6; ++f) row[f * PB] = cx<T>{vr[f], vi[f]};
+        u.kz = -u.kz;
+      }
+    }
+  }
+  bar();
+  fft_dit<+1, MAXR>(lds, 6 * PB, 1, W, plz, twz, tid, nt, bar);
+  store_results<T, PB, W>(bx, a.spec + q0, a.sbias, q0, np, lds, tid, nt);
 }
 
 // ------------------------------------------------------- heat equation

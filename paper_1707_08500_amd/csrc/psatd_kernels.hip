@@ -101,6 +101,16 @@ __global__ __launch_bounds__(NT, sizeof(T) == 4 ? 4 : 1) void k_z_update(UpdArgs
   }
 }
 
+// J's transform in registers (FP64).
+template <typename T, int PB, bool INC, int MAXR>
+__global__ __launch_bounds__(kThreadsHeld) void k_z_held(UpdArgs<T> a, int nitems, int remap) {
+  cx<T>* lds = reinterpret_cast<cx<T>*>(psatd_lds);
+  for (int it = first_item(remap); it < nitems; it += gridDim.x) {
+    body_z_held<T, PB, INC, MAXR>(a, it, fresh_tid(), kThreadsHeld, lds, BlockBarrier{});
+    __syncthreads();
+  }
+}
+
 // Register z pass (FP32 forms, padded z length N).  The VGPR budget keeps
 // at least MINW waves per SIMD resident.
 template <int N, int L, int W, int MINW>
@@ -243,6 +253,10 @@ hipError_t prepare_t(int ldsF, int ldsI, int ldsU, int ldsX, int ldsY) {
       if ((e = set_lds((const void*)k_inv_half<T, I, MAXR>, kMaxDynLds)) != hipSuccess) return e;
     }
     if ((e = set_lds((const void*)k_z_update<T, 256, 8, I, MAXR, SPL>, ldsU)) != hipSuccess) return e;
+    if constexpr (sizeof(T) == 8) {
+      for (const void* f : {(const void*)k_z_held<T, 4, I, MAXR>, (const void*)k_z_held<T, 8, I, MAXR>})
+        if ((e = set_lds(f, kMaxDynLds / 2)) != hipSuccess) return e;
+    }
     if ((e = set_lds((const void*)k_z_update<T, 256, 10, I, MAXR, SPL>, ldsU)) != hipSuccess) return e;
   }
   const void* heat[] = {(const void*)k_z_heat<T, 4, I, MAXR, SPL>, (const void*)k_z_heat<T, 8, I, MAXR, SPL>,
@@ -328,9 +342,19 @@ static hipError_t upd_launch(const DevPlan& p, const ZLaunch& l, int g, const Up
   return hipGetLastError();
 }
 
+template <typename T, int PB, int MAXR>
+static hipError_t held_launch(const DevPlan& p, const ZLaunch& l, int g, const UpdArgs<T>& a, hipStream_t st) {
+  hipLaunchKernelGGL((k_z_held<T, PB, IncOf<T>::value, MAXR>), dim3(g), dim3(kThreadsHeld), l.lds, st, a, l.nu, p.xcd);
+  return hipGetLastError();
+}
+
 template <typename T, int MAXR, int SPL>
 static hipError_t upd_shape(const DevPlan& p, const ZLaunch& l, int g, const UpdArgs<T>& a, hipStream_t st) {
   if constexpr (SPL == 0) {
+    if constexpr (sizeof(T) == 8) {
+      if (l.held && l.PB == 4) return held_launch<T, 4, MAXR>(p, l, g, a, st);
+      if (l.held) return held_launch<T, 8, MAXR>(p, l, g, a, st);
+    }
     if (l.narrow && p.ntu == 512 && l.PB == 8) return upd_launch<T, 256, 8, MAXR, SPL>(p, l, g, a, st);
     if (l.narrow && p.ntu == 512 && l.PB == 10) return upd_launch<T, 256, 10, MAXR, SPL>(p, l, g, a, st);
   }

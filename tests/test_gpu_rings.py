@@ -112,3 +112,26 @@ def test_narrow_z_tiles(precision):
     check(case, eE, eB, precision, TOL[precision])
     first = state(case)
     assert torch.equal(first, rerun(case, E, B, lambda c: None, 2, z_threads=1024))
+
+
+# (N, boxes, guard): 8 pencils from the shortest z whose nine-field tiles do not share a
+# compute unit to the longest whose held tiles do, odd lengths, two boxes that share
+# planes; 4 pencils to the same end.  All with a ragged last tile but the boxes.
+HELD = [((70, 75, 70), 1, 0), ((70, 75, 99), 1, 0), ((70, 75, 100), 1, 0), ((64, 64, 160), 2, 8),
+        ((48, 45, 147), 1, 0), ((48, 45, 200), 1, 0)]
+
+
+@pytest.mark.parametrize("N,boxes,guard", HELD)
+@pytest.mark.parametrize("maxr", [16, 8])
+def test_held_z_tiles(N, boxes, guard, maxr):
+    """FP64 tiles with J's transform in registers: against the oracle, and against the
+    nine-field tiles of 1024 threads within twice its bar (each is within one)."""
+    say(f"held z tiles, {N}, {boxes} boxes, radix {maxr}")
+    lo, n, g = synth.uniform_decomposition(N, (1, 1, boxes), guard)
+    E, B, J = random_fields(N, 61, p=16)
+    case, eE, eB, _ = run_both(N, lo, n, g, 16, 0.5, 1.0, "f64", "replicated", (E, B, J), 2)
+    check(case, eE, eB, "f64", TOL["f64"])
+    first = state(case)
+    for nt in (512, 1024):
+        other = rerun(case, E, B, lambda c: None, 2, z_threads=nt, max_radix_z=maxr)
+        assert float((other - first).abs().max()) <= 2 * TOL["f64"] * float(first.abs().max())
