@@ -115,7 +115,8 @@ typedef enum {
                                  many padded planes fit a compute unit's LDS): one launch per such class,
                                  each with the fewest threads that keep 16 waves per compute unit and the
                                  LDS of its own largest plane */
-  PSATD_TUNE_Z_THREADS = 9,   /* threads per work-group of the z-update: 512 or 1024 */
+  PSATD_TUNE_Z_THREADS = 9,   /* threads per work-group of the z-update: 512 (the
+                                 default: 256 where smaller tiles measured faster) or 1024 */
   PSATD_TUNE_SPLIT_XY = 10,   /* 1: x rows and y columns in separate passes through the workspace
                                  (automatic when a padded plane exceeds the LDS; needs no batching) */
   PSATD_TUNE_FUSE_EB = 11,    /* 1: the inverse pass writes each new E, B value into every guard copy

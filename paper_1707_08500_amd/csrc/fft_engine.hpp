@@ -227,18 +227,6 @@ PSATD_HD int plan_pos(const FftPlanD* pl, int k) {
   return pos;
 }
 
-// Inverse of plan_pos: the index held at position p.
-PSATD_HD int plan_index(const FftPlanD* pl, int p) {
-  int k = 0;
-  uint32_t rem = (uint32_t)p;
-  for (int s = 0; s < pl->nstages; ++s) {
-    const uint32_t t = fdiv(rem, pl->sdiv[s]);
-    rem -= t * (uint32_t)pl->stride[s];
-    k += (int)t * pl->prod[s];
-  }
-  return k;
-}
-
 // twiddle W_N^e for direction DIR from the forward table
 template <int DIR, typename T>
 PSATD_HD cx<T> twid(const cx<T>* tw, int e) {

@@ -471,7 +471,7 @@ struct FwdArgs {
   const PlaneRec* planes;  // item = field * planes + plane
   FastDiv np;
   const T* in[9];
-  cx<T>* spec;             // spectral workspace (box-major, see spec_at)
+  cx<T>* spec;             // spectral workspace (see spec_at)
   int64_t sbias;           // spectral offset of the first box held by spec
   // Fields f < npull read their guard cells from the owners (pull pieces of
   // the plane's record) instead of the box's own, possibly stale, guard
