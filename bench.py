@@ -231,7 +231,9 @@ def algorithmic_bytes(plan, dec_lo, dec_n, dec_g, sb):
     interior z-planes only (all the inverse pass reads).  The FP32 forms add
     increments, so their inverse pass reads and writes the interior cells.  With
     the fused E,B exchange the inverse pass also writes every guard copy (no
-    read), and the exchange phase moves nothing."""
+    read), and the exchange phase moves nothing.  Counted per padded plane of every
+    box and for all nine fields: plans whose boxes share planes, and the later steps
+    of a run, which keep J's transform, move less than this."""
     fused = bool(plan.tuning()["fuse_eb"])
     inc = plan.precision != "f64"
     out = dict(exchange_J=0, fft_xy_fwd=0, z_update=0, fft_xy_inv=0, exchange_EB=0)
