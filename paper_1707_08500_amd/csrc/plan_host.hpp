@@ -847,6 +847,18 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
   h.lists = std::move(w);
 }
 
+// Bytes of the spectral workspace that every layout has room for: one batch's half
+// spectra of 9 fields, each box's planes its own and back to back.
+inline int64_t workspace_bytes(const HostTables& h) {
+  return 9 * h.batch_slab * (int64_t)(2 * real_size(h.prec));
+}
+
+// Bytes that the fastest layout takes: an unbatched plan's shared planes at pitches of
+// their own, which may be more.  A batched plan runs in one batch's planes back to back.
+inline int64_t roomy_workspace_bytes(const HostTables& h) {
+  return h.batches.size() == 1 ? h.lists.elems * (int64_t)(2 * real_size(h.prec)) : workspace_bytes(h);
+}
+
 // Deposited currents: every box interior cut, along each axis, where the set of
 // padded copies changes; the regions with more than one copy (boxes ascending,
 // then z, y, x positions ascending).

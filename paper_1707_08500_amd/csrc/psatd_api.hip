@@ -114,9 +114,7 @@ std::vector<unsigned char> device_twiddles(const HostTables& h) {
   return out;
 }
 
-int64_t workspace_need(const psatd_plan_s* p) {
-  return 9 * p->h.batch_slab * (int64_t)(2 * real_size(p->h.prec));
-}
+int64_t workspace_need(const psatd_plan_s* p) { return workspace_bytes(p->h); }
 
 void drop_graphs(psatd_plan_t p) {
   for (auto& g : p->graphs) {
@@ -129,12 +127,11 @@ void drop_graphs(psatd_plan_t p) {
 // The boxes for a workspace of `bytes`: with the pitched planes where they fit
 // (they may take a little more than workspace_need), else back to back.
 const BoxD* boxes_in(const psatd_plan_s* p, int64_t bytes) {
-  const int64_t pitched = p->h.lists.elems * (int64_t)(2 * real_size(p->h.prec));
-  return p->h.batches.size() == 1 && bytes >= pitched ? p->dp.box : p->tight;
+  return bytes >= roomy_workspace_bytes(p->h) && p->h.batches.size() == 1 ? p->dp.box : p->tight;
 }
 
-// The plan's own workspace is allocated for the pitched planes, or with
-// workspace_need bytes where that is all there is.
+// The plan's own workspace is allocated for the pitched planes of an unbatched
+// plan, or with workspace_need bytes where that is all there is.
 psatd_status ensure_workspace(psatd_plan_t p) {
   if (p->ws && p->ws_bytes >= workspace_need(p)) return PSATD_OK;
   if (p->ws && !p->ws_owned)
@@ -145,7 +142,7 @@ psatd_status ensure_workspace(psatd_plan_t p) {
     p->ws = nullptr;
   }
   int64_t need = std::max<int64_t>(workspace_need(p), 256);
-  const int64_t pitched = p->h.lists.elems * (int64_t)(2 * real_size(p->h.prec));
+  const int64_t pitched = roomy_workspace_bytes(p->h);
   if (pitched > need && hipMalloc(&p->ws, (size_t)pitched) == hipSuccess) {
     need = pitched;
   } else {
