@@ -72,7 +72,6 @@ struct psatd_plan_s {
   void* blob = nullptr;  // device tables
   void* lists = nullptr;  // device work lists (they depend on the knobs)
   const BoxD* tight = nullptr;  // in lists: the boxes with their spectral planes back to back
-  size_t lists_bytes = 0;
   int32_t tune[PSATD_NTUNE] = {0, 1, 0, 0, 0, 0, 0, 16, 256, 512, 0, 1, 0, 0};
   void* ws = nullptr;
   int64_t ws_bytes = 0;
@@ -156,12 +155,17 @@ psatd_status ensure_workspace(psatd_plan_t p) {
 
 // Builds the work lists for the plan's current knobs and uploads them.  Boxes
 // share the planes of their columns in an unbatched plan, except under the
-// register z pass, which addresses each box's own 9 fields.
+// register z pass, which addresses each box's own 9 fields.  Where that fails,
+// the lists of before stay, on the host and on the device.
 psatd_status upload_lists(psatd_plan_t p) {
   HostTables& h = p->h;
   DevPlan& d = p->dp;
   std::vector<unsigned char> hb;
   size_t off[6];
+  WorkLists was;
+  std::swap(was, h.lists);
+  void* fresh = nullptr;
+  psatd_status st = PSATD_OK;
   try {
     const bool one = h.batches.size() == 1;
     build_lists(h, one && !d.zreg, d.ntxy == 0 && !h.split && one, d.zcl && one);
@@ -180,17 +184,23 @@ psatd_status upload_lists(psatd_plan_t p) {
     put(4, w.tiles.data(), w.tiles.size() * sizeof(ZItem));
     put(5, w.tight.data(), w.tight.size() * sizeof(BoxD));
   } catch (...) {
-    return fail(p, PSATD_E_NOMEM, "host allocation failed");
+    st = fail(p, PSATD_E_NOMEM, "host allocation failed");
   }
-  if (hb.size() > p->lists_bytes) {
-    void* fresh = nullptr;
-    HIPCHK(p, hipMalloc(&fresh, hb.size()));
-    if (p->lists) (void)hipFree(p->lists);
-    p->lists = fresh;
-    p->lists_bytes = hb.size();
+  if (st == PSATD_OK) {
+    st = [&]() -> psatd_status {
+      HIPCHK(p, hipMalloc(&fresh, hb.size()));
+      HIPCHK(p, hipMemcpy(fresh, hb.data(), hb.size(), hipMemcpyHostToDevice));
+      return PSATD_OK;
+    }();
   }
-  HIPCHK(p, hipMemcpy(p->lists, hb.data(), hb.size(), hipMemcpyHostToDevice));
-  unsigned char* base = reinterpret_cast<unsigned char*>(p->lists);
+  if (st != PSATD_OK) {
+    if (fresh) (void)hipFree(fresh);
+    std::swap(was, h.lists);
+    return st;
+  }
+  if (p->lists) (void)hipFree(p->lists);
+  p->lists = fresh;
+  unsigned char* base = reinterpret_cast<unsigned char*>(fresh);
   d.box = reinterpret_cast<const BoxD*>(base + off[0]);
   d.pullp = reinterpret_cast<const PullPiece*>(base + off[1]);
   d.fwd = reinterpret_cast<const PlaneRec*>(base + off[2]);
@@ -198,6 +208,42 @@ psatd_status upload_lists(psatd_plan_t p) {
   d.tiles = reinterpret_cast<const ZItem*>(base + off[4]);
   p->tight = reinterpret_cast<const BoxD*>(base + off[5]);
   return PSATD_OK;
+}
+
+// What the knobs set, apart from the FFT schedules: kept over a psatd_set_tuning
+// that may fail after it has changed some of it.
+struct Knobs {
+  DevPlan dp;
+  int32_t tune[PSATD_NTUNE];
+  std::vector<Batch> batches;
+  int64_t batch_slab;
+  int32_t batch_boxes;
+  std::vector<int32_t> itemsU;
+  int PB, ldsU, ntxy, ntu;
+  bool split, fuse_eb;
+};
+
+Knobs save_knobs(const psatd_plan_s* p) {
+  const HostTables& h = p->h;
+  Knobs k{p->dp, {}, h.batches, h.batch_slab, h.batch_boxes, h.itemsU, h.PB, h.ldsU, h.ntxy, h.ntu, h.split, h.fuse_eb};
+  std::memcpy(k.tune, p->tune, sizeof(k.tune));
+  return k;
+}
+
+void restore_knobs(psatd_plan_t p, Knobs& k) {
+  HostTables& h = p->h;
+  p->dp = k.dp;
+  std::memcpy(p->tune, k.tune, sizeof(k.tune));
+  h.batches.swap(k.batches);
+  h.batch_slab = k.batch_slab;
+  h.batch_boxes = k.batch_boxes;
+  h.itemsU.swap(k.itemsU);
+  h.PB = k.PB;
+  h.ldsU = k.ldsU;
+  h.ntxy = k.ntxy;
+  h.ntu = k.ntu;
+  h.split = k.split;
+  h.fuse_eb = k.fuse_eb;
 }
 
 bool aligned16(const void* q) { return ((uintptr_t)q & 15u) == 0; }
@@ -711,11 +757,11 @@ psatd_status psatd_modified_k(psatd_plan_t p, int32_t s, int32_t axis, double* o
   return PSATD_OK;
 }
 
-psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
-  if (!p) return fail(nullptr, PSATD_E_INVALID, "null plan");
-  if (key < 0 || key >= PSATD_NTUNE) return fail(p, PSATD_E_INVALID, "unknown tuning key");
+namespace {
+
+// Sets one knob.  relist: the work lists follow it.
+psatd_status set_knob(psatd_plan_t p, int32_t key, int32_t value, bool& relist) {
   DevPlan& d = p->dp;
-  bool relist = false;  // the work lists follow the knob
   switch (key) {
     case PSATD_TUNE_Z_PENCILS: {
       if (value == 0) {  // one launch per class of tile size
@@ -821,10 +867,10 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
         HIPCHK(p, hipMemcpy(const_cast<void*>(d.tw), t.data(), t.size(), hipMemcpyHostToDevice));
       }
       HIPCHK(p, hipMemcpy(const_cast<int32_t*>(d.pos), trial.pos.data(), trial.pos.size() * 4, hipMemcpyHostToDevice));
-      p->h.plans = trial.plans;
-      p->h.twr = trial.twr;
-      p->h.twi = trial.twi;
-      p->h.pos = trial.pos;
+      p->h.plans.swap(trial.plans);
+      p->h.twr.swap(trial.twr);
+      p->h.twi.swap(trial.twi);
+      p->h.pos.swap(trial.pos);
       p->h.maxr = trial.maxr;
       p->h.maxrz = trial.maxrz;
       d.maxr = trial.maxr;
@@ -855,12 +901,35 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
     }
   }
   p->tune[key] = value;
-  drop_graphs(p);
-  if (relist) {
-    HIPCHK(p, hipStreamSynchronize(p->stream));
-    return upload_lists(p);
-  }
   return PSATD_OK;
+}
+
+}  // namespace
+
+psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
+  if (!p) return fail(nullptr, PSATD_E_INVALID, "null plan");
+  if (key < 0 || key >= PSATD_NTUNE) return fail(p, PSATD_E_INVALID, "unknown tuning key");
+  try {
+    Knobs was = save_knobs(p);
+    psatd_status st = PSATD_E_NOMEM;
+    bool relist = false;
+    try {
+      st = set_knob(p, key, value, relist);
+      if (st == PSATD_OK && relist) {
+        const hipError_t e = hipStreamSynchronize(p->stream);
+        st = e == hipSuccess ? upload_lists(p)
+                             : fail(p, PSATD_E_HIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(e));
+      }
+    } catch (...) {
+      restore_knobs(p, was);
+      throw;
+    }
+    if (st != PSATD_OK) restore_knobs(p, was);
+    else drop_graphs(p);
+    return st;
+  } catch (...) {
+    return fail(p, PSATD_E_NOMEM, "host allocation failed");
+  }
 }
 
 psatd_status psatd_get_tuning(psatd_plan_t p, int32_t key, int32_t* value) {

@@ -282,10 +282,46 @@ void check_workspace(int prec) {
   std::printf("workspace ok\n");
 }
 
+// The knobs that remake the work lists, each with a value other than the default.
+struct Knob {
+  int32_t key, value;
+};
+const Knob kListKnobs[] = {{PSATD_TUNE_Z_PENCILS, 4}, {PSATD_TUNE_SPLIT_XY, 1}, {PSATD_TUNE_BATCH_BOXES, 3},
+                           {PSATD_TUNE_FUSE_EB, 1},   {PSATD_TUNE_XY_THREADS, 1024}, {PSATD_TUNE_Z_THREADS, 1024}};
+
+// A knob whose lists cannot be allocated or copied to the device leaves the plan as it was.
+void check_failures(int prec) {
+  for (const Knob& k : kListKnobs)
+    for (int copy = 0; copy < 2; ++copy) {
+      psatd_plan_t p = cubes(48, 2, 8, prec);
+      // lists shorter than any that the knobs make, so that stale ones show
+      CHECK(p && psatd_set_tuning(p, PSATD_TUNE_Z_PENCILS, 8) == PSATD_OK, "failures: plan");
+      const std::string before = step(p);
+      const std::vector<int32_t> was = knobs(p);
+      CHECK(ok(before), "failures: %s", before.c_str());
+      (copy ? fake::copies_left : fake::mallocs_left) = 0;
+      const psatd_status st = psatd_set_tuning(p, k.key, k.value);
+      const bool tried = (copy ? fake::copies_left : fake::mallocs_left) < 0;
+      fake::mallocs_left = fake::copies_left = -1;
+      CHECK(tried == (st != PSATD_OK), "knob %d: a refused upload is reported", k.key);
+      if (tried) {
+        CHECK(st == (copy ? PSATD_E_HIP : PSATD_E_NOMEM), "knob %d: status %d", k.key, st);
+        CHECK(knobs(p) == was, "knob %d: a failed call keeps the knobs", k.key);
+        const std::string after = step(p);
+        CHECK(after == before, "knob %d: after a failed call: %s", k.key, after.c_str());
+      }
+      CHECK(psatd_set_tuning(p, k.key, k.value) == PSATD_OK && ok(step(p)), "knob %d: %s", k.key, step(p).c_str());
+      psatd_destroy(p);
+    }
+  std::printf("failures ok\n");
+}
+
 }  // namespace
 
 int main() {
   check_workspace(PSATD_F32_VALU);
   check_workspace(PSATD_F64);
+  check_failures(PSATD_F32_VALU);
+  check_failures(PSATD_F64);
   return g_fail ? 1 : 0;
 }
