@@ -277,7 +277,11 @@ psatd_status psatd_modified_k(psatd_plan_t plan, int32_t s, int32_t axis, double
 /*
  * psatd_set_tuning / psatd_get_tuning -- launch-shape knobs (psatd_tune_key).  Setting a
  * value the plan cannot use (e.g. a z tile that does not fit the LDS) returns
- * PSATD_E_INVALID and leaves the plan unchanged.  Cached graphs are dropped.
+ * PSATD_E_INVALID and leaves the plan unchanged.  Cached graphs are dropped.  Steps in
+ * flight, on any stream, and graphs in which the caller captured psatd_step_noalloc go on
+ * with the settings they were enqueued with, and the call may stand inside such a capture;
+ * not so the MAX_RADIX knobs, which wait for the plan's stream and rewrite its tables.
+ * The plan keeps the device lists of every setting it has had until psatd_destroy.
  */
 psatd_status psatd_set_tuning(psatd_plan_t plan, int32_t key, int32_t value);
 psatd_status psatd_get_tuning(psatd_plan_t plan, int32_t key, int32_t* value);

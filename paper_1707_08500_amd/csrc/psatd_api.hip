@@ -53,6 +53,25 @@ void* scratch_of(int device) {
   return g_scratch_ptr[device];
 }
 
+// A device copy of work lists.  It is not rewritten or freed while the plan
+// lives, whatever the knobs are set to meanwhile: launches in flight on any
+// stream, and graphs that a caller has captured (psatd_step_noalloc), go on
+// reading it.  A setting that comes back finds its copy again, so a plan holds
+// one per distinct list that its settings have asked for.
+struct ListCopy {
+  std::vector<unsigned char> bytes;
+  void* dev;
+};
+
+// Allocations and synchronous copies are refused to a thread while a capture in
+// the runtime's default mode runs anywhere in the process; the plan's lists have
+// nothing to do with what is captured.
+struct RelaxedCapture {
+  hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+  RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+  ~RelaxedCapture() { (void)hipThreadExchangeStreamCaptureMode(&mode); }
+};
+
 struct GraphEntry {
   void* ptr[9];
   int32_t nsteps;
@@ -70,7 +89,7 @@ struct psatd_plan_s {
   hipStream_t cap_stream = nullptr;
   int device = 0;
   void* blob = nullptr;  // device tables
-  void* lists = nullptr;  // device work lists (they depend on the knobs)
+  std::vector<ListCopy> lists;  // device work lists (they depend on the knobs)
   const BoxD* tight = nullptr;  // in lists: the boxes with their spectral planes back to back
   int32_t tune[PSATD_NTUNE] = {0, 1, 0, 0, 0, 0, 0, 16, 256, 512, 0, 1, 0, 0};
   void* ws = nullptr;
@@ -153,6 +172,28 @@ psatd_status ensure_workspace(psatd_plan_t p) {
   return PSATD_OK;
 }
 
+// The device copy of a list: the one the plan has, or a new one.
+psatd_status device_list(psatd_plan_t p, std::vector<unsigned char>& bytes, const unsigned char** dev) {
+  for (const ListCopy& c : p->lists)
+    if (c.bytes == bytes) {
+      *dev = static_cast<const unsigned char*>(c.dev);
+      return PSATD_OK;
+    }
+  p->lists.reserve(p->lists.size() + 1);
+  const RelaxedCapture relaxed;
+  void* fresh = nullptr;
+  HIPCHK(p, hipMalloc(&fresh, bytes.size()));
+  hipError_t e = hipMemcpyAsync(fresh, bytes.data(), bytes.size(), hipMemcpyHostToDevice, p->cap_stream);
+  if (e == hipSuccess) e = hipStreamSynchronize(p->cap_stream);
+  if (e != hipSuccess) {
+    (void)hipFree(fresh);
+    HIPCHK(p, e);
+  }
+  p->lists.push_back({std::move(bytes), fresh});
+  *dev = static_cast<const unsigned char*>(fresh);
+  return PSATD_OK;
+}
+
 // Builds the work lists for the plan's current knobs and uploads them.  Boxes
 // share the planes of their columns in an unbatched plan, except under the
 // register z pass, which addresses each box's own 9 fields.  Where that fails,
@@ -160,53 +201,43 @@ psatd_status ensure_workspace(psatd_plan_t p) {
 psatd_status upload_lists(psatd_plan_t p) {
   HostTables& h = p->h;
   DevPlan& d = p->dp;
-  std::vector<unsigned char> hb;
-  size_t off[6];
   WorkLists was;
   std::swap(was, h.lists);
-  void* fresh = nullptr;
   psatd_status st = PSATD_OK;
+  size_t off[5];
+  const unsigned char *base = nullptr, *tiles = nullptr;
   try {
     const bool one = h.batches.size() == 1;
     build_lists(h, one && !d.zreg, d.ntxy == 0 && !h.split && one, d.zcl && one);
     const WorkLists& w = h.lists;
-    size_t total = 0;
-    auto put = [&](int i, const void* src, size_t bytes) {
-      off[i] = total;
-      total += (bytes + 255) & ~(size_t)255;
-      hb.resize(total);
-      if (bytes) std::memcpy(hb.data() + off[i], src, bytes);
+    std::vector<unsigned char> hb, ht;  // the tiles by themselves: they follow other knobs
+    auto put = [](std::vector<unsigned char>& to, const void* src, size_t bytes) {
+      const size_t at = to.size();
+      to.resize(at + ((bytes + 255) & ~(size_t)255));
+      if (bytes) std::memcpy(to.data() + at, src, bytes);
+      return at;
     };
-    put(0, w.box.data(), w.box.size() * sizeof(BoxD));
-    put(1, w.pull.data(), w.pull.size() * sizeof(PullPiece));
-    put(2, w.fwd.data(), w.fwd.size() * sizeof(PlaneRec));
-    put(3, w.inv.data(), w.inv.size() * sizeof(PlaneRec));
-    put(4, w.tiles.data(), w.tiles.size() * sizeof(ZItem));
-    put(5, w.tight.data(), w.tight.size() * sizeof(BoxD));
+    off[0] = put(hb, w.box.data(), w.box.size() * sizeof(BoxD));
+    off[1] = put(hb, w.pull.data(), w.pull.size() * sizeof(PullPiece));
+    off[2] = put(hb, w.fwd.data(), w.fwd.size() * sizeof(PlaneRec));
+    off[3] = put(hb, w.inv.data(), w.inv.size() * sizeof(PlaneRec));
+    off[4] = put(hb, w.tight.data(), w.tight.size() * sizeof(BoxD));
+    put(ht, w.tiles.data(), w.tiles.size() * sizeof(ZItem));
+    st = device_list(p, hb, &base);
+    if (st == PSATD_OK) st = device_list(p, ht, &tiles);
   } catch (...) {
     st = fail(p, PSATD_E_NOMEM, "host allocation failed");
   }
-  if (st == PSATD_OK) {
-    st = [&]() -> psatd_status {
-      HIPCHK(p, hipMalloc(&fresh, hb.size()));
-      HIPCHK(p, hipMemcpy(fresh, hb.data(), hb.size(), hipMemcpyHostToDevice));
-      return PSATD_OK;
-    }();
-  }
   if (st != PSATD_OK) {
-    if (fresh) (void)hipFree(fresh);
     std::swap(was, h.lists);
     return st;
   }
-  if (p->lists) (void)hipFree(p->lists);
-  p->lists = fresh;
-  unsigned char* base = reinterpret_cast<unsigned char*>(fresh);
   d.box = reinterpret_cast<const BoxD*>(base + off[0]);
   d.pullp = reinterpret_cast<const PullPiece*>(base + off[1]);
   d.fwd = reinterpret_cast<const PlaneRec*>(base + off[2]);
   d.inv = reinterpret_cast<const PlaneRec*>(base + off[3]);
-  d.tiles = reinterpret_cast<const ZItem*>(base + off[4]);
-  p->tight = reinterpret_cast<const BoxD*>(base + off[5]);
+  p->tight = reinterpret_cast<const BoxD*>(base + off[4]);
+  d.tiles = reinterpret_cast<const ZItem*>(tiles);
   return PSATD_OK;
 }
 
@@ -548,7 +579,7 @@ void psatd_destroy(psatd_plan_t p) {
   drop_graphs(p);
   if (p->ws_owned && p->ws) (void)hipFree(p->ws);
   if (p->blob) (void)hipFree(p->blob);
-  if (p->lists) (void)hipFree(p->lists);
+  for (const ListCopy& c : p->lists) (void)hipFree(c.dev);
   if (p->cap_stream) (void)hipStreamDestroy(p->cap_stream);
   delete p;
 }
@@ -776,7 +807,6 @@ psatd_status set_knob(psatd_plan_t p, int32_t key, int32_t value, bool& relist) 
         return fail(p, PSATD_E_INVALID, "z pencils must be 0 (per launch class), 4, 6, 8 or 16");
       if (!z_tile_fits(p->h, max_padded_z(p->h), value))
         return fail(p, PSATD_E_INVALID, "z tile does not fit the LDS");
-      HIPCHK(p, hipStreamSynchronize(p->stream));
       set_z_tile(p->h, value);
       HIPCHK(p, prepare_kernels(d.f64, d.spl, p->h.ldsF, p->h.ldsI, z_lds_max(p->h), p->h.ldsX, p->h.ldsY));
       d.zcl = 0;
@@ -800,7 +830,6 @@ psatd_status set_knob(psatd_plan_t p, int32_t key, int32_t value, bool& relist) 
       if (value < 0) return fail(p, PSATD_E_INVALID, "boxes per batch must be >= 0");
       if (value > 0 && value < p->h.nsub && p->h.split)
         return fail(p, PSATD_E_INVALID, "the split x/y passes do not batch");
-      HIPCHK(p, hipStreamSynchronize(p->stream));
       set_batches(p->h, value);
       relist = true;
       if (p->h.batches.size() > 1) {  // a later batch must still read its old guards
@@ -915,11 +944,7 @@ psatd_status psatd_set_tuning(psatd_plan_t p, int32_t key, int32_t value) {
     bool relist = false;
     try {
       st = set_knob(p, key, value, relist);
-      if (st == PSATD_OK && relist) {
-        const hipError_t e = hipStreamSynchronize(p->stream);
-        st = e == hipSuccess ? upload_lists(p)
-                             : fail(p, PSATD_E_HIP, std::string("hipStreamSynchronize: ") + hipGetErrorString(e));
-      }
+      if (st == PSATD_OK && relist) st = upload_lists(p);
     } catch (...) {
       restore_knobs(p, was);
       throw;

@@ -12,6 +12,7 @@
 #include <functional>
 #include <map>
 #include <string>
+#include <utility>
 #include <vector>
 
 namespace fake {
@@ -37,8 +38,18 @@ bool refuse(int& left) {
   return left-- == 0;
 }
 
+// The stream under capture, and whether this thread may still allocate and copy.
+hipStream_t capturing = nullptr;
+hipStreamCaptureMode mode = hipStreamCaptureModeGlobal;
+bool capture_broken = false;
+bool unsafe_in_capture() {
+  if (!capturing || mode == hipStreamCaptureModeRelaxed) return false;
+  return capture_broken = true;
+}
+
 hipError_t Malloc(void** p, size_t bytes) {
   *p = nullptr;
+  if (unsafe_in_capture()) return hipErrorStreamCaptureUnsupported;
   if (refuse(mallocs_left)) return hipErrorOutOfMemory;
   *p = std::aligned_alloc(256, (bytes + 255) & ~(size_t)255);
   blocks[(uintptr_t)*p] = {bytes, true};
@@ -46,12 +57,24 @@ hipError_t Malloc(void** p, size_t bytes) {
   return hipSuccess;
 }
 hipError_t Free(void* p) {
+  if (unsafe_in_capture()) return hipErrorStreamCaptureUnsupported;
   if (p) blocks.at((uintptr_t)p).live = false;
   return hipSuccess;
 }
 hipError_t Memcpy(void* d, const void* s, size_t bytes) {
+  if (unsafe_in_capture()) return hipErrorStreamCaptureUnsupported;
   if (refuse(copies_left)) return hipErrorUnknown;
   if (bytes) std::memcpy(d, s, bytes);
+  return hipSuccess;
+}
+
+hipError_t Synchronize(hipStream_t s) {
+  if (!capturing || s != capturing) return hipSuccess;
+  capture_broken = true;
+  return hipErrorStreamCaptureUnsupported;
+}
+hipError_t ExchangeMode(hipStreamCaptureMode* m) {
+  std::swap(*m, mode);
   return hipSuccess;
 }
 
@@ -74,14 +97,14 @@ hipError_t SymbolAddress(void** p) {
 #define hipGetLastError() hipSuccess
 #define hipStreamCreateWithFlags(s, f) (*(s) = (hipStream_t)(uintptr_t)1, hipSuccess)
 #define hipStreamDestroy(s) hipSuccess
-#define hipStreamSynchronize(s) hipSuccess
+#define hipStreamSynchronize(s) fake::Synchronize(s)
 #define hipStreamBeginCapture(s, m) hipSuccess
 #define hipStreamEndCapture(s, g) hipSuccess
 #define hipGraphInstantiate(x, g, a, b, c) hipSuccess
 #define hipGraphLaunch(x, s) hipSuccess
 #define hipGraphDestroy(g) hipSuccess
 #define hipGraphExecDestroy(x) hipSuccess
-#define hipThreadExchangeStreamCaptureMode(m) hipSuccess
+#define hipThreadExchangeStreamCaptureMode(m) fake::ExchangeMode(m)
 
 #include "psatd_api.hip"
 
@@ -316,6 +339,57 @@ void check_failures(int prec) {
   std::printf("failures ok\n");
 }
 
+// What a step's launches were given stays as it was through later tuning calls:
+// they may not have run yet (another stream), or run again (a captured graph).
+void check_lists_stay(int prec) {
+  auto live = [] {
+    size_t n = 0;
+    for (const auto& b : fake::blocks) n += b.second.live;
+    return n;
+  };
+  const size_t outside = live();
+  psatd_plan_t p = cubes(48, 2, 8, prec);
+  const std::vector<int32_t> first = knobs(p);
+  CHECK(ok(trace([&] { return psatd_step_noalloc(p, F, F, F); })), "lists: step");
+  const auto given = g_reads;
+  size_t blocks = 0;
+  for (int round = 0; round < 3; ++round) {
+    for (const Knob& k : kListKnobs) {
+      CHECK(psatd_set_tuning(p, k.key, k.value) == PSATD_OK && ok(step(p)), "lists: knob %d", k.key);
+      for (const auto& g : given)
+        CHECK(fake::covers(g.first, g.second.size()) && !std::memcmp(g.first, g.second.data(), g.second.size()),
+              "lists: rewritten or freed by knob %d", k.key);
+      CHECK(psatd_set_tuning(p, k.key, first[k.key]) == PSATD_OK, "lists: knob %d back", k.key);
+    }
+    for (int k : {PSATD_TUNE_FUSE_EB, PSATD_TUNE_XY_THREADS, PSATD_TUNE_Z_PENCILS, PSATD_TUNE_PULL_EB})
+      CHECK(psatd_set_tuning(p, k, first[k]) == PSATD_OK, "lists: knob %d back", k);
+    if (round == 1) blocks = fake::blocks.size();
+  }
+  CHECK(fake::blocks.size() == blocks, "lists: settings that come back allocate again");
+  psatd_destroy(p);
+  CHECK(live() == outside, "lists: memory not given back");
+  std::printf("lists ok\n");
+}
+
+// The knobs that only choose among launches may be set while a stream, the plan's
+// own too, is being captured.
+void check_capture(int prec) {
+  psatd_plan_t p = cubes(48, 2, 8, prec);
+  const hipStream_t st = (hipStream_t)(uintptr_t)2;
+  CHECK(psatd_set_stream(p, st) == PSATD_OK, "capture: stream");
+  fake::capturing = st;
+  for (const Knob& k : kListKnobs) {
+    CHECK(ok(trace([&] { return psatd_step_noalloc(p, F, F, F); })), "capture: step");
+    CHECK(psatd_set_tuning(p, k.key, k.value) == PSATD_OK && !fake::capture_broken, "capture: knob %d", k.key);
+    if (k.key == PSATD_TUNE_SPLIT_XY) CHECK(psatd_set_tuning(p, k.key, 0) == PSATD_OK, "capture: unsplit");
+    if (k.key == PSATD_TUNE_BATCH_BOXES) CHECK(psatd_set_tuning(p, k.key, 0) == PSATD_OK, "capture: unbatched");
+  }
+  CHECK(fake::mode == hipStreamCaptureModeGlobal, "capture: the thread's mode is given back");
+  fake::capturing = nullptr;
+  psatd_destroy(p);
+  std::printf("capture ok\n");
+}
+
 }  // namespace
 
 int main() {
@@ -323,5 +397,9 @@ int main() {
   check_workspace(PSATD_F64);
   check_failures(PSATD_F32_VALU);
   check_failures(PSATD_F64);
+  check_lists_stay(PSATD_F32_VALU);
+  check_lists_stay(PSATD_F64);
+  check_capture(PSATD_F32_VALU);
+  check_capture(PSATD_F64);
   return g_fail ? 1 : 0;
 }
