@@ -721,17 +721,37 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
     }
   }
   // The inverse pass in two halves: FP32 planes beyond the LDS of which half fits
-  // it and a quarter fits the registers set aside for it.
+  // it and a quarter fits the registers set aside for it.  A plane is one group and
+  // fills a compute unit, so the pass takes whole rounds of planes, where the split
+  // passes have some 16 short groups for each.  So only where the rounds are full
+  // enough on average: 0.67 (in a single round 0.55) if every transform takes two
+  // stages, else 0.75 (a lone group exposes the barriers of each stage).  A step in
+  // halves against one split, one box of 200^2 to 512 x 96: 1 to 4 planes (0.02 to
+  // 0.09 of a round) 1.13 to 1.32; 16 (0.38) 0.99 to 1.11; 48 (two rounds, 0.56) 1.00
+  // to 1.09.  Two stages: 24 planes (0.56) 0.95 to 1.01, 0.66 to 0.75 0.90 to 1.01.
+  // Three: 0.70 0.94 to 1.04; 0.75 to 0.78 0.90 to 1.04, below 1 on average; 0.82 to
+  // 0.98 0.88 to 1.00.
+  auto two_stages = [](int N) {
+    std::vector<int> r;
+    return factorize(N, r, 16) && r.size() <= 2;
+  };
   auto halve = [&](const std::vector<char>& in) {
     if (h.prec != PSATD_F32_VALU || h.fuse_eb || h.ldsF <= kMaxDynLds) return 0;
     int half = 0, quarter = 0;
+    int64_t groups = 0;  // planes of the 6 fields
+    bool two = true;
     for (int s = 0; s < h.nsub; ++s) {
       if (!in[s]) continue;
       const BoxD& b = h.box[s];
+      groups += 6 * b.n[2];
+      two = two && two_stages(b.P[0] / 2) && two_stages(b.P[1]);
       half = std::max(half, (half_elems(b.P[1], b.ld, b.H) + b.P[0] / 2 + b.P[1] + b.P[0]) * 8 +
                                 (b.P[0] / 2 + b.P[1]) * 4);
       quarter = std::max(quarter, (b.P[1] + 1) / 2 * half_cols(b.H));
     }
+    const int64_t places = (groups + kComputeUnits - 1) / kComputeUnits * kComputeUnits;
+    const int least = !two ? 75 : (places == kComputeUnits ? 55 : 67);
+    if (100 * groups < least * places) return 0;
     return half <= kMaxDynLds && quarter <= kHalfHold * kThreadsHalf ? half : 0;
   };
   auto add_planes = [&](const std::vector<char>& in, XyLaunch& l) {

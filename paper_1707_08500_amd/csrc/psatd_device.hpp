@@ -15,9 +15,10 @@ namespace psatd {
 
 // Launch shapes (gfx950: 64-wide waves, 160 KiB LDS per compute unit).
 constexpr int kThreadsXY = 256;   // x/y plane passes, exchange, scatter/gather
-constexpr int kThreadsHalf = 1024;  // x/y passes over planes in two halves
+constexpr int kThreadsHalf = 1024;  // inverse x/y pass over planes in two halves
 constexpr int kMaxR = 16;         // largest radix codelet (radix 11 is always available)
 constexpr int kMaxDynLds = 160 * 1024;
+constexpr int kComputeUnits = 256;
 
 // One padded subdomain (Sec. 3.2, Fig. 2a).  Axes (x, y, z).
 struct BoxD {
@@ -1323,13 +1324,12 @@ PSATD_HD void body_inv_xy(const InvArgs<T>& a, int item, int tid, int nt, cx<T>*
 // halves, with what is not being transformed in registers (the vector registers
 // of a compute unit hold three times its LDS).  That saves the passes of their
 // own for y and x and the round trip through the workspace between them: one
-// 256^3 box 0.55 -> 0.39 ms; planes of 200^2 to 360 x 176 8 to 30 % faster (300 x
-// 144, in three stages each way, 4 % slower).  The forward pass keeps the split
-// passes: 256^2 0.40 -> 0.35 ms in halves, but 200^2 to 240 x 216 0.21 -> 0.24 and
-// 0.12 -> 0.15 (a lone group per compute unit exposes every stage).  So do FP64
-// planes (176^2, 8 boxes: inverse 1.19 -> 1.36 ms), and FP32 planes that fit the
-// LDS once stay whole (176^2 as two 512-thread groups per compute unit, 64 boxes:
-// 3.5 -> 4.3 ms).
+// 256^3 box 0.55 -> 0.39 ms.  The planes it is taken for are build_lists' choice.
+// The forward pass keeps the split passes: 256^2 0.40 -> 0.35 ms in halves, but
+// 200^2 to 240 x 216 0.21 -> 0.24 and 0.12 -> 0.15 (a lone group per compute unit
+// exposes every stage).  So do FP64 planes (176^2, 8 boxes: inverse 1.19 -> 1.36
+// ms), and FP32 planes that fit the LDS once stay whole (176^2 as two 512-thread
+// groups per compute unit, 64 boxes: 3.5 -> 4.3 ms).
 constexpr int kHalfHold = 10;  // values held per thread and quarter plane
 
 // LDS elements of half a plane: ceil(Py/2) rows, or Py rows of half the columns.

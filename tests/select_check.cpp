@@ -1,0 +1,83 @@
+// Host check of the launches that the planner chooses by size (plan_host.hpp),
+// built and run by test_select.py: on both sides of each limit, and for the
+// shapes with which the GPU tests mean to reach a kernel.
+#include <cstdio>
+#include <cstdlib>
+
+#include <hip/hip_runtime.h>
+
+#include "plan_host.hpp"
+
+using namespace psatd;
+
+namespace {
+
+int g_fail = 0;
+#define EXPECT(c, ...)                     \
+  do {                                     \
+    if (!(c)) {                            \
+      std::fprintf(stderr, __VA_ARGS__);   \
+      std::fprintf(stderr, " (%s)\n", #c); \
+      ++g_fail;                            \
+    }                                      \
+  } while (0)
+
+// The lists of a grid N in k equal boxes per axis with guards g.
+HostTables lists(int prec, std::array<int64_t, 3> N, std::array<int, 3> k = {1, 1, 1},
+                 std::array<int32_t, 3> g = {0, 0, 0}, int ntu = 512, bool fuse = false) {
+  std::vector<int64_t> lo, n;
+  std::vector<int32_t> gu;
+  for (int z = 0; z < k[2]; ++z)
+    for (int y = 0; y < k[1]; ++y)
+      for (int x = 0; x < k[0]; ++x)
+        for (int u = 0; u < 3; ++u) {
+          const int c = u == 0 ? x : (u == 1 ? y : z);
+          lo.push_back(c * (N[u] / k[u]));
+          n.push_back(N[u] / k[u]);
+          gu.push_back(g[u]);
+        }
+  HostTables h;
+  std::string err;
+  const double d[3] = {1, 1, 1};
+  if (build_host(h, err, N.data(), d, k[0] * k[1] * k[2], lo.data(), n.data(), gu.data(), 16, 0.5, 1.0, prec,
+                 PSATD_J_REPLICATED) != PSATD_OK) {
+    std::fprintf(stderr, "%s\n", err.c_str());
+    std::exit(1);
+  }
+  h.ntu = ntu;
+  h.fuse_eb = fuse;
+  build_lists(h, true, !h.xyc.empty(), !h.zcls.empty());
+  return h;
+}
+
+bool halves(const HostTables& h) { return h.split && h.lists.xy[0][0].half > 0; }
+
+void check_halves() {
+  auto one = [](int64_t x, int64_t y, int64_t z) { return lists(PSATD_F32_VALU, {x, y, z}); };
+  // two stages each way: from 0.55 of one round of 256 planes of the 6 fields, 0.67 of more
+  EXPECT(!halves(one(256, 256, 22)) && halves(one(256, 256, 24)), "256 x 256, one round");
+  EXPECT(halves(one(256, 256, 42)) && !halves(one(256, 256, 44)), "256 x 256, into the second round");
+  EXPECT(!halves(one(256, 256, 56)) && halves(one(256, 256, 60)), "256 x 256, two rounds");
+  EXPECT(halves(one(256, 256, 256)), "256^3");
+  // three stages along x (150 = 5 5 6): from 0.75
+  EXPECT(!halves(one(300, 144, 30)) && halves(one(300, 144, 32)), "300 x 144, one round");
+  EXPECT(!halves(one(300, 144, 63)) && halves(one(300, 144, 64)), "300 x 144, two rounds");
+  for (int z : {1, 2, 4, 16}) EXPECT(!halves(one(192, 256, z)), "%d planes", z);
+  EXPECT(halves(lists(PSATD_F32_VALU, {368, 368, 128}, {2, 2, 2}, {8, 8, 8})), "eight boxes");
+  // not fused, not FP64, not planes that fit the LDS
+  EXPECT(!halves(lists(PSATD_F32_VALU, {256, 256, 64}, {1, 1, 1}, {0, 0, 0}, 512, true)), "fused exchange");
+  EXPECT(!halves(lists(PSATD_F64, {256, 256, 64})), "FP64");
+  EXPECT(!halves(one(96, 96, 256)), "planes that fit the LDS");
+  // test_gpu_halves.py
+  EXPECT(halves(lists(PSATD_F32_VALU, {210, 201, 36}, {1, 1, 1}, {3, 12, 2})), "216 x 225");
+  EXPECT(halves(lists(PSATD_F32_VALU, {420, 1, 40}, {1, 1, 1}, {0, 87, 1})), "420 x 175, one row");
+  EXPECT(halves(one(256, 192, 30)), "256 x 192");
+  std::printf("halves ok\n");
+}
+
+}  // namespace
+
+int main() {
+  check_halves();
+  return g_fail ? 1 : 0;
+}
