@@ -656,11 +656,22 @@ inline std::vector<Ring> build_rings(const HostTables& h, std::vector<BoxD>& box
 }
 
 // Pencils per heat z tile: the widest of 32, 16 and 8 of which four 256-thread
-// tiles (16 waves) fit a compute unit's LDS, else 4.
-inline int heat_pencils_for(int Pz, int real_bytes) {
-  for (int PB : {32, 16, 8})
-    if (4 * heat_tile_lds(Pz, PB, real_bytes) <= kMaxDynLds) return PB;
-  return 4;
+// tiles (16 waves) fit a compute unit's LDS, else 4; narrower while that leaves
+// compute units without a tile.  Four steps with 4, 8, 16, 32 pencils (us), one box,
+// FP32: 16 16 256 94, 97, 106, 139; 24 24 128 93, 94, 97, 110; 64^3 114, 112, 110,
+// 117; 96^3 187, 163, 163, 171; FP64: 48^3 110, 109, 110, 116; 64^3 150, 128, 128,
+// 137; more tiles, 27 boxes of 48^3 padded, FP32: 354, 259, 205, 200.
+inline int heat_pencils(const HostTables& h) {
+  const int Pz = max_padded_z(h), rb = (int)real_size(h.prec);
+  int PB = 32;
+  while (PB > 4 && 4 * heat_tile_lds(Pz, PB, rb) > kMaxDynLds) PB /= 2;
+  auto tiles = [&] {
+    int64_t n = 0;
+    for (const BoxD& b : h.box) n += ((int64_t)b.P[1] * b.H + PB - 1) / PB;
+    return n;
+  };
+  while (PB > 4 && tiles() < kComputeUnits) PB /= 2;
+  return PB;
 }
 
 // Fills h.lists for the current batches and z tile.  share: columns share
@@ -860,7 +871,7 @@ inline void build_lists(HostTables& h, bool share, bool xy_classes, bool z_class
   }
   if (h.batches.size() == 1) {
     std::vector<char> in(h.nsub, 1);
-    w.heat.PB = heat_pencils_for(max_padded_z(h), (int)real_size(h.prec));
+    w.heat.PB = heat_pencils(h);
     w.heat.lds = (int32_t)heat_tile_lds(max_padded_z(h), w.heat.PB, (int)real_size(h.prec));
     add_tiles(in, w.heat);
   }

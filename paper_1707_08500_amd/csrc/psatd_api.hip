@@ -693,8 +693,11 @@ psatd_status psatd_heat_run(psatd_plan_t p, void* u, double diffusivity, int32_t
   d.box = boxes_in(p, p->ws_bytes);
   void* in9[9] = {u, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
   void* out6[6] = {u, nullptr, nullptr, nullptr, nullptr, nullptr};
+  // boxes without guards have nothing to pull: their planes load in one run, in place
+  // (four steps of one 16^3 box in FP32 80.5 -> 79.2 us, of 48^3 in FP64 109.8 -> 108.0)
+  const int npull = d.pull && d.nG ? 1 : 0;
   for (int i = 0; i < nsteps; ++i) {
-    for (const XyLaunch& l : p->h.lists.xy[0]) HIPCHK(p, launch_fwd(d, l, 0, in9, 1, d.pull ? 1 : 0, p->ws, p->stream));
+    for (const XyLaunch& l : p->h.lists.xy[0]) HIPCHK(p, launch_fwd(d, l, 0, in9, 1, npull, p->ws, p->stream));
     HIPCHK(p, launch_heat_z(d, p->h.lists.heat, p->ws, diffusivity, d.dt, p->stream));
     for (const XyLaunch& l : p->h.lists.xy[0]) HIPCHK(p, launch_inv(d, l, 0, p->ws, out6, 1, p->stream));
     // pulled as in the field step: guard cells are read from their owners

@@ -1074,9 +1074,10 @@ PSATD_HD int64_t heat_tile_lds(int Pz, int PB, int real_bytes) {
 // spectrum), inverse z transform.  g is the product of a factor per kz and one
 // per (kx, ky), so a tile takes Pz + PB exponentials instead of Pz PB:
 // g1 g2, or (g1 - 1) + (g2 - 1) + (g1 - 1)(g2 - 1), whose terms the product
-// cannot cancel (both factors are in (0, 1]).  One field in LDS leaves room for
-// wide tiles: 32 pencils (256-byte runs) in place of the field pass's 10, with
-// the factors and the direct loads, 0.29 -> 0.15 ms on 64 boxes of 96^3 padded, FP32.
+// cannot cancel (both factors are at most 1, or for a negative dt both at least 1).
+// One field in LDS leaves room for wide tiles: 32 pencils (256-byte runs) in place of
+// the field pass's 10, with the factors and the direct loads, 0.29 -> 0.15 ms on 64
+// boxes of 96^3 padded, FP32.
 template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_z_heat(const HeatArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar,
                           Eng eng = Eng{}) {

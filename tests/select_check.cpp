@@ -75,9 +75,34 @@ void check_halves() {
   std::printf("halves ok\n");
 }
 
+void check_heat() {
+  auto pencils = [](int prec, std::array<int64_t, 3> N, std::array<int, 3> k = {1, 1, 1}) {
+    return lists(prec, N, k).lists.heat.PB;
+  };
+  // as wide as four tiles fit the LDS, while every compute unit has a tile
+  EXPECT(pencils(PSATD_F32_VALU, {96, 96, 96}, {1, 1, 1}) == 16, "4704 pencils");
+  EXPECT(pencils(PSATD_F32_VALU, {192, 192, 192}, {2, 2, 2}) == 32, "37632 pencils");
+  EXPECT(pencils(PSATD_F32_VALU, {64, 64, 64}) == 8 && pencils(PSATD_F64, {64, 64, 64}) == 8, "2112 pencils");
+  EXPECT(pencils(PSATD_F64, {48, 48, 48}) == 4, "1200 pencils");
+  EXPECT(pencils(PSATD_F32_VALU, {16, 16, 256}) == 4, "144 pencils");
+  EXPECT(pencils(PSATD_F64, {192, 192, 192}, {2, 2, 2}) == 16, "FP64, 96 long");
+  // 250 and 256 tiles of 32 pencils
+  EXPECT(pencils(PSATD_F32_BF16X6, {30, 500, 4}) == 16, "8000 pencils");
+  EXPECT(pencils(PSATD_F32_VALU, {30, 512, 8}) == 32, "8192 pencils");
+  // test_gpu_heat_tiles.py
+  for (int prec : {PSATD_F64, PSATD_F32_VALU, PSATD_F32_BF16X6}) {
+    EXPECT(pencils(prec, {16, 14, 96}) == 4, "126 pencils");
+    EXPECT(pencils(prec, {60, 70, 12}) == 8, "2170 pencils");
+    EXPECT(pencils(prec, {96, 96, 20}) == 16, "4704 pencils, short z");
+    EXPECT(lists(prec, {72, 60, 48}, {3, 3, 3}, {8, 8, 8}).lists.heat.PB == 32, "27 boxes");
+  }
+  std::printf("heat ok\n");
+}
+
 }  // namespace
 
 int main() {
   check_halves();
+  check_heat();
   return g_fail ? 1 : 0;
 }
