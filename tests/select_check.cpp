@@ -99,10 +99,45 @@ void check_heat() {
   std::printf("heat ok\n");
 }
 
+const ZLaunch& ztile(const HostTables& h) { return h.lists.z[0][0]; }
+
+void check_held() {
+  auto held = [](std::array<int64_t, 3> N, int ntu = 512) {
+    const HostTables h = lists(PSATD_F64, N, {1, 1, 1}, {0, 0, 0}, ntu);
+    return ztile(h).held ? ztile(h).PB : 0;
+  };
+  // test_gpu_rings.py
+  EXPECT(held({70, 75, 70}) == 8 && held({70, 75, 99}) == 8 && held({70, 75, 100}) == 8, "8 pencils");
+  EXPECT(held({48, 45, 147}) == 4 && held({48, 45, 200}) == 4, "4 pencils");
+  const HostTables two = lists(PSATD_F64, {64, 64, 160}, {1, 1, 2}, {8, 8, 8});
+  EXPECT(ztile(two).held && ztile(two).PB == 8, "two boxes");
+  // the other sides: tiles of which two share a compute unit with nine fields, pairs past
+  // the threads, one round of tiles, other thread counts and FP32
+  EXPECT(!held({70, 75, 56}) && held({70, 75, 70}), "short z");
+  EXPECT(!held({70, 75, 105}) && !held({48, 45, 210}), "long z");
+  EXPECT(!held({48, 45, 70}) && held({70, 75, 70}) && held({70, 60, 70}), "tiles");  // 141, 338 and 270
+  EXPECT(!held({70, 75, 70}, 1024), "1024 threads");
+  EXPECT(!ztile(lists(PSATD_F32_VALU, {70, 75, 70})).held, "FP32");
+  std::printf("held ok\n");
+}
+
+void check_narrow() {
+  for (int prec : {PSATD_F64, PSATD_F32_VALU})  // test_gpu_rings.py: 27 boxes of 32^3 padded
+    EXPECT(ztile(lists(prec, {72, 72, 72}, {3, 3, 3}, {4, 4, 4})).narrow, "27 boxes");
+  auto narrow = [](int prec, std::array<int64_t, 3> N) { return ztile(lists(prec, N)).narrow != 0; };
+  // three FP32 tiles or two FP64 ones to a compute unit, and more than one round of them
+  EXPECT(narrow(PSATD_F32_VALU, {128, 100, 70}) && !narrow(PSATD_F32_VALU, {128, 100, 75}), "FP32, z");
+  EXPECT(narrow(PSATD_F64, {128, 100, 64}) && !narrow(PSATD_F64, {128, 100, 70}), "FP64, z");
+  EXPECT(!narrow(PSATD_F32_VALU, {64, 64, 64}) && !narrow(PSATD_F64, {54, 64, 64}), "one round");
+  std::printf("narrow ok\n");
+}
+
 }  // namespace
 
 int main() {
   check_halves();
   check_heat();
+  check_held();
+  check_narrow();
   return g_fail ? 1 : 0;
 }
