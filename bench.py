@@ -225,19 +225,43 @@ def load_state(plan, inputs, E, B, J):
     torch.cuda.empty_cache()
 
 
-def algorithmic_bytes(plan, dec_lo, dec_n, dec_g, sb):
+def distinct_planes(N, lo, n, g, padded):
+    """Padded (x, y) planes of all boxes, those that boxes of one column (same
+    extent and guards along x and y) share counted once; and the same weighted with
+    a plane's half spectrum and real elements: (complex elements, real elements)."""
+    Nz = int(N[2])
+    columns = {}
+    for s in range(len(lo)):
+        columns.setdefault(tuple(int(v[s][u]) for v in (lo, n, g) for u in (0, 1)), []).append(s)
+    spec = real = 0
+    for boxes in columns.values():
+        px, py, _ = padded[boxes[0]]
+        first = [(int(lo[s][2]) - int(g[s][2])) % Nz for s in boxes]
+        zs = {(z0 + z) % Nz for s, z0 in zip(boxes, first) for z in range(padded[s][2])}
+        count = len(zs)
+        if count == Nz and any((z0 - first[0]) % Nz + padded[s][2] > 2 * Nz for s, z0 in zip(boxes, first)):
+            count = sum(padded[s][2] for s in boxes)  # wraps twice: the boxes keep planes of their own
+        spec += count * py * (px // 2 + 1)
+        real += count * py * px
+    return spec, real
+
+
+def algorithmic_bytes(plan, dec_lo, dec_n, dec_g, sb, run=None):
     """Bytes each phase must move at least once, per launch (one step).  The z
     pass reads 9 complex fields at every k-point and writes the 6 results on the
     interior z-planes only (all the inverse pass reads).  The FP32 forms add
     increments, so their inverse pass reads and writes the interior cells.  With
     the fused E,B exchange the inverse pass also writes every guard copy (no
-    read), and the exchange phase moves nothing.  Counted per padded plane of every
-    box and for all nine fields: plans whose boxes share planes, and the later steps
-    of a run, which keep J's transform, move less than this."""
-    fused = bool(plan.tuning()["fuse_eb"])
+    read), and the exchange phase moves nothing.  Counted for nine fields and the
+    padded planes of every box; with run = (grid, steps) instead the mean of a step
+    of such a run as the plan makes it: the planes that boxes share once, J's
+    transform in the first step only (unbatched plans), J's exchange once, and the
+    E,B exchange once where the forward pass pulls it."""
+    tune = plan.tuning()
+    fused = bool(tune["fuse_eb"])
     inc = plan.precision != "f64"
     out = dict(exchange_J=0, fft_xy_fwd=0, z_update=0, fft_xy_inv=0, exchange_EB=0)
-    kpoints = 0
+    kpoints = cells = 0
     for s in range(len(dec_lo)):
         (px, py, pz), _ = plan.layout(s)
         nx, ny, nz = (int(v) for v in dec_n[s])
@@ -245,14 +269,27 @@ def algorithmic_bytes(plan, dec_lo, dec_n, dec_g, sb):
         H = px // 2 + 1
         guard = V - nx * ny * nz
         out["exchange_J"] += guard * 3 * 2 * sb
-        out["fft_xy_fwd"] += 9 * V * sb + 9 * pz * py * H * 2 * sb
-        out["z_update"] += (9 * pz + 6 * nz) * py * H * 2 * sb
+        out["z_update"] += 6 * nz * py * H * 2 * sb
         out["fft_xy_inv"] += 6 * nz * py * H * 2 * sb + (2 if inc else 1) * 6 * nz * ny * nx * sb
         if fused:
             out["fft_xy_inv"] += guard * 6 * sb
         else:
             out["exchange_EB"] += guard * 6 * 2 * sb
         kpoints += pz * py * H
+        cells += V
+    spec, real, fields = kpoints, cells, 9
+    if run:
+        grid, steps = run
+        one = not 0 < tune.get("batch_boxes", 0) < len(dec_lo)
+        if one and not tune.get("z_reg"):
+            spec, real = distinct_planes(grid, dec_lo, dec_n, dec_g, [plan.layout(s)[0] for s in range(len(dec_lo))])
+        if one:
+            fields = 6 + 3 / steps
+        out["exchange_J"] /= steps
+        if tune.get("pull_eb"):
+            out["exchange_EB"] /= steps
+    out["fft_xy_fwd"] = fields * (real * sb + spec * 2 * sb)
+    out["z_update"] += 9 * spec * 2 * sb
     return out, kpoints
 
 
@@ -539,7 +576,7 @@ def measure_form(wl_name, wl, dec, inputs, prec, steps, warmup, profile_steps, g
     if profile:
         load_state(plan, inputs, E, B, J)
         res["phases_ms"] = plan.run_profiled(E, B, J, profile_steps)
-    res["algo_bytes"], _ = algorithmic_bytes(plan, lo, n, g, 8 if prec == "f64" else 4)
+    res["algo_bytes"], _ = algorithmic_bytes(plan, lo, n, g, 8 if prec == "f64" else 4, run=(N, profile_steps))
     if gate_steps:
         load_state(plan, inputs, E, B, J)
         plan.run(E, B, J, gate_steps)
