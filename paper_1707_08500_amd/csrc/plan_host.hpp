@@ -1132,10 +1132,8 @@ inline psatd_status build_host(HostTables& h, std::string& err, const int64_t gr
     v.assign(nsub + 1, 0);
     for (int s = 0; s < nsub; ++s) v[s + 1] = v[s] + (int32_t)count(h.box[s]);
   };
-  const int PB = h.PB;
-  (void)PB;
   prefix(h.itemsF, [](const BoxD& b) { return (int64_t)b.P[2] * 9; });
-  set_z_tile(h, PB);
+  set_z_tile(h, h.PB);
   prefix(h.itemsI, [](const BoxD& b) { return (int64_t)b.n[2] * 6; });
   prefix(h.itemsP, [](const BoxD& b) { return (int64_t)b.P[2]; });
   prefix(h.itemsN, [](const BoxD& b) { return (int64_t)b.n[2]; });

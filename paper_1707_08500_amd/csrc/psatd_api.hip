@@ -542,7 +542,6 @@ psatd_status psatd_plan(psatd_plan_t* out, const int64_t grid_n[3], const double
   d.itemsG = reinterpret_cast<const int32_t*>(B + o_iG);
   d.fillp = reinterpret_cast<const FillPiece*>(B + o_fp);
   d.pieceOf = reinterpret_cast<const int32_t*>(B + o_pOf);
-  d.npiece = (int32_t)h.push.size();
   d.nG = h.itemsG.back();
   d.itemsZR = reinterpret_cast<const int32_t*>(B + o_iZR);
   d.nzg = (int32_t)h.zgroups.size();

@@ -196,15 +196,10 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_rsrc(const void* base, 
 }
 
 typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
-// One complex value at byte offset voff + soff (soff wave-uniform).
+// One complex FP32 value at byte offset voff + soff (soff wave-uniform).
 __device__ __forceinline__ void buf_load(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, cx<float>* v) {
   const u32x2 w = __builtin_amdgcn_raw_buffer_load_b64(rs, (int)voff, (int)soff, 0);
-  __builtin_memcpy(v, &w, sizeof(w));
-}
-__device__ __forceinline__ void buf_load(__amdgpu_buffer_rsrc_t rs, uint32_t voff, uint32_t soff, cx<double>* v) {
-  const u32x4 w = __builtin_amdgcn_raw_buffer_load_b128(rs, (int)voff, (int)soff, 0);
   __builtin_memcpy(v, &w, sizeof(w));
 }
 
@@ -518,10 +513,10 @@ PSATD_HD void copy_rect_to_plane(const T* src, int sP0, int ly, int lx, int y0, 
   }
 }
 
-// Rows [y0, y1) of a padded plane into LDS rows 0, 1, ...
+// The rows of a padded plane into the LDS.
 template <typename T>
-PSATD_HD void load_rows(const FwdArgs<T>& a, const PlaneRec& rec, const BoxD& bx, int f, int y0, int y1, cx<T>* lds,
-                        const int32_t* posx, int tid, int nt) {
+PSATD_HD void load_plane(const FwdArgs<T>& a, const PlaneRec& rec, const BoxD& bx, int f, cx<T>* lds,
+                         const int32_t* posx, int tid, int nt) {
   const int Px = bx.P[0], Py = bx.P[1], Nh = Px >> 1, ld = bx.ld, z = rec.z;
   if (f < a.npull) {
     // The box's own interior cells, then every guard region of this plane
@@ -534,36 +529,33 @@ PSATD_HD void load_rows(const FwdArgs<T>& a, const PlaneRec& rec, const BoxD& bx
     const T* inf = a.in[f];
     int dealt = 0;
     if (z >= gz && z < gz + bx.n[2]) {
-      const int lo = y0 > gy ? y0 : gy, hi = y1 < gy + bx.n[1] ? y1 : gy + bx.n[1];  // interior rows among them
-      const int ny = hi > lo ? hi - lo : 0;
+      const int ny = bx.n[1];
       const int r0 = (int)(((int64_t)ny * wave) / nw), r1 = (int)(((int64_t)ny * (wave + 1)) / nw);
       if (r1 > r0)
-        copy_rect_to_plane<T>(inf + bx.foff + ((int64_t)z * Py + lo + r0) * Px + gx, Px, r1 - r0, bx.n[0],
-                              lo + r0 - y0, gx, lds, ld, posx, lane, 64);
+        copy_rect_to_plane<T>(inf + bx.foff + ((int64_t)z * Py + gy + r0) * Px + gx, Px, r1 - r0, bx.n[0], gy + r0,
+                              gx, lds, ld, posx, lane, 64);
       dealt = nw;
     }
     for (int b = rec.p0; b < rec.p1; ++b) {
       if (dealt++ % nw != wave) continue;
       const PullPiece k = uniform_load(a.pull + b);
-      const int lo = y0 > k.qy ? y0 : k.qy, hi = y1 < k.qy + k.ly ? y1 : k.qy + k.ly;
-      if (hi <= lo) continue;
-      copy_rect_to_plane<T>(inf + k.so + (int64_t)(z - k.qz) * k.sPl + (int64_t)(lo - k.qy) * k.sP0, k.sP0, hi - lo,
-                            k.lx, lo - y0, k.qx, lds, ld, posx, lane, 64);
+      copy_rect_to_plane<T>(inf + k.so + (int64_t)(z - k.qz) * k.sPl, k.sP0, k.ly, k.lx, k.qy, k.qx, lds, ld, posx,
+                            lane, 64);
     }
     return;
   }
-  const cx<T>* src = reinterpret_cast<const cx<T>*>(a.in[f] + bx.foff + ((int64_t)z * Py + y0) * Px);
+  const cx<T>* src = reinterpret_cast<const cx<T>*>(a.in[f] + bx.foff + (int64_t)z * Py * Px);
   if ((Nh & 1) == 0 && (reinterpret_cast<uintptr_t>(src) % sizeof(Pair<cx<T>>)) == 0) {
     // two neighbouring complex values per access (rows of even length)
     const Pair<cx<T>>* src2 = reinterpret_cast<const Pair<cx<T>>*>(src);
-    copy_grid<4, Pair<cx<T>>>(y1 - y0, Nh >> 1, tid, nt, [&](int i, int, int) { return src2[i]; },
+    copy_grid<4, Pair<cx<T>>>(Py, Nh >> 1, tid, nt, [&](int i, int, int) { return src2[i]; },
                               [&](int, int y, int x2, Pair<cx<T>> v) {
                                 cx<T>* row = lds + y * ld;
                                 row[posx[2 * x2]] = v.a;
                                 row[posx[2 * x2 + 1]] = v.b;
                               });
   } else {
-    copy_grid<8, cx<T>>(y1 - y0, Nh, tid, nt, [&](int i, int, int) { return src[i]; },
+    copy_grid<8, cx<T>>(Py, Nh, tid, nt, [&](int i, int, int) { return src[i]; },
                         [&](int, int y, int x, cx<T> v) { lds[y * ld + posx[x]] = v; });
   }
 }
@@ -598,7 +590,7 @@ PSATD_HD void body_fwd_xy(const FwdArgs<T>& a, int item, int tid, int nt, cx<T>*
   // together with the three twiddle tables
   for (int i = tid; i < Nh + Py + Px; i += nt)  // twx, twy, twr are contiguous
     twx[i] = i < Nh ? gtx[i] : (i < Nh + Py ? gty[i - Nh] : gtr[i - Nh - Py]);
-  load_rows(a, rec, bx, f, 0, Py, lds, posx, tid, nt);
+  load_plane(a, rec, bx, f, lds, posx, tid, nt);
   bar();
   eng.template dit<-1, MAXR>(lds, Py, ld, 1, plx, twx, tid, nt, bar);
   pair_pass_rows<true>(lds, Py, ld, Nh, twr, tid, nt);

@@ -34,7 +34,7 @@ struct DevPlan {
   const FillPiece* fillp;    // guard fill: pieces with offsets and pitches
   const int32_t* itemsG;     // guard fill: prefix over pieces of their z extent
   const int32_t* pieceOf;    // guard fill: item -> piece
-  int32_t npiece, nG;
+  int32_t nG;
   const int32_t* push_off;
   int32_t fuse;              // 1: the inverse pass writes the E,B guard copies
   int32_t spl;               // BF16 terms of the matrix-core DFT stage (0: VALU only)
