@@ -181,10 +181,13 @@ psatd_status psatd_field_layout(psatd_plan_t plan, int32_t s, int64_t padded_n[3
 
 /*
  * Workspace: device scratch for the half-spectrum intermediates.  psatd_workspace_bytes
- * gives the size; psatd_set_workspace hands the plan caller-owned device memory (at
+ * gives the least size; psatd_set_workspace hands the plan caller-owned device memory (at
  * least that many bytes, 256-byte aligned; NULL/0 returns to plan-owned memory, which
  * the plan allocates at the first step).  The caller keeps the memory alive while the
- * plan uses it.
+ * plan uses it.  An unbatched plan lays its spectral planes out at pitches that spread
+ * them over the memory channels where the workspace has room for them (up to two 128-byte
+ * lines per plane more, less the planes that boxes share), and allocates that much for
+ * itself if it can; a batched plan takes psatd_workspace_bytes.
  */
 psatd_status psatd_workspace_bytes(psatd_plan_t plan, int64_t* bytes);
 psatd_status psatd_set_workspace(psatd_plan_t plan, void* dev, int64_t bytes);

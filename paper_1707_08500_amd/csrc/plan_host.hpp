@@ -2,7 +2,7 @@
 // validation of the decomposition (Sec. 3.2: boxes tiling the periodic grid,
 // guard cells per side), per-box padded extents, FFT radix schedules and their
 // twiddle / position tables, modified-wavenumber table layout (Sec. 3.1),
-// owner lookup, neighbour lists and the work lists of every phase.
+// owner lookup, guard pieces and the work lists of every phase.
 #pragma once
 #include <algorithm>
 #include <array>
@@ -54,6 +54,8 @@ struct HostTables {
   std::vector<SumRegion> sumr;    // deposited currents: regions of equal copies, the
   std::vector<SumCopy> sumc;      // copies, and the work list over their z-planes
   std::vector<int32_t> itemsS, regionOf;
+  // prefixes over the boxes: planes of 9 fields, z tiles of PB pencils, interior planes
+  // of 6 fields; padded and interior planes (the work lists of scatter and gather)
   std::vector<int32_t> itemsF, itemsU, itemsI, itemsP, itemsN;
   WorkLists lists;
   bool split = false;  // x/y pass split into x rows and y columns (large planes)
@@ -78,13 +80,13 @@ struct HostTables {
   std::vector<char> plan_z;  // per plan: 1 if it is a z schedule
   int spl = 0;        // BF16 terms of the matrix-core first stage (0: VALU form)
   int ntxy = 512;     // threads per work-group of the x/y passes
-  int ntu = 512;      // threads per work-group of the z-update (1024 for FP32 by default)
+  int ntu = 512;      // threads per work-group of the z-update
   bool zreg = false;  // the register z pass applies (FP32 VALU form, every padded z length scheduled)
   std::vector<int32_t> boxlds;     // dynamic LDS bytes of one x/y plane of each box
   std::vector<XyClass> xyc;       // x/y launch classes (empty: one launch for every box)
-  std::vector<int32_t> itemsXYC;  // their work lists
+  std::vector<int32_t> itemsXYC;  // their boxes and counts
   std::vector<ZClass> zcls;       // z launch classes (empty: one tile size for every box)
-  std::vector<int32_t> itemsZC;   // their work lists
+  std::vector<int32_t> itemsZC;   // their boxes and counts
   std::vector<ZGroup> zgroups;    // one per distinct padded z length
   std::vector<int32_t> itemsZR;   // their work lists, nsub + 1 prefix entries each
 };
@@ -579,7 +581,7 @@ struct Ring {
 // as does every box when share is false.
 // The x/y passes are bound by issue and memory together, so a plane not
 // transformed is time saved in full: 64^3 boxes with 16 guards transform 64 of
-// their 96 planes (forward pass 1.11 -> 0.72 ms FP32, 2.31 -> 1.50 ms FP64 on
+// their 96 planes (forward pass 1.11 -> 0.74 ms FP32, 2.31 -> 1.50 ms FP64 on
 // 64 boxes), 128^3 with 24 guards 128 of 176 (9.5 -> 6.4 ms on 64 boxes).
 inline std::vector<Ring> build_rings(const HostTables& h, std::vector<BoxD>& box, bool share) {
   std::vector<Ring> rings;

@@ -187,7 +187,7 @@ psatd_status device_list(psatd_plan_t p, std::vector<unsigned char>& bytes, cons
   if (e == hipSuccess) e = hipStreamSynchronize(p->cap_stream);
   if (e != hipSuccess) {
     (void)hipFree(fresh);
-    HIPCHK(p, e);
+    return fail(p, PSATD_E_HIP, std::string("work list upload: ") + hipGetErrorString(e));
   }
   p->lists.push_back({std::move(bytes), fresh});
   *dev = static_cast<const unsigned char*>(fresh);
@@ -301,7 +301,7 @@ hipError_t exchange_J(const DevPlan& d, int jmode, void* const J[3], hipStream_t
 // later steps of a run with J held fixed find it already consistent.
 // keep_j: an earlier step of the same call left J's spectra in the workspace
 // (the z pass overwrites E and B only), so the x/y passes transform 6 fields
-// instead of 9: 64 boxes of 64^3 with 16 guards, FP32 forward pass 0.72 -> 0.48
+// instead of 9: 64 boxes of 64^3 with 16 guards, FP32 forward pass 0.74 -> 0.49
 // ms.  A batched workspace holds one batch at a time and keeps nothing.
 // last: the run's last step.  With the pulled E,B exchange the guard copies
 // are refreshed only then (every forward pass of the run reads guard cells

@@ -139,10 +139,10 @@ constexpr int kMaxZGroups = 8;
 
 // A launch class of the x/y passes: the boxes whose padded planes fit the
 // same number of times into a compute unit's LDS, run with their own group
-// size and dynamic LDS.  Its work lists are prefixes over all boxes (zero for
-// the boxes of other classes) at the given offsets of one table: planes of the
-// 9 fields (F), of one field (P), interior planes of the 6 outputs (I) and of
-// one output (N), with their totals.
+// size and dynamic LDS.  Its counts are prefixes over all boxes (zero for the
+// boxes of other classes, which is how its boxes are told) at the given offsets
+// of one table: planes of the 9 fields (F), of one field (P), interior planes of
+// the 6 outputs (I) and of one output (N), with their totals.
 struct XyClass {
   int32_t nt, lds;
   int32_t F, nF, P, nP, I, nI, N, nN;
@@ -152,8 +152,8 @@ constexpr int kMaxXyClasses = 3;
 // A launch class of the z pass: the boxes whose z tile takes the same number
 // of pencils (FP32: the widest of 10, 8, 6 of which two tiles fit a compute
 // unit's LDS, else 4; FP64: 8 where one tile fits, else 4), launched with the
-// LDS of the class's longest padded z.  Work list: a prefix over all boxes at
-// offset U of one table.
+// LDS of the class's longest padded z.  Its tiles are counted by a prefix over all
+// boxes (zero for the others) at offset U of one table.
 struct ZClass {
   int32_t PB, lds, U, nU;
 };
@@ -885,8 +885,8 @@ PSATD_HD void stage_tile(const BoxD& bx, const cx<T>* src, int64_t sbias, int q0
 // stores straight from the last stage's butterflies measured 1.0 -> 1.5 ms (64 boxes
 // of 96^3 padded, FP32).  Issue-bound (65 % of the time is VALU busy); with the
 // loads and pairs as here 1.03 -> 0.90 ms, FP64 2.32 -> 2.08 ms, 8 boxes of 176^3 in
-// FP64 2.44 -> 2.03 ms; the pairs in the matrix-core forms 0.220 -> 0.211 ms on 8
-// boxes of 96^3.
+// FP64 2.44 -> 2.03 ms; the matrix-core forms, with the pairs and what mfma_dft.hpp
+// says of its stage, 0.220 -> 0.161 ms on 8 boxes of 96^3.
 template <typename T, int PB, bool INC, int MAXR, class Bar, class Eng = FftValu>
 PSATD_HD void body_z_update(const UpdArgs<T>& a, int item, int tid, int nt, cx<T>* lds, Bar bar, Eng eng = Eng{}) {
   constexpr bool VALU = std::is_same<Eng, FftValu>::value;
