@@ -60,7 +60,7 @@ void* scratch_of(int device) {
 // one per distinct list that its settings have asked for.
 struct ListCopy {
   std::vector<unsigned char> bytes;
-  void* dev;
+  void* dev = nullptr;
 };
 
 // Allocations and synchronous copies are refused to a thread while a capture in
@@ -172,25 +172,20 @@ psatd_status ensure_workspace(psatd_plan_t p) {
   return PSATD_OK;
 }
 
-// The device copy of a list: the one the plan has, or a new one.
+// The device copy of a list: the one the plan has, or a new one, whose upload is
+// on its way on cap_stream.
 psatd_status device_list(psatd_plan_t p, std::vector<unsigned char>& bytes, const unsigned char** dev) {
   for (const ListCopy& c : p->lists)
     if (c.bytes == bytes) {
       *dev = static_cast<const unsigned char*>(c.dev);
       return PSATD_OK;
     }
-  p->lists.reserve(p->lists.size() + 1);
-  const RelaxedCapture relaxed;
-  void* fresh = nullptr;
-  HIPCHK(p, hipMalloc(&fresh, bytes.size()));
-  hipError_t e = hipMemcpyAsync(fresh, bytes.data(), bytes.size(), hipMemcpyHostToDevice, p->cap_stream);
-  if (e == hipSuccess) e = hipStreamSynchronize(p->cap_stream);
-  if (e != hipSuccess) {
-    (void)hipFree(fresh);
-    return fail(p, PSATD_E_HIP, std::string("work list upload: ") + hipGetErrorString(e));
-  }
-  p->lists.push_back({std::move(bytes), fresh});
-  *dev = static_cast<const unsigned char*>(fresh);
+  p->lists.emplace_back();
+  ListCopy& c = p->lists.back();
+  c.bytes.swap(bytes);
+  HIPCHK(p, hipMalloc(&c.dev, c.bytes.size()));
+  HIPCHK(p, hipMemcpyAsync(c.dev, c.bytes.data(), c.bytes.size(), hipMemcpyHostToDevice, p->cap_stream));
+  *dev = static_cast<const unsigned char*>(c.dev);
   return PSATD_OK;
 }
 
@@ -203,6 +198,8 @@ psatd_status upload_lists(psatd_plan_t p) {
   DevPlan& d = p->dp;
   WorkLists was;
   std::swap(was, h.lists);
+  const size_t had = p->lists.size();
+  const RelaxedCapture relaxed;
   psatd_status st = PSATD_OK;
   size_t off[5];
   const unsigned char *base = nullptr, *tiles = nullptr;
@@ -228,7 +225,14 @@ psatd_status upload_lists(psatd_plan_t p) {
   } catch (...) {
     st = fail(p, PSATD_E_NOMEM, "host allocation failed");
   }
+  if (p->lists.size() > had) {
+    const hipError_t e = hipStreamSynchronize(p->cap_stream);
+    if (st == PSATD_OK && e != hipSuccess)
+      st = fail(p, PSATD_E_HIP, std::string("work list upload: ") + hipGetErrorString(e));
+  }
   if (st != PSATD_OK) {
+    for (; p->lists.size() > had; p->lists.pop_back())
+      if (p->lists.back().dev) (void)hipFree(p->lists.back().dev);
     std::swap(was, h.lists);
     return st;
   }

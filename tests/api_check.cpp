@@ -315,14 +315,15 @@ const Knob kListKnobs[] = {{PSATD_TUNE_Z_PENCILS, 4}, {PSATD_TUNE_SPLIT_XY, 1}, 
 // A knob whose lists cannot be allocated or copied to the device leaves the plan as it was.
 void check_failures(int prec) {
   for (const Knob& k : kListKnobs)
-    for (int copy = 0; copy < 2; ++copy) {
+    for (int which = 0; which < 4; ++which) {  // the first or the second allocation or copy
+      const int copy = which & 1, nth = which >> 1;
       psatd_plan_t p = cubes(48, 2, 8, prec);
       // lists shorter than any that the knobs make, so that stale ones show
       CHECK(p && psatd_set_tuning(p, PSATD_TUNE_Z_PENCILS, 8) == PSATD_OK, "failures: plan");
       const std::string before = step(p);
       const std::vector<int32_t> was = knobs(p);
       CHECK(ok(before), "failures: %s", before.c_str());
-      (copy ? fake::copies_left : fake::mallocs_left) = 0;
+      (copy ? fake::copies_left : fake::mallocs_left) = nth;
       const psatd_status st = psatd_set_tuning(p, k.key, k.value);
       const bool tried = (copy ? fake::copies_left : fake::mallocs_left) < 0;
       fake::mallocs_left = fake::copies_left = -1;
